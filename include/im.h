@@ -143,6 +143,11 @@ int im_workspace_destroy(im_workspace *ws);
  *     add up (a large search's levels spread over more workgroups): 1, 2, 4
  *     or 8, or 0 (default) for the most of 8, 4, 2 whose searches fit the
  *     slots (IM_OPT_MAX_SLOTS).
+ *   The reverse decrements run as searches from up to 64 sources of one
+ *   snapshot wherever the sparse lists are on and the round's (node,
+ *   snapshot) pairs fit 32-bit positions and the device; otherwise
+ *   (im_select_noalloc among them) through the three engine tiers from
+ *   sources packed by snapshot, which the next two options schedule.
  *   IM_OPT_REV_SPLIT: every reverse task that reaches the last engine tier
  *     runs as this many tasks (1, default, 2 or 4), each with the sources of
  *     one group of the word's snapshot bits, whose decrements add up (a

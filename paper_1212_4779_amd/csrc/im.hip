@@ -32,6 +32,7 @@
 
 #include "im.h"
 #include "im_bfs.h"
+#include "im_rev.h"
 #include "im_host.h"
 #include "im_mlp.h"
 
@@ -751,6 +752,7 @@ struct FwdArgs {
     // snapshot of the word ([W][64], zero on entry); pairs covered in several
     // snapshots are listed in mlist[w][0 .. mcnt[w])
     uint32_t *bcnt, *mcnt, *mlist;
+    // mcnt = nullptr: bcnt counts every newly covered (node, snapshot) pair instead
     const unsigned long long *key;   // keys of this round, one per instance
     uint32_t t;
     Batch b;
@@ -1099,9 +1101,11 @@ __global__ __launch_bounds__(FWD_NT) void k_forward_coop(FwdArgs a)
             trav += (uint64_t)__popcll(b) * dg;
             r = atomicAdd(&wcnt[w], 1u);
             if (pack) {
-                multi = __popcll(b) != 1;
+                multi = a.mcnt && __popcll(b) != 1;
                 if (multi) rm = atomicAdd(&wmc[w], 1u);
-                else atomicAdd(&L.pk[w * 64 + (uint32_t)__ffsll((unsigned long long)b) - 1], 1u);
+                else
+                    for (; b; b &= b - 1)
+                        atomicAdd(&L.pk[w * 64 + (uint32_t)__ffsll((unsigned long long)b) - 1], 1u);
             }
         }
         __syncthreads();
@@ -1182,11 +1186,12 @@ __global__ __launch_bounds__(FWB_NT) void k_forward_block(FwdArgs a)
             relax += dg;
             trav += (uint64_t)__popcll(b) * dg;
             if (pack) {
-                multi = __popcll(b) != 1;
-                if (!multi) atomicAdd(&pk[__ffsll((unsigned long long)b) - 1], 1u);
+                multi = a.mcnt && __popcll(b) != 1;
+                if (!multi)
+                    for (; b; b &= b - 1) atomicAdd(&pk[__ffsll((unsigned long long)b) - 1], 1u);
             }
         }
-        if (pack) {
+        if (pack && a.mcnt) {
             const uint32_t p = wave_append(multi, &a.mcnt[w]);
             if (multi) a.mlist[off + p] = x;
         }
@@ -1336,6 +1341,12 @@ struct im_workspace {
     uint32_t *pk = nullptr;    // packing counters: bcnt, bcur [64][64], gcnt, mcnt [64]
     uint32_t *boff = nullptr;  // [64][64]
     uint32_t *plist = nullptr, *mlist = nullptr;  // [W][n]
+    // reverse searches of one snapshot's sources (im_rev.h); rv_on: this call's
+    // buffers are in place
+    bool rv_on = false;
+    uint64_t cap_rv_src = 0, cap_rv_bins = 0;
+    uint32_t *rv_src = nullptr, *rv_q = nullptr, *rv_cnt = nullptr, *rv_cur = nullptr;
+    uint2 *rv_tasks = nullptr;           // its length follows the bin cursors
     unsigned fwd_grid = 0;      // co-resident workgroups of the cooperative forward search
     unsigned fwd_per_word = 16; // forward-search workgroups per snapshot word
     unsigned long long *keys = nullptr;
@@ -1566,6 +1577,7 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
     dfree(ws->cnt); dfree(ws->scan_sums); dfree(ws->mask_out); dfree(ws->mask_in);
     dfree(ws->gain); dfree(ws->sel); dfree(ws->covered); dfree(ws->newly);
     dfree(ws->fpend); dfree(ws->fqa); dfree(ws->fqb); dfree(ws->fvis); dfree(ws->bqa); dfree(ws->bqb); dfree(ws->fctr);
+    dfree(ws->rv_src); dfree(ws->rv_q); dfree(ws->rv_cnt); dfree(ws->rv_cur); dfree(ws->rv_tasks);
     dfree(ws->pk); dfree(ws->boff); dfree(ws->plist); dfree(ws->mlist);
     dfree(ws->tnodes); dfree(ws->tcounts); dfree(ws->keys); dfree(ws->ovf_q); dfree(ws->ovf_q2); dfree(ws->ctrs);
     dfree(ws->b_reach);
@@ -1717,6 +1729,32 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
         ws->cap_k = ck;
     }
     return IM_OK;
+}
+
+// Buffers of the reverse searches by snapshot: `pairs` (node, snapshot) pairs
+// (n R, summed over a batch's instances) can be newly covered in one round.
+// Without the sparse lists the searches would read every arc's masks for a
+// single bit, and past 2^32 pairs the source positions do not fit 32 bits:
+// such calls, and those whose buffers do not fit the device, keep the packed
+// snapshots of im_bfs.h.
+static void reserve_rev(im_workspace *ws, uint64_t pairs, uint32_t W)
+{
+    ws->rv_on = false;
+    const uint64_t bins = (uint64_t)ws->batch.count * W * 64;
+    if (!ws->sparse || t_arena || pairs >= 0xFFFFFFFFull || bins >= 0x40000000ull) return;
+    if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins) {
+        const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
+        const uint64_t ct = cs / 64 + cb;   // at most one partial task per bin
+        ws->cap_rv_src = ws->cap_rv_bins = 0;
+        if (dalloc(&ws->rv_src, cs) || dalloc(&ws->rv_tasks, ct) || dalloc(&ws->rv_q, ct) ||
+            dalloc(&ws->rv_cnt, cb) || dalloc(&ws->rv_cur, cb + 1)) {
+            dfree(ws->rv_src); dfree(ws->rv_tasks); dfree(ws->rv_q); dfree(ws->rv_cnt); dfree(ws->rv_cur);
+            return;
+        }
+        ws->cap_rv_src = cs;
+        ws->cap_rv_bins = cb;
+    }
+    ws->rv_on = true;
 }
 
 // ---------------------------------------------------------------------------
@@ -2243,6 +2281,63 @@ static int launch_forward(FwdArgs f, im_workspace *ws, bool single, hipStream_t 
     return IM_OK;
 }
 
+// A6: the reverse searches of one round by snapshot (im_rev.h). A table entry
+// takes 24 bytes, so three 2,048-entry workgroups share a CU; they hold every
+// task of the uniform-IC and NetHEPT-shaped graphs but a few. 1,024 entries
+// (five per CU) measured the same there and slower on weighted-cascade graphs
+// of 60,000 nodes (27 against 23 ms), whose tasks visit about 1,900 nodes.
+// Against packed snapshots, reverse steps of a selection: 10^6 nodes, p =
+// 0.01, R = 256: 22 -> 5.3 ms; weighted cascade, 15,000 nodes: 13.2 -> 3.9 ms,
+// 60,000 nodes: 157 -> 23 ms; 16 uneven instances: 177 -> 7.4 ms.
+constexpr int REVA_NT = 256, REVA_CS = 2048, REVA_LIM = 1640;
+constexpr int REVB_NT = 512, REVB_CS = 4096, REVB_LIM = 3200;
+
+static void rev_search(const im_graph *g, uint32_t R, im_workspace *ws, uint32_t *ctr,
+                       const unsigned long long *key, hipStream_t s)
+{
+    const uint32_t n = g->n, W = (R + 63) / 64, nbins = ws->batch.count * W * 64;
+    uint32_t *ntasks = ws->rv_cur + nbins;
+    {
+        PhaseTimer pt(ws, IM_PH_PACK, s);
+        const dim3 grid(grid_for(n, 256, 64), W);
+        if (ws->batch.count > 1)
+            k_rev_count<<<grid, 256, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, W,
+                                             ws->batch.node_inst, ws->rv_cnt);
+        k_rev_plan<<<1, RVP_NT, 0, s>>>(ws->rv_cnt, ws->rv_cur, nbins, W, ws->rv_tasks, ntasks, key,
+                                        ws->batch.count == 1 ? ws->aff_gain : 0ull);
+        k_rev_fill<<<grid, 256, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, W,
+                                        ws->batch.node_inst, ws->rv_cur, ws->rv_src);
+    }
+    RevArgs a;
+    a.row = ws->in_row; a.col = ws->in_col; a.mask = ws->mask_in; a.m = g->m;
+    a.n = n; a.W = W;
+    a.hub = hub_lists(ws, 1);
+    a.sp = sparse_lists(ws, 1);
+    a.node_inst = ws->batch.node_inst; a.inst_off = ws->batch.node_off;
+    a.src = ws->rv_src; a.tasks = ws->rv_tasks; a.ntasks = ntasks;
+    a.b_reach = ws->b_reach; a.b_qa = ws->b_qa; a.b_qb = ws->b_qb; a.b_vis = ws->b_vis;
+    a.slot_n = ws->slots_n;
+    a.gain = ws->gain;
+    a.stats = ws->stats;
+    a.in_q = nullptr; a.in_n = nullptr; a.out_q = ws->rv_q; a.out_n = ctr + 1; a.grab = ctr + 0;
+    a.tier = 1;
+    {
+        PhaseTimer pt(ws, IM_PH_REV_T1, s);
+        auto k1 = k_rev_search<REVA_NT, REVA_CS, REVA_LIM, false>;
+        static const unsigned g1 = per_cu(k1, REVA_NT);
+        k1<<<(unsigned)ws->num_cu * g1, REVA_NT, 0, s>>>(a);
+    }
+    a.in_q = ws->rv_q; a.in_n = ctr + 1; a.out_q = nullptr; a.out_n = nullptr; a.grab = ctr + 2;
+    a.tier = 2;
+    {
+        PhaseTimer pt(ws, IM_PH_REV_T2, s);
+        auto k2 = k_rev_search<REVB_NT, REVB_CS, REVB_LIM, true>;
+        static const unsigned g2 = per_cu(k2, REVB_NT);
+        // one dense slot per workgroup
+        k2<<<std::min<unsigned>((unsigned)ws->num_cu * g2, ws->slots), REVB_NT, 0, s>>>(a);
+    }
+}
+
 // A4-A6: one greedy round
 static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *seeds_out,
                         uint64_t *gains_out, im_workspace *ws, uint32_t *ctr, hipStream_t s)
@@ -2253,7 +2348,8 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
         // a single graph: few workgroups, so that few atomics meet on the key
         k_argmax<<<grid_for(n, 256, ws->batch.count == 1 ? 256 : 2048), 256, 0, s>>>(ws->gain, ws->sel, n,
                                                          ws->keys + (uint64_t)t * ws->batch.count,
-                                                         ws->batch, t, ws->pk, (uint32_t)PK_ZERO);
+                                                         ws->batch, t, ws->pk,
+                                                         ws->rv_on ? 0u : (uint32_t)PK_ZERO);
     }
 
     FwdArgs f;
@@ -2269,6 +2365,7 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
     uint32_t *bcnt = ws->pk, *bcur = ws->pk + 64 * 64, *gcnt = ws->pk + 2 * 64 * 64,
              *mcnt = gcnt + 64;
     f.bcnt = bcnt; f.mcnt = mcnt; f.mlist = ws->mlist;
+    if (ws->rv_on) { f.bcnt = ws->batch.count == 1 ? ws->rv_cnt : nullptr; f.mcnt = nullptr; }
     f.key = ws->keys + (uint64_t)t * ws->batch.count; f.t = t; f.b = ws->batch;
     f.seeds_out = seeds_out; f.gains_out = gains_out; f.sel = ws->sel;
     f.stats = ws->stats;
@@ -2278,24 +2375,28 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
         if (rc) return rc;
     }
 
-    {
-        // the forward search counted the single-bit sources per bit and
-        // listed the others
-        PhaseTimer pt(ws, IM_PH_PACK, s);
-        dim3 pg(grid_for(n, PK_NT, 64), W);
-        const uint64_t aff = ws->batch.count == 1 ? ws->aff_gain : 0ull;
-        k_pack_fill<<<pg, PK_NT, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, bcnt, ws->boff,
-                                         gcnt, bcur, ws->plist, mcnt, ws->keys + (uint64_t)t * ws->batch.count,
-                                         aff);
+    if (ws->rv_on) {
+        rev_search(g, R, ws, ctr, ws->keys + (uint64_t)t * ws->batch.count, s);
+    } else {
+        {
+            // the forward search counted the single-bit sources per bit and
+            // listed the others
+            PhaseTimer pt(ws, IM_PH_PACK, s);
+            dim3 pg(grid_for(n, PK_NT, 64), W);
+            const uint64_t aff = ws->batch.count == 1 ? ws->aff_gain : 0ull;
+            k_pack_fill<<<pg, PK_NT, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, bcnt, ws->boff,
+                                             gcnt, bcur, ws->plist, mcnt, ws->keys + (uint64_t)t * ws->batch.count,
+                                             aff);
+        }
+        BfsArgs a = bfs_args(ws, ws->in_row, ws->in_col, ws->mask_in, g->m, n, R, W);
+        a.gcnt = gcnt; a.mcnt = mcnt; a.bcnt = bcnt; a.boff = ws->boff;
+        a.plist = ws->plist; a.mlist = ws->mlist; a.tbits = ws->newly;
+        a.hub = hub_lists(ws, 1);
+        a.sp = sparse_lists(ws, 1);
+        a.pass = PASS_REV;
+        a.st_trav = ST_TRAV_REV;
+        run_tiers<MODE_DEC, false>(a, ws, ctr, IM_PH_REV_T0, s);
     }
-    BfsArgs a = bfs_args(ws, ws->in_row, ws->in_col, ws->mask_in, g->m, n, R, W);
-    a.gcnt = gcnt; a.mcnt = mcnt; a.bcnt = bcnt; a.boff = ws->boff;
-    a.plist = ws->plist; a.mlist = ws->mlist; a.tbits = ws->newly;
-    a.hub = hub_lists(ws, 1);
-    a.sp = sparse_lists(ws, 1);
-    a.pass = PASS_REV;
-    a.st_trav = ST_TRAV_REV;
-    run_tiers<MODE_DEC, false>(a, ws, ctr, IM_PH_REV_T0, s);
     if (ws->batch.count == 1 && ws->aff_gain) affected_update(g, R, t, ws, s);
     {
         PhaseTimer pt(ws, IM_PH_CLEAR, s);
@@ -2305,10 +2406,12 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
 }
 
 // workspace growth and input validation (synchronous)
+// (rounds: the call runs greedy rounds of the dynamic update)
 static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_workspace *ws,
-                             hipStream_t s)
+                             hipStream_t s, bool rounds = true)
 {
     int rc;
+    ws->rv_on = false;
     if ((rc = ws_reserve(ws, g->n, g->m, (R + 63) / 64, k, g->n))) return rc;
     if (ws->aff_gain && ws->batch.count == 1) {
         const uint64_t nW = (uint64_t)g->n * ((R + 63) / 64);
@@ -2336,6 +2439,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
             ws->cap_aff_k = k + 1;
         }
     }
+    if (rounds && k) reserve_rev(ws, (uint64_t)g->n * R, (R + 63) / 64);
     if ((rc = validate(g, ws, s, ws->row32))) return rc;
     if (ws->live_edge == 1) {
         if (ws->batch.count > 1) return im_fail(IM_EINVAL, "linear-threshold snapshots apply to single graphs only");
@@ -2383,6 +2487,7 @@ static int enqueue_prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_
     fill<uint32_t>(ws->gain, n, 0u, s);
     fill<uint8_t>(ws->sel, n, (uint8_t)0, s);
     fill<uint64_t>(ws->covered, (uint64_t)n * W, 0ull, s);
+    if (ws->rv_on) fill<uint32_t>(ws->rv_cnt, (uint64_t)ws->batch.count * W * 64, 0u, s);
     const bool rev = need == PREP_REVERSE || ws->live_edge == 1;
     if (rev || need == PREP_INDEG) build_reverse(g, ws, s, !rev);
     build_masks(g, R, seed, ws, ws->mask_out, rev, s);
@@ -2405,7 +2510,7 @@ static int prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_t k, im_
                    hipStream_t s, int need = PREP_REVERSE)
 {
     int rc;
-    if ((rc = check_and_reserve(g, R, k, ws, s))) return rc;
+    if ((rc = check_and_reserve(g, R, k, ws, s, need == PREP_REVERSE))) return rc;
     return enqueue_prepare(g, R, seed, k, ws, s, need);
 }
 
@@ -4128,7 +4233,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
                        hipStream_t s, im_graph *mg, uint32_t *Rmax_out, uint32_t *kmax_out)
 {
     int rc;
-    uint64_t N = 0, M = 0, K = 0;
+    uint64_t N = 0, M = 0, K = 0, pairs = 0;
     uint32_t Rmax = 0, kmax = 0, nmax = 0;
     if (ws->live_edge || ws->pair_coins)
         return im_fail(IM_EINVAL, "batches draw one coin per stored arc (independent cascade)");
@@ -4140,6 +4245,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
         N += inst[i].g.n;
         M += inst[i].g.m;
         K += inst[i].k;
+        pairs += (uint64_t)inst[i].g.n * inst[i].R;
         Rmax = std::max(Rmax, inst[i].R);
         kmax = std::max(kmax, inst[i].k);
     }
@@ -4149,6 +4255,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     const uint32_t W = (Rmax + 63) / 64;
     ws->batch.count = count;  // sizes the per-round key arrays
     rc = ws_reserve(ws, (uint32_t)N, M, W, kmax, nmax);
+    if (!rc) reserve_rev(ws, pairs, W);
     ws->batch.count = 1;
     if (!rc) rc = reserve_batch(ws, count, N, M);
     if (rc) return rc;
