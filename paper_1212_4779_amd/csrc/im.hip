@@ -33,6 +33,7 @@
 #include "im.h"
 #include "im_bfs.h"
 #include "im_rev.h"
+#include "im_lt.h"
 #include "im_host.h"
 #include "im_mlp.h"
 
@@ -1410,9 +1411,15 @@ struct im_workspace {
     // linear-threshold snapshots
     int live_edge = 0;                   // 0: independent cascade, 1: linear threshold
     uint64_t *lt_start = nullptr;        // [m] start of each in-arc's draw interval
-    uint32_t *lt_task = nullptr;         // [n+1] prefix of the large rows' chunk counts
+    uint32_t *lt_task = nullptr;         // [n+1] the large in-rows, and their number
     uint64_t cap_lt_m = 0;
     uint32_t cap_lt_n = 0;
+    // ... and their forests (im_lt.h), for the dynamic update; lt_on: this
+    // call's buffers are in place
+    bool lt_on = false;
+    uint64_t cap_lt_nR = 0, cap_lt_nW = 0;
+    uint32_t *lt_par = nullptr, *lt_cur = nullptr, *lt_ord = nullptr, *lt_stamp = nullptr;
+    unsigned long long *lt_sc = nullptr, *lt_pos = nullptr;
     // undirected graphs: one coin per pair (directed engines), component method state
     int pair_coins = 0;
     uint32_t *pair = nullptr;
@@ -1601,6 +1608,7 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
     ws->und = nullptr;
     dfree(ws->pair);
     dfree(ws->lt_start); dfree(ws->lt_task);
+    dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord); dfree(ws->lt_stamp); dfree(ws->lt_sc); dfree(ws->lt_pos);
     dfree(ws->a_reach); dfree(ws->a_pend); dfree(ws->a_qa); dfree(ws->a_qb); dfree(ws->a_vis);
     dfree(ws->a_mark); dfree(ws->a_list); dfree(ws->a_cnt); dfree(ws->a_ctrs);
     dfree(ws->v_row32); dfree(ws->v_mask); dfree(ws->v_reach); dfree(ws->v_pend); dfree(ws->v_cov);
@@ -1757,6 +1765,27 @@ static void reserve_rev(im_workspace *ws, uint64_t pairs, uint32_t W)
     ws->rv_on = true;
 }
 
+// Buffers of the linear-threshold forests: 28 bytes per (node, snapshot).
+// Calls whose forests do not fit the device keep the general engines.
+static void reserve_lt(im_workspace *ws, uint64_t nR, uint64_t nW)
+{
+    ws->lt_on = false;
+    if (t_arena) return;
+    if (nR > ws->cap_lt_nR || nW > ws->cap_lt_nW) {
+        const uint64_t cR = std::max(nR, ws->cap_lt_nR), cW = std::max(nW, ws->cap_lt_nW);
+        ws->cap_lt_nR = ws->cap_lt_nW = 0;
+        if (dalloc(&ws->lt_par, cR) || dalloc(&ws->lt_cur, cR) || dalloc(&ws->lt_ord, cR) ||
+            dalloc(&ws->lt_sc, cR) || dalloc(&ws->lt_pos, cR) || dalloc(&ws->lt_stamp, cW)) {
+            dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord);
+            dfree(ws->lt_sc); dfree(ws->lt_pos); dfree(ws->lt_stamp);
+            return;
+        }
+        ws->cap_lt_nR = cR;
+        ws->cap_lt_nW = cW;
+    }
+    ws->lt_on = true;
+}
+
 // ---------------------------------------------------------------------------
 // host-side steps
 // ---------------------------------------------------------------------------
@@ -1828,71 +1857,24 @@ static void build_reverse(const im_graph *g, im_workspace *ws, hipStream_t s, bo
 // (b_e = prob[e]; a part past 2^32 is never drawn); the node's draw for
 // snapshot r, the top 32 bits of output r+1 of SplitMix64 seeded with output
 // v+1 of SplitMix64(seed), keeps the arc whose sub-interval holds it.
-// The reverse CSR lists in-arcs in no particular order, so each in-arc's
-// interval start is the sum of t over the in-arcs of its row with a smaller
-// arc id: one thread per row for rows of up to LT_SMALL in-arcs, one
-// workgroup per LT_SMALL-entry chunk (the row streamed through LDS) above.
+// The reverse CSR lists in-arcs in no particular order: lt_rows sorts every
+// in-row by arc id and adds up the lengths (im_lt.h). Adding up, for every
+// in-arc, the lengths of the smaller ids of its row instead took time with
+// the square of the in-degree: 8.8 ms on the 15,000-node graph, whose longest
+// rows set it.
 // ---------------------------------------------------------------------------
-constexpr uint32_t LT_SMALL = 256;
-
-__device__ __forceinline__ uint64_t lt_len(const float *prob, uint32_t e)
+static void lt_rows(const im_graph *g, im_workspace *ws, hipStream_t s)
 {
-    return (uint64_t)((double)prob[e] * 4294967296.0);
-}
-
-__global__ __launch_bounds__(256) void k_lt_start_small(const uint32_t *in_row,
-                                                        const uint32_t *in2out, const float *prob,
-                                                        uint32_t n, uint64_t *start,
-                                                        uint32_t *chunks)
-{
-    for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < n; v += gridDim.x * 256) {
-        const uint32_t a = in_row[v], b = in_row[v + 1];
-        chunks[v] = b - a > LT_SMALL ? (b - a + LT_SMALL - 1) / LT_SMALL : 0u;
-        if (b - a > LT_SMALL) continue;
-        for (uint32_t j = a; j < b; j++) {
-            const uint32_t id = in2out[j];
-            uint64_t acc = 0;
-            for (uint32_t i = a; i < b; i++) {
-                const uint32_t o = in2out[i];
-                if (o < id) acc += lt_len(prob, o);
-            }
-            start[j] = acc;
-        }
-    }
-}
-
-// chunk tasks of the large rows: task t belongs to the row v with
-// pre[v] <= t < pre[v+1] (pre: exclusive prefix of the chunk counts, pre[n] = total)
-__global__ __launch_bounds__(LT_SMALL) void k_lt_start_large(const uint32_t *in_row,
-                                                             const uint32_t *in2out,
-                                                             const float *prob, uint32_t n,
-                                                             const uint32_t *pre, uint64_t *start)
-{
-    __shared__ uint32_t s_id[LT_SMALL];
-    __shared__ uint64_t s_len[LT_SMALL];
-    const uint32_t T = pre[n];
-    for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
-        uint32_t lo = 0, hi = n;   // largest v with pre[v] <= t
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (pre[mid] <= t) lo = mid; else hi = mid;
-        }
-        const uint32_t v = lo, a = in_row[v], b = in_row[v + 1];
-        const uint32_t j = a + (t - pre[v]) * LT_SMALL + threadIdx.x;
-        const uint32_t id = j < b ? in2out[j] : 0xFFFFFFFFu;
-        uint64_t acc = 0;
-        for (uint32_t c = a; c < b; c += LT_SMALL) {
-            const uint32_t i = c + threadIdx.x;
-            s_id[threadIdx.x] = i < b ? in2out[i] : 0xFFFFFFFFu;
-            s_len[threadIdx.x] = i < b ? lt_len(prob, in2out[i]) : 0ull;
-            __syncthreads();
-            const uint32_t lim = min(LT_SMALL, b - c);
-            for (uint32_t q = 0; q < lim; q++)
-                if (s_id[q] < id) acc += s_len[q];
-            __syncthreads();
-        }
-        if (j < b) start[j] = acc;
-    }
+    const uint32_t n = g->n;
+    uint32_t *nbig = ws->lt_task + n;
+    int passes = 1;
+    while (passes < 4 && (g->m >> (8 * passes))) passes++;
+    fill<uint32_t>(nbig, 1, 0u, s);
+    k_lt_sort_small<<<grid_for(n, 4), 256, 0, s>>>(ws->in_row, ws->in2out, ws->in_col, g->prob, n,
+                                                   ws->lt_start, ws->lt_task, nbig);
+    k_lt_sort_big<<<(unsigned)ws->num_cu * 4u, LTS_NT, 0, s>>>(ws->in_row, ws->in2out, ws->in_col,
+                                                              g->prob, ws->lt_start, ws->lt_task,
+                                                              nbig, passes);
 }
 
 // one wavefront per (node, word): lane r draws snapshot 64w + r, then every
@@ -1950,11 +1932,7 @@ static void build_masks(const im_graph *g, uint32_t R, uint64_t seed, im_workspa
         // linear threshold (the reverse CSR is built): interval starts, then masks
         PhaseTimer pt(ws, IM_PH_MASK_GEN, s);
         const uint32_t n = g->n;
-        k_lt_start_small<<<grid_for(n, 256), 256, 0, s>>>(ws->in_row, ws->in2out, g->prob, n,
-                                                          ws->lt_start, ws->cnt);
-        exclusive_scan(ws->cnt, ws->lt_task, (uint64_t)n + 1, ws->scan_sums, s);
-        k_lt_start_large<<<2048, LT_SMALL, 0, s>>>(ws->in_row, ws->in2out, g->prob, n,
-                                                   ws->lt_task, ws->lt_start);
+        lt_rows(g, ws, s);
         k_lt_masks<<<grid_for((uint64_t)n * W, 4, 16384), 256, 0, s>>>(
             ws->in_row, ws->in2out, g->prob, ws->lt_start, n, m, R, seed, mask_out, ws->mask_in);
         return;
@@ -2281,6 +2259,40 @@ static int launch_forward(FwdArgs f, im_workspace *ws, bool single, hipStream_t 
     return IM_OK;
 }
 
+// A3 on linear-threshold snapshots: the forests and the subtree sizes (im_lt.h).
+// Against the general engines (a selection, k = 50): 15,000 nodes, 59,000
+// arcs, R = 100; 200,000 nodes, 2*10^6 arcs, R = 256.
+static LtForest lt_forest(const im_graph *g, uint32_t R, im_workspace *ws)
+{
+    return LtForest{g->n, R, ws->lt_par, ws->lt_cur, ws->lt_ord, ws->lt_sc, ws->lt_pos};
+}
+
+static void lt_prepare(const im_graph *g, uint32_t R, uint64_t seed, im_workspace *ws, hipStream_t s)
+{
+    const uint32_t n = g->n, nb = (n + 255) / 256;
+    if (n == 0) return;
+    const LtForest f = lt_forest(g, R, ws);
+    fill<unsigned long long>(ws->lt_sc, (uint64_t)n * R, 1ull, s);
+    fill<uint32_t>(ws->lt_stamp, (uint64_t)n * ((R + 63) / 64), 0u, s);
+    {
+        PhaseTimer pt(ws, IM_PH_MASK_GEN, s);
+        lt_rows(g, ws, s);
+        k_lt_parent<<<dim3(nb, (R + LTP_R - 1) / LTP_R), 256, 0, s>>>(
+            ws->row32, ws->in_row, ws->in2out, ws->in_col, g->prob, ws->lt_start, seed, f);
+    }
+    {
+        PhaseTimer pt(ws, IM_PH_INIT_T0, s);
+        k_lt_up<<<dim3(nb, R), 256, 0, s>>>(f);
+        k_lt_cycle<<<dim3(nb, R), 256, 0, s>>>(f);
+    }
+    {
+        PhaseTimer pt(ws, IM_PH_INIT_T1, s);
+        k_lt_gain<<<dim3(nb, (R + LTG_R - 1) / LTG_R), 256, 0, s>>>(f, ws->gain, ws->stats);
+    }
+    PhaseTimer pt(ws, IM_PH_INIT_T2, s);
+    k_lt_order<<<R, LTO_NT, 0, s>>>(f);
+}
+
 // A6: the reverse searches of one round by snapshot (im_rev.h). A table entry
 // takes 24 bytes, so three 2,048-entry workgroups share a CU; they hold every
 // task of the uniform-IC and NetHEPT-shaped graphs but a few. 1,024 entries
@@ -2349,7 +2361,13 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
         k_argmax<<<grid_for(n, 256, ws->batch.count == 1 ? 256 : 2048), 256, 0, s>>>(ws->gain, ws->sel, n,
                                                          ws->keys + (uint64_t)t * ws->batch.count,
                                                          ws->batch, t, ws->pk,
-                                                         ws->rv_on ? 0u : (uint32_t)PK_ZERO);
+                                                         ws->rv_on || ws->lt_on ? 0u : (uint32_t)PK_ZERO);
+    }
+    if (ws->lt_on) {
+        PhaseTimer pt(ws, IM_PH_FORWARD, s);
+        k_lt_round<<<R, LTR_NT, 0, s>>>(lt_forest(g, R, ws), ws->row32, ws->in_row, ws->keys + t, t,
+                                        seeds_out, gains_out, ws->sel, ws->gain, ws->lt_stamp, ws->stats);
+        return IM_OK;
     }
 
     FwdArgs f;
@@ -2411,7 +2429,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
                              hipStream_t s, bool rounds = true)
 {
     int rc;
-    ws->rv_on = false;
+    ws->rv_on = ws->lt_on = false;
     if ((rc = ws_reserve(ws, g->n, g->m, (R + 63) / 64, k, g->n))) return rc;
     if (ws->aff_gain && ws->batch.count == 1) {
         const uint64_t nW = (uint64_t)g->n * ((R + 63) / 64);
@@ -2439,7 +2457,8 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
             ws->cap_aff_k = k + 1;
         }
     }
-    if (rounds && k) reserve_rev(ws, (uint64_t)g->n * R, (R + 63) / 64);
+    if (rounds && k && ws->live_edge == 1) reserve_lt(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64));
+    if (rounds && k && !ws->lt_on) reserve_rev(ws, (uint64_t)g->n * R, (R + 63) / 64);
     if ((rc = validate(g, ws, s, ws->row32))) return rc;
     if (ws->live_edge == 1) {
         if (ws->batch.count > 1) return im_fail(IM_EINVAL, "linear-threshold snapshots apply to single graphs only");
@@ -2489,6 +2508,13 @@ static int enqueue_prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_
     fill<uint64_t>(ws->covered, (uint64_t)n * W, 0ull, s);
     if (ws->rv_on) fill<uint32_t>(ws->rv_cnt, (uint64_t)ws->batch.count * W * 64, 0u, s);
     const bool rev = need == PREP_REVERSE || ws->live_edge == 1;
+    if (ws->lt_on) {
+        build_reverse(g, ws, s);
+        lt_prepare(g, R, seed, ws, s);
+        HIPCHK(hipGetLastError());
+        ws->last_stream = s;
+        return IM_OK;
+    }
     if (rev || need == PREP_INDEG) build_reverse(g, ws, s, !rev);
     build_masks(g, R, seed, ws, ws->mask_out, rev, s);
     {
@@ -4835,7 +4861,7 @@ extern "C" int im_autotune_lazy(const im_graph *g, uint32_t R, uint32_t k, uint6
             ws->lazy_engine = eng;
             float ms_min = -1.0f;
             for (int rep = 0; rep < 2 && !rc; rep++) {
-                if ((rc = check_and_reserve(g, R, kt, ws, s))) break;
+                if ((rc = check_and_reserve(g, R, kt, ws, s, false))) break;
                 if ((rc = (int)(hipEventRecord(e0, s) != hipSuccess ? IM_EHIP : IM_OK))) break;
                 rc = enqueue_prepare(g, R, seed, kt, ws, s, model ? PREP_INDEG : PREP_FORWARD);
                 if (!rc) rc = select_lazy(g, R, kt, B, model, sd, gd, ws, s);
