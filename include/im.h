@@ -72,6 +72,15 @@ int im_workspace_destroy(im_workspace *ws);
  *   IM_OPT_HUB_DEGREE: nodes with at least this many arcs (in the direction
  *     of a pass) are expanded through per-snapshot live lists instead of the
  *     snapshot masks; 0 disables the lists; otherwise >= 16. Default 256.
+ *   Rounds of the dynamic update run by snapshot -- a forward search per
+ *   snapshot, reverse searches from up to 64 sources of one snapshot --
+ *   wherever the sparse lists are on, IM_OPT_AFFECTED_GAIN is 0 and the call's
+ *   (node, snapshot) pairs fit 32-bit positions and the device; otherwise
+ *   (im_select_noalloc among them) by word, on the engines that
+ *   IM_OPT_COOP_GAIN, IM_OPT_FWD_GROUPS, IM_OPT_REV_SPLIT and
+ *   IM_OPT_REV_FIRST_TIER schedule. Linear-threshold rounds need no searches
+ *   (see IM_OPT_LIVE_EDGE); their engine counters (relax, reached, arcs_read)
+ *   stay 0.
  *   IM_OPT_COOP_GAIN: rounds whose seed gain (summed over snapshots) is at
  *     least this value run the forward search on a cooperative grid
  *     (IM_OPT_FWD_GROUPS workgroups per snapshot word); smaller rounds use
@@ -143,11 +152,6 @@ int im_workspace_destroy(im_workspace *ws);
  *     add up (a large search's levels spread over more workgroups): 1, 2, 4
  *     or 8, or 0 (default) for the most of 8, 4, 2 whose searches fit the
  *     slots (IM_OPT_MAX_SLOTS).
- *   The reverse decrements run as searches from up to 64 sources of one
- *   snapshot wherever the sparse lists are on and the round's (node,
- *   snapshot) pairs fit 32-bit positions and the device; otherwise
- *   (im_select_noalloc among them) through the three engine tiers from
- *   sources packed by snapshot, which the next two options schedule.
  *   IM_OPT_REV_SPLIT: every reverse task that reaches the last engine tier
  *     runs as this many tasks (1, default, 2 or 4), each with the sources of
  *     one group of the word's snapshot bits, whose decrements add up (a

@@ -753,7 +753,6 @@ struct FwdArgs {
     // snapshot of the word ([W][64], zero on entry); pairs covered in several
     // snapshots are listed in mlist[w][0 .. mcnt[w])
     uint32_t *bcnt, *mcnt, *mlist;
-    // mcnt = nullptr: bcnt counts every newly covered (node, snapshot) pair instead
     const unsigned long long *key;   // keys of this round, one per instance
     uint32_t t;
     Batch b;
@@ -1102,11 +1101,9 @@ __global__ __launch_bounds__(FWD_NT) void k_forward_coop(FwdArgs a)
             trav += (uint64_t)__popcll(b) * dg;
             r = atomicAdd(&wcnt[w], 1u);
             if (pack) {
-                multi = a.mcnt && __popcll(b) != 1;
+                multi = __popcll(b) != 1;
                 if (multi) rm = atomicAdd(&wmc[w], 1u);
-                else
-                    for (; b; b &= b - 1)
-                        atomicAdd(&L.pk[w * 64 + (uint32_t)__ffsll((unsigned long long)b) - 1], 1u);
+                else atomicAdd(&L.pk[w * 64 + (uint32_t)__ffsll((unsigned long long)b) - 1], 1u);
             }
         }
         __syncthreads();
@@ -1187,12 +1184,11 @@ __global__ __launch_bounds__(FWB_NT) void k_forward_block(FwdArgs a)
             relax += dg;
             trav += (uint64_t)__popcll(b) * dg;
             if (pack) {
-                multi = a.mcnt && __popcll(b) != 1;
-                if (!multi)
-                    for (; b; b &= b - 1) atomicAdd(&pk[__ffsll((unsigned long long)b) - 1], 1u);
+                multi = __popcll(b) != 1;
+                if (!multi) atomicAdd(&pk[__ffsll((unsigned long long)b) - 1], 1u);
             }
         }
-        if (pack && a.mcnt) {
+        if (pack) {
             const uint32_t p = wave_append(multi, &a.mcnt[w]);
             if (multi) a.mlist[off + p] = x;
         }
@@ -1342,24 +1338,23 @@ struct im_workspace {
     uint32_t *pk = nullptr;    // packing counters: bcnt, bcur [64][64], gcnt, mcnt [64]
     uint32_t *boff = nullptr;  // [64][64]
     uint32_t *plist = nullptr, *mlist = nullptr;  // [W][n]
-    // reverse searches of one snapshot's sources (im_rev.h); rv_on: this call's
-    // buffers are in place
+    // rounds by snapshot (im_rev.h); rv_on: this call's buffers are in place
     bool rv_on = false;
-    uint64_t cap_rv_src = 0, cap_rv_bins = 0;
-    uint32_t *rv_src = nullptr, *rv_q = nullptr, *rv_cnt = nullptr, *rv_cur = nullptr;
-    uint2 *rv_tasks = nullptr;           // its length follows the bin cursors
+    uint64_t cap_rv_src = 0, cap_rv_bins = 0, cap_rv_nW = 0;
+    uint32_t *rv_src = nullptr, *rv_q = nullptr, *rv_stamp = nullptr;
+    uint2 *rv_tasks = nullptr;
     unsigned fwd_grid = 0;      // co-resident workgroups of the cooperative forward search
     unsigned fwd_per_word = 16; // forward-search workgroups per snapshot word
     unsigned long long *keys = nullptr;
     uint64_t cap_keys = 0;
     // batches
-    Batch batch = {1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    Batch batch = {1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     uint32_t cap_count = 0;
     uint64_t cap_bn = 0, cap_bm = 0;
     uint32_t *b_node_inst = nullptr, *b_mcol = nullptr;
     float *b_mprob = nullptr;
     uint32_t *b_u32 = nullptr;          // R, k, kpre, node_off per instance
-    uint64_t *b_u64 = nullptr;          // arc_off, seed per instance
+    uint64_t *b_u64 = nullptr;          // arc_off, seed, pair_off per instance
     InstDesc *b_desc = nullptr;
     void *b_host = nullptr;             // pinned staging of the above
     uint32_t *ovf_q = nullptr, *ovf_q2 = nullptr;
@@ -1584,7 +1579,7 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
     dfree(ws->cnt); dfree(ws->scan_sums); dfree(ws->mask_out); dfree(ws->mask_in);
     dfree(ws->gain); dfree(ws->sel); dfree(ws->covered); dfree(ws->newly);
     dfree(ws->fpend); dfree(ws->fqa); dfree(ws->fqb); dfree(ws->fvis); dfree(ws->bqa); dfree(ws->bqb); dfree(ws->fctr);
-    dfree(ws->rv_src); dfree(ws->rv_q); dfree(ws->rv_cnt); dfree(ws->rv_cur); dfree(ws->rv_tasks);
+    dfree(ws->rv_src); dfree(ws->rv_q); dfree(ws->rv_stamp); dfree(ws->rv_tasks);
     dfree(ws->pk); dfree(ws->boff); dfree(ws->plist); dfree(ws->mlist);
     dfree(ws->tnodes); dfree(ws->tcounts); dfree(ws->keys); dfree(ws->ovf_q); dfree(ws->ovf_q2); dfree(ws->ctrs);
     dfree(ws->b_reach);
@@ -1739,28 +1734,30 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
     return IM_OK;
 }
 
-// Buffers of the reverse searches by snapshot: `pairs` (node, snapshot) pairs
-// (n R, summed over a batch's instances) can be newly covered in one round.
-// Without the sparse lists the searches would read every arc's masks for a
-// single bit, and past 2^32 pairs the source positions do not fit 32 bits:
-// such calls, and those whose buffers do not fit the device, keep the packed
-// snapshots of im_bfs.h.
-static void reserve_rev(im_workspace *ws, uint64_t pairs, uint32_t W)
+// Buffers of the rounds by snapshot: `pairs` (node, snapshot) pairs (n R,
+// summed over a batch's instances) can be newly covered in one round. Without
+// the sparse lists the searches would read every arc's masks for a single bit,
+// past 2^32 pairs the source positions do not fit 32 bits, and the
+// affected-set recompute takes the newly covered nodes by word: such calls,
+// and those whose buffers do not fit the device, run the rounds by word
+// (k_forward_coop and the three tiers of im_bfs.h).
+static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W)
 {
     ws->rv_on = false;
     const uint64_t bins = (uint64_t)ws->batch.count * W * 64;
-    if (!ws->sparse || t_arena || pairs >= 0xFFFFFFFFull || bins >= 0x40000000ull) return;
-    if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins) {
+    if (!ws->sparse || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins >= 0x40000000ull) return;
+    if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins || nW > ws->cap_rv_nW) {
         const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
-        const uint64_t ct = cs / 64 + cb;   // at most one partial task per bin
-        ws->cap_rv_src = ws->cap_rv_bins = 0;
+        const uint64_t ct = cs / 64 + cb, cw = std::max(nW, ws->cap_rv_nW);   // (one partial task per bin)
+        ws->cap_rv_src = ws->cap_rv_bins = ws->cap_rv_nW = 0;
         if (dalloc(&ws->rv_src, cs) || dalloc(&ws->rv_tasks, ct) || dalloc(&ws->rv_q, ct) ||
-            dalloc(&ws->rv_cnt, cb) || dalloc(&ws->rv_cur, cb + 1)) {
-            dfree(ws->rv_src); dfree(ws->rv_tasks); dfree(ws->rv_q); dfree(ws->rv_cnt); dfree(ws->rv_cur);
+            dalloc(&ws->rv_stamp, cw)) {
+            dfree(ws->rv_src); dfree(ws->rv_tasks); dfree(ws->rv_q); dfree(ws->rv_stamp);
             return;
         }
         ws->cap_rv_src = cs;
         ws->cap_rv_bins = cb;
+        ws->cap_rv_nW = cw;
     }
     ws->rv_on = true;
 }
@@ -2293,38 +2290,52 @@ static void lt_prepare(const im_graph *g, uint32_t R, uint64_t seed, im_workspac
     k_lt_order<<<R, LTO_NT, 0, s>>>(f);
 }
 
-// A6: the reverse searches of one round by snapshot (im_rev.h). A table entry
-// takes 24 bytes, so three 2,048-entry workgroups share a CU; they hold every
-// task of the uniform-IC and NetHEPT-shaped graphs but a few. 1,024 entries
-// (five per CU) measured the same there and slower on weighted-cascade graphs
-// of 60,000 nodes (27 against 23 ms), whose tasks visit about 1,900 nodes.
-// Against packed snapshots, reverse steps of a selection: 10^6 nodes, p =
-// 0.01, R = 256: 22 -> 5.3 ms; weighted cascade, 15,000 nodes: 13.2 -> 3.9 ms,
-// 60,000 nodes: 157 -> 23 ms; 16 uneven instances: 177 -> 7.4 ms.
+// A5 and A6 of one round by snapshot (im_rev.h). A table entry of the reverse
+// search takes 24 bytes, so three 2,048-entry workgroups share a CU; they hold
+// every task of the uniform-IC and NetHEPT-shaped graphs but a few. 1,024
+// entries (five per CU) measured the same there and slower on weighted-cascade
+// graphs of 60,000 nodes (27 against 23 ms), whose tasks visit about 1,900
+// nodes. Rounds by snapshot against rounds by word, ms per selection:
+//                                        forward and packing     reverse
+//   10^6 nodes, p = 0.01, R = 256        8.5 -> 1.7              22 -> 5.6
+//   weighted cascade, 15,000, R = 100    9.8 -> 3.0              13.2 -> 3.8
+//   weighted cascade, 60,000, R = 128    11.1 -> 3.5             157 -> 15.6
+//   16 uneven instances                  12.6 -> 2.8             177 -> 7.3
 constexpr int REVA_NT = 256, REVA_CS = 2048, REVA_LIM = 1640;
 constexpr int REVB_NT = 512, REVB_CS = 4096, REVB_LIM = 3200;
 
-static void rev_search(const im_graph *g, uint32_t R, im_workspace *ws, uint32_t *ctr,
-                       const unsigned long long *key, hipStream_t s)
+static SnapGraph snap_graph(const im_graph *g, uint32_t W, int d, im_workspace *ws)
 {
-    const uint32_t n = g->n, W = (R + 63) / 64, nbins = ws->batch.count * W * 64;
-    uint32_t *ntasks = ws->rv_cur + nbins;
+    SnapGraph s;
+    s.row = d ? ws->in_row : ws->row32;
+    s.col = d ? ws->in_col : g->col;
+    s.mask = d ? ws->mask_in : ws->mask_out;
+    s.m = g->m; s.n = g->n; s.W = W;
+    s.hub = hub_lists(ws, d);
+    s.sp = sparse_lists(ws, d);
+    return s;
+}
+
+static void rev_search(const im_graph *g, uint32_t R, uint32_t t, uint32_t *seeds_out,
+                       uint64_t *gains_out, im_workspace *ws, uint32_t *ctr, hipStream_t s)
+{
+    const uint32_t W = (R + 63) / 64;
+    uint32_t *ntasks = ctr + 5;
     {
-        PhaseTimer pt(ws, IM_PH_PACK, s);
-        const dim3 grid(grid_for(n, 256, 64), W);
-        if (ws->batch.count > 1)
-            k_rev_count<<<grid, 256, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, W,
-                                             ws->batch.node_inst, ws->rv_cnt);
-        k_rev_plan<<<1, RVP_NT, 0, s>>>(ws->rv_cnt, ws->rv_cur, nbins, W, ws->rv_tasks, ntasks, key,
-                                        ws->batch.count == 1 ? ws->aff_gain : 0ull);
-        k_rev_fill<<<grid, 256, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, W,
-                                        ws->batch.node_inst, ws->rv_cur, ws->rv_src);
+        FwdSnapArgs f;
+        f.g = snap_graph(g, W, 0, ws);
+        f.b = ws->batch;
+        f.R = R; f.Rmax = R; f.t = t;
+        f.key = ws->keys + (uint64_t)t * ws->batch.count;
+        f.seeds_out = seeds_out; f.gains_out = gains_out; f.sel = ws->sel;
+        f.covered = ws->covered;
+        f.src = ws->rv_src; f.tasks = ws->rv_tasks; f.ntasks = ntasks; f.stamp = ws->rv_stamp;
+        f.stats = ws->stats;
+        PhaseTimer pt(ws, IM_PH_FORWARD, s);
+        k_fwd_snap<<<ws->batch.count * R, FWS_NT, 0, s>>>(f);
     }
     RevArgs a;
-    a.row = ws->in_row; a.col = ws->in_col; a.mask = ws->mask_in; a.m = g->m;
-    a.n = n; a.W = W;
-    a.hub = hub_lists(ws, 1);
-    a.sp = sparse_lists(ws, 1);
+    a.g = snap_graph(g, W, 1, ws);
     a.node_inst = ws->batch.node_inst; a.inst_off = ws->batch.node_off;
     a.src = ws->rv_src; a.tasks = ws->rv_tasks; a.ntasks = ntasks;
     a.b_reach = ws->b_reach; a.b_qa = ws->b_qa; a.b_qb = ws->b_qb; a.b_vis = ws->b_vis;
@@ -2369,6 +2380,10 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
                                         seeds_out, gains_out, ws->sel, ws->gain, ws->lt_stamp, ws->stats);
         return IM_OK;
     }
+    if (ws->rv_on) {
+        rev_search(g, R, t, seeds_out, gains_out, ws, ctr, s);
+        return IM_OK;
+    }
 
     FwdArgs f;
     f.skip = nullptr;
@@ -2383,7 +2398,6 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
     uint32_t *bcnt = ws->pk, *bcur = ws->pk + 64 * 64, *gcnt = ws->pk + 2 * 64 * 64,
              *mcnt = gcnt + 64;
     f.bcnt = bcnt; f.mcnt = mcnt; f.mlist = ws->mlist;
-    if (ws->rv_on) { f.bcnt = ws->batch.count == 1 ? ws->rv_cnt : nullptr; f.mcnt = nullptr; }
     f.key = ws->keys + (uint64_t)t * ws->batch.count; f.t = t; f.b = ws->batch;
     f.seeds_out = seeds_out; f.gains_out = gains_out; f.sel = ws->sel;
     f.stats = ws->stats;
@@ -2393,28 +2407,24 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
         if (rc) return rc;
     }
 
-    if (ws->rv_on) {
-        rev_search(g, R, ws, ctr, ws->keys + (uint64_t)t * ws->batch.count, s);
-    } else {
-        {
-            // the forward search counted the single-bit sources per bit and
-            // listed the others
-            PhaseTimer pt(ws, IM_PH_PACK, s);
-            dim3 pg(grid_for(n, PK_NT, 64), W);
-            const uint64_t aff = ws->batch.count == 1 ? ws->aff_gain : 0ull;
-            k_pack_fill<<<pg, PK_NT, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, bcnt, ws->boff,
-                                             gcnt, bcur, ws->plist, mcnt, ws->keys + (uint64_t)t * ws->batch.count,
-                                             aff);
-        }
-        BfsArgs a = bfs_args(ws, ws->in_row, ws->in_col, ws->mask_in, g->m, n, R, W);
-        a.gcnt = gcnt; a.mcnt = mcnt; a.bcnt = bcnt; a.boff = ws->boff;
-        a.plist = ws->plist; a.mlist = ws->mlist; a.tbits = ws->newly;
-        a.hub = hub_lists(ws, 1);
-        a.sp = sparse_lists(ws, 1);
-        a.pass = PASS_REV;
-        a.st_trav = ST_TRAV_REV;
-        run_tiers<MODE_DEC, false>(a, ws, ctr, IM_PH_REV_T0, s);
+    {
+        // the forward search counted the single-bit sources per bit and
+        // listed the others
+        PhaseTimer pt(ws, IM_PH_PACK, s);
+        dim3 pg(grid_for(n, PK_NT, 64), W);
+        const uint64_t aff = ws->batch.count == 1 ? ws->aff_gain : 0ull;
+        k_pack_fill<<<pg, PK_NT, 0, s>>>(ws->tnodes, ws->tcounts, ws->newly, n, bcnt, ws->boff,
+                                         gcnt, bcur, ws->plist, mcnt, ws->keys + (uint64_t)t * ws->batch.count,
+                                         aff);
     }
+    BfsArgs a = bfs_args(ws, ws->in_row, ws->in_col, ws->mask_in, g->m, n, R, W);
+    a.gcnt = gcnt; a.mcnt = mcnt; a.bcnt = bcnt; a.boff = ws->boff;
+    a.plist = ws->plist; a.mlist = ws->mlist; a.tbits = ws->newly;
+    a.hub = hub_lists(ws, 1);
+    a.sp = sparse_lists(ws, 1);
+    a.pass = PASS_REV;
+    a.st_trav = ST_TRAV_REV;
+    run_tiers<MODE_DEC, false>(a, ws, ctr, IM_PH_REV_T0, s);
     if (ws->batch.count == 1 && ws->aff_gain) affected_update(g, R, t, ws, s);
     {
         PhaseTimer pt(ws, IM_PH_CLEAR, s);
@@ -2458,7 +2468,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
         }
     }
     if (rounds && k && ws->live_edge == 1) reserve_lt(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64));
-    if (rounds && k && !ws->lt_on) reserve_rev(ws, (uint64_t)g->n * R, (R + 63) / 64);
+    if (rounds && k && !ws->lt_on) reserve_rev(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64), (R + 63) / 64);
     if ((rc = validate(g, ws, s, ws->row32))) return rc;
     if (ws->live_edge == 1) {
         if (ws->batch.count > 1) return im_fail(IM_EINVAL, "linear-threshold snapshots apply to single graphs only");
@@ -2506,7 +2516,7 @@ static int enqueue_prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_
     fill<uint32_t>(ws->gain, n, 0u, s);
     fill<uint8_t>(ws->sel, n, (uint8_t)0, s);
     fill<uint64_t>(ws->covered, (uint64_t)n * W, 0ull, s);
-    if (ws->rv_on) fill<uint32_t>(ws->rv_cnt, (uint64_t)ws->batch.count * W * 64, 0u, s);
+    if (ws->rv_on) fill<uint32_t>(ws->rv_stamp, (uint64_t)n * W, 0u, s);
     const bool rev = need == PREP_REVERSE || ws->live_edge == 1;
     if (ws->lt_on) {
         build_reverse(g, ws, s);
@@ -4219,12 +4229,12 @@ static int reserve_batch(im_workspace *ws, uint32_t count, uint64_t N, uint64_t 
 {
     int rc;
     if (count > ws->cap_count) {
-        if ((rc = dalloc(&ws->b_u32, 4ull * (count + 1))) || (rc = dalloc(&ws->b_u64, 2ull * (count + 1))) ||
+        if ((rc = dalloc(&ws->b_u32, 4ull * (count + 1))) || (rc = dalloc(&ws->b_u64, 3ull * (count + 1))) ||
             (rc = dalloc(&ws->b_desc, count)))
             return rc;
         if (ws->b_host) (void)hipHostFree(ws->b_host);
         ws->b_host = nullptr;
-        size_t bytes = (4ull * (count + 1)) * 4 + (2ull * (count + 1)) * 8 + (uint64_t)count * sizeof(InstDesc);
+        size_t bytes = (4ull * (count + 1)) * 4 + (3ull * (count + 1)) * 8 + (uint64_t)count * sizeof(InstDesc);
         HIPCHK(hipHostMalloc(&ws->b_host, bytes, hipHostMallocDefault));
         ws->cap_count = count;
     }
@@ -4281,15 +4291,15 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     const uint32_t W = (Rmax + 63) / 64;
     ws->batch.count = count;  // sizes the per-round key arrays
     rc = ws_reserve(ws, (uint32_t)N, M, W, kmax, nmax);
-    if (!rc) reserve_rev(ws, pairs, W);
+    if (!rc) reserve_rev(ws, pairs, N * W, W);
     ws->batch.count = 1;
     if (!rc) rc = reserve_batch(ws, count, N, M);
     if (rc) return rc;
     // per-instance tables, staged in pinned memory
     uint32_t *hu = (uint32_t *)ws->b_host;              // R, k, kpre, node_off
-    uint64_t *h64 = (uint64_t *)(hu + 4ull * (count + 1));  // arc_off, seed
-    InstDesc *hd = (InstDesc *)(h64 + 2ull * (count + 1));
-    uint64_t no = 0, ao = 0, kp = 0;
+    uint64_t *h64 = (uint64_t *)(hu + 4ull * (count + 1));  // arc_off, seed, pair_off
+    InstDesc *hd = (InstDesc *)(h64 + 3ull * (count + 1));
+    uint64_t no = 0, ao = 0, kp = 0, po = 0;
     for (uint32_t i = 0; i < count; i++) {
         if (inst[i].g.m && (!inst[i].g.col || !inst[i].g.prob))
             return im_fail(IM_EINVAL, "instance %u: null col or prob", i);
@@ -4300,6 +4310,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
         hu[3 * (count + 1) + i] = (uint32_t)no;
         h64[i] = ao;
         h64[(count + 1) + i] = inst[i].seed;
+        h64[2 * (count + 1) + i] = po;
         hd[i].row_ptr = inst[i].g.row_ptr;
         hd[i].col = inst[i].g.col;
         hd[i].prob = inst[i].g.prob;
@@ -4310,11 +4321,12 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
         no += inst[i].g.n;
         ao += inst[i].g.m;
         kp += inst[i].k;
+        po += (uint64_t)inst[i].g.n * inst[i].R;
     }
     hu[3 * (count + 1) + count] = (uint32_t)no;
     h64[count] = ao;
     HIPCHK(hipMemcpyAsync(ws->b_u32, hu, (4ull * (count + 1)) * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(ws->b_u64, h64, (2ull * (count + 1)) * 8, hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(ws->b_u64, h64, (3ull * (count + 1)) * 8, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(ws->b_desc, hd, (uint64_t)count * sizeof(InstDesc), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemsetAsync(ws->err, 0, sizeof(uint32_t), s));
     launch_merge(inst, count, ws, s);
@@ -4332,6 +4344,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     b.node_off = ws->b_u32 + 3 * (count + 1);
     b.arc_off = ws->b_u64;
     b.seed = ws->b_u64 + (count + 1);
+    b.pair_off = ws->b_u64 + 2 * (count + 1);
     ws->batch = b;
     mg->n = (uint32_t)N;
     mg->m = M;
@@ -4343,7 +4356,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     return IM_OK;
 }
 
-static const Batch kSingle = {1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+static const Batch kSingle = {1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
 
 extern "C" int im_select_batch(const im_instance *inst, uint32_t count, uint32_t *seeds_out,
                                uint64_t *gains_out, im_workspace *ws, void *stream)

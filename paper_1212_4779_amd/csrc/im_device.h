@@ -46,6 +46,7 @@ struct Batch {
     const uint32_t *node_off;   // [count+1]
     const uint64_t *arc_off;    // [count+1]
     const uint64_t *seed;       // [count]
+    const uint64_t *pair_off;   // [count] (node, snapshot) pairs of the instances before
 };
 
 // largest i with off[i] <= x (off[0] = 0 <= x < off[count])

@@ -1,5 +1,6 @@
-// im_rev.h -- the reverse step of the dynamic update, 64 sources of one
-// snapshot per search.
+// im_rev.h -- a round of the dynamic update by snapshot: the forward step, one
+// workgroup per snapshot (k_fwd_snap), and the reverse step, 64 sources of one
+// snapshot per search (k_rev_search).
 //
 // A round's newly covered (node, snapshot) pairs each subtract one from the
 // gain of every node that reaches the node in that snapshot (the delete loop
@@ -14,9 +15,7 @@
 // decrement.
 //
 // Only the arcs live in the one snapshot are read, from the per-snapshot live
-// lists (nodes without lists read their arcs' mask words). The pairs are
-// sorted by (instance, snapshot) each round (k_rev_plan, k_rev_fill); the
-// searches run in LDS tables of 2,048 entries, those that outgrow them in
+// lists (nodes without lists read their arcs' mask words). The searches run in LDS tables of 2,048 entries, those that outgrow them in
 // tables of 4,096 entries and, past that, in a dense slot in global memory.
 // The bound is the latency of a level: row bounds and list offsets, then the
 // listed heads (two dependent global loads), then the table update.
@@ -25,8 +24,8 @@
 
 #include "im_bfs.h"
 
-struct RevArgs {
-    // reverse graph and its per-snapshot live lists
+// a graph in one direction with its masks and per-snapshot live lists
+struct SnapGraph {
     const uint32_t *row;      // [n+1]
     const uint32_t *col;      // [m]
     const uint64_t *mask;     // [W][m]
@@ -34,9 +33,13 @@ struct RevArgs {
     uint32_t n, W;
     HubLists hub;
     SparseLists sp;
+};
+
+struct RevArgs {
+    SnapGraph g;                // reverse arcs
     const uint32_t *node_inst;  // batches: instance of each node (nullptr: one graph)
     const uint32_t *inst_off;   // batches: first node of each instance
-    // the round's sources, sorted by bin, and its tasks (RevTask)
+    // the round's sources and its tasks (rev_task)
     const uint32_t *src;
     const uint2 *tasks;
     const uint32_t *ntasks;
@@ -61,14 +64,14 @@ __device__ __forceinline__ uint2 rev_task(uint32_t first, uint32_t cnt, uint32_t
     return make_uint2(first, cnt | (bit << 8) | (word << 16));
 }
 
-// where the heads of x's reverse arcs live in snapshot 64w + b are: kind 0
+// where the heads of x's arcs live in snapshot 64w + b are: kind 0
 // the sparse lists, 1 the hub lists, 2 the arcs themselves (heads whose mask
 // word has the bit)
 struct RevSpan {
     uint32_t start, len, kind;
 };
 
-__device__ __forceinline__ RevSpan rev_span(const RevArgs &a, uint32_t w, uint32_t b, uint32_t x)
+__device__ __forceinline__ RevSpan rev_span(const SnapGraph &a, uint32_t w, uint32_t b, uint32_t x)
 {
     const uint64_t p = (uint64_t)w * a.n + x;
     // independent loads; the counts of a node without lists are not used
@@ -91,7 +94,7 @@ __device__ __forceinline__ RevSpan rev_span(const RevArgs &a, uint32_t w, uint32
 }
 
 // the head at position pos of a span of this kind; false: not live
-__device__ __forceinline__ bool rev_head(const RevArgs &a, uint32_t w, uint32_t b, uint32_t kind,
+__device__ __forceinline__ bool rev_head(const SnapGraph &a, uint32_t w, uint32_t b, uint32_t kind,
                                          uint32_t pos, uint32_t &v)
 {
     const uint32_t *heads = kind == 0 ? a.sp.adj : kind == 1 ? a.hub.adj : a.col;
@@ -114,7 +117,7 @@ struct RevBig {                // the longer spans of one chunk of the frontier
 // 2^30) with its span and delta. relax(own, v) is called for every live head.
 // All threads call it; ends with a barrier.
 template <int NT, typename Relax>
-__device__ __forceinline__ void rev_expand(RevBig<NT> &B, const RevArgs &a, uint32_t w, uint32_t b,
+__device__ __forceinline__ void rev_expand(RevBig<NT> &B, const SnapGraph &a, uint32_t w, uint32_t b,
                                            bool take, uint32_t own, const RevSpan &sp, Relax relax,
                                            uint64_t &arcs)
 {
@@ -232,12 +235,12 @@ __device__ bool rev_run_lds(RevLds<NT, CS> &L, const RevArgs &a, uint2 tk, RevCo
                 // the bits gained since the last expansion; bits that arrive
                 // later re-queue the entry for the next level
                 d = atomicExch((unsigned long long *)&L.pend[idx], 0ull);
-                sp = rev_span(a, w, b, L.keys[idx]);
+                sp = rev_span(a.g, w, b, L.keys[idx]);
             }
             // a longer span's delta is looked up by its owner: the bits taken
             // above are part of reach, and passing on bits of reach that are
             // still pending only brings them forward
-            rev_expand<NT>(L.B, a, w, b, take, idx, sp,
+            rev_expand<NT>(L.B, a.g, w, b, take, idx, sp,
                            [&](uint32_t own, uint32_t v) {
                                const uint64_t bits = own == idx && take ? d : L.reach[own];
                                rev_relax<NT, CS, LIM>(L, v, bits, cur ^ 1, &L.nn);
@@ -252,7 +255,7 @@ __device__ bool rev_run_lds(RevLds<NT, CS> &L, const RevArgs &a, uint2 tk, RevCo
         const uint32_t key = L.keys[i];
         if (key == IM_EMPTY) continue;
         if (ok) {
-            const uint32_t pc = (uint32_t)__popcll(L.reach[i]), dg = a.row[key + 1] - a.row[key];
+            const uint32_t pc = (uint32_t)__popcll(L.reach[i]), dg = a.g.row[key + 1] - a.g.row[key];
             atomicSub(&a.gain[key], pc);
             c.relax += dg;
             c.reached += 1;
@@ -296,9 +299,9 @@ __device__ void rev_run_dense(RevBig<NT> &B, uint32_t *ctr, const RevArgs &a, ui
             if (take) {
                 x = cur[base + tid];
                 d = atomicExch((unsigned long long *)&rec[(uint64_t)(x - base0) * 2 + 1], 0ull);
-                sp = rev_span(a, w, b, x);
+                sp = rev_span(a.g, w, b, x);
             }
-            rev_expand<NT>(B, a, w, b, take, x - base0, sp,
+            rev_expand<NT>(B, a.g, w, b, take, x - base0, sp,
                            [&](uint32_t own, uint32_t v) {
                                const uint64_t bits =
                                    own == x - base0 && take
@@ -316,7 +319,7 @@ __device__ void rev_run_dense(RevBig<NT> &B, uint32_t *ctr, const RevArgs &a, ui
     for (uint32_t i = tid; i < nv; i += NT) {
         const uint32_t x = vis[i];
         uint64_t *r = &rec[(uint64_t)(x - base0) * 2];
-        const uint32_t pc = (uint32_t)__popcll(*r), dg = a.row[x + 1] - a.row[x];
+        const uint32_t pc = (uint32_t)__popcll(*r), dg = a.g.row[x + 1] - a.g.row[x];
         *r = 0;   // pend is zero at the fixpoint
         atomicSub(&a.gain[x], pc);
         c.relax += dg;
@@ -384,92 +387,105 @@ __global__ __launch_bounds__(NT) void k_rev_search(RevArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// The round's sources. A bin is one snapshot of one instance: (inst * W + w)
-// * 64 + b. The forward search counts the pairs per bin (batches: k_rev_count).
+// The forward step, one workgroup per snapshot (of every instance): commit the
+// instance's argmax, search from it over the snapshot's live arcs, pruned at
+// covered, and leave the newly covered nodes, which are the search's queue,
+// as the reverse step's sources, 64 to a task.
+// A word of 64 snapshots searched together needs many workgroups, and a grid
+// barrier per level, to be as wide; the snapshots' searches are independent,
+// so a level here costs its four dependent accesses (queue, list offsets,
+// listed heads, covered) and three workgroup barriers. Figures: rev_search.
 // ---------------------------------------------------------------------------
-constexpr int RVP_NT = 1024;
+struct FwdSnapArgs {
+    SnapGraph g;                     // forward arcs
+    Batch b;
+    uint32_t R, Rmax, t;             // R: of one graph; Rmax workgroups per instance
+    const unsigned long long *key;   // one per instance
+    uint32_t *seeds_out;
+    uint64_t *gains_out;
+    uint8_t *sel;
+    uint64_t *covered;               // [W][n]
+    uint32_t *src;                   // a snapshot's queue: up to n (its instance's) nodes
+    uint2 *tasks;
+    uint32_t *ntasks;                // zero before the launch
+    uint32_t *stamp;                 // [W][n] last round (plus one) that newly covered the node
+                                     // in any snapshot of the word, for the (node, word) counters
+    unsigned long long *stats;
+};
 
-// One workgroup: bin starts (into cur, the fill's cursors), the task list and
-// its length; the bin counts return to zero.
-__global__ __launch_bounds__(RVP_NT) void k_rev_plan(uint32_t *cnt, uint32_t *cur, uint32_t nbins,
-                                                     uint32_t W, uint2 *tasks, uint32_t *ntasks,
-                                                     const unsigned long long *key, uint64_t aff_gain)
+constexpr int FWS_NT = 512, FWS_Q = 4096;   // queue entries kept in LDS as well
+
+__global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
 {
-    __shared__ uint32_t s_w[RVP_NT / 64 + 1], s_t[RVP_NT], s_o[RVP_NT], s_c[RVP_NT];
-    const int tid = threadIdx.x;
-    // a round updated by the affected-set recompute has no reverse tasks
-    const bool none = aff_gain && (*key >> 32) < aff_gain;
-    uint32_t off0 = 0, t0 = 0;
-    for (uint32_t base = 0; base < nbins; base += RVP_NT) {
-        const uint32_t i = base + tid;
-        const uint32_t c = i < nbins ? cnt[i] : 0u;
-        if (c) cnt[i] = 0;
-        uint32_t tot, tt;
-        const uint32_t o = off0 + block_excl_scan<RVP_NT>(c, s_w, &tot);
-        const uint32_t te = block_excl_scan<RVP_NT>((c + 63) / 64, s_w, &tt);
-        if (i < nbins) cur[i] = o;
-        s_t[tid] = te; s_o[tid] = o; s_c[tid] = c;
-        __syncthreads();
-        // the tile's tasks, spread over the threads
-        for (uint32_t t = tid; t < tt && !none; t += RVP_NT) {
-            const uint32_t k = (uint32_t)upper_index<RVP_NT>(s_t, t), g = t - s_t[k], bin = base + k;
-            tasks[t0 + t] = rev_task(s_o[k] + 64u * g, min(64u, s_c[k] - 64u * g), bin & 63u,
-                                     (bin >> 6) % W);
+    __shared__ RevBig<FWS_NT> B;
+    __shared__ uint32_t q[FWS_Q], cnt, s_t0;
+    __shared__ unsigned long long red[FWS_NT / 64];
+    const uint32_t tid = threadIdx.x, inst = blockIdx.x / a.Rmax, r = blockIdx.x - inst * a.Rmax;
+    const unsigned long long key = a.key[inst];
+    const bool single = a.b.count == 1;
+    const uint32_t R = single ? a.R : a.b.R[inst];
+    if (key == 0 || r >= R) return;   // the instance has its k seeds
+    const uint32_t v = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
+    uint32_t ni = a.g.n;
+    uint64_t base = 0;
+    if (!single) { ni = a.b.node_off[inst + 1] - a.b.node_off[inst]; base = a.b.pair_off[inst]; }
+    base += (uint64_t)r * ni;
+    if (r == 0 && tid == 0) {
+        const uint32_t out = (single ? 0u : a.b.kpre[inst]) + a.t;
+        a.seeds_out[out] = v - (single ? 0u : a.b.node_off[inst]);
+        a.gains_out[out] = key >> 32;
+        a.sel[v] = 1;
+    }
+    const uint32_t w = r / 64, b = r % 64;
+    const unsigned long long bit = 1ull << b;
+    unsigned long long *cov = (unsigned long long *)a.covered + (uint64_t)w * a.g.n;
+    uint32_t *src = a.src + base;
+    if (tid == 0) {
+        const bool fresh = !(atomicOr(&cov[v], bit) & bit);
+        if (fresh) { q[0] = v; src[0] = v; }
+        cnt = fresh ? 1u : 0u;
+        B.n = 0;
+    }
+    __syncthreads();
+    uint64_t arcs = 0;
+    for (uint32_t head = 0;;) {
+        const uint32_t end = cnt;
+        __syncthreads();   // (cnt grows from here on)
+        if (head == end) break;
+        for (; head < end; head += FWS_NT) {
+            const uint32_t i = head + tid;
+            const bool take = i < end;
+            RevSpan sp = {0, 0, 0};
+            if (take) sp = rev_span(a.g, w, b, i < (uint32_t)FWS_Q ? q[i] : src[i]);
+            rev_expand<FWS_NT>(B, a.g, w, b, take, 0u, sp,
+                               [&](uint32_t, uint32_t y) {
+                                   if (atomicOr(&cov[y], bit) & bit) return;
+                                   const uint32_t p = atomicAdd(&cnt, 1u);
+                                   if (p < (uint32_t)FWS_Q) q[p] = y;
+                                   src[p] = y;
+                               },
+                               arcs);
         }
-        off0 += tot;
-        t0 += tt;
-        __syncthreads();
+        head = end;
     }
-    if (tid == 0) *ntasks = none ? 0u : t0;
-}
-
-// batches: the newly covered pairs per bin
-__global__ __launch_bounds__(256) void k_rev_count(const uint32_t *tnodes, const uint32_t *tcounts,
-                                                   const uint64_t *newly, uint32_t n, uint32_t W,
-                                                   const uint32_t *node_inst, uint32_t *cnt)
-{
-    const uint32_t w = blockIdx.y, c = tcounts[w];
-    const uint64_t off = (uint64_t)w * n;
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < c; i += gridDim.x * 256u) {
-        const uint32_t x = tnodes[off + i];
-        uint32_t *bins = cnt + ((uint64_t)node_inst[x] * W + w) * 64;
-        for (uint64_t b = newly[off + x]; b; b &= b - 1)
-            atomicAdd(&bins[__ffsll((unsigned long long)b) - 1], 1u);
+    const uint32_t N = cnt;
+    uint64_t trav = 0, relax = 0, pairs = 0;
+    for (uint32_t i = tid; i < N; i += FWS_NT) {
+        const uint32_t x = i < (uint32_t)FWS_Q ? q[i] : src[i];
+        const uint32_t od = a.g.row[x + 1] - a.g.row[x];
+        trav += od;
+        if (atomicExch(&a.stamp[(uint64_t)w * a.g.n + x], a.t + 1) != a.t + 1) { relax += od; pairs++; }
     }
-}
-
-// Place the sources: src[cur[bin]++] = node. One graph: each workgroup counts
-// its pairs per bit in LDS and takes one range of every bin; batches: one
-// atomic per pair on the bins of many instances.
-__global__ __launch_bounds__(256) void k_rev_fill(const uint32_t *tnodes, const uint32_t *tcounts,
-                                                  const uint64_t *newly, uint32_t n, uint32_t W,
-                                                  const uint32_t *node_inst, uint32_t *cur,
-                                                  uint32_t *src)
-{
-    __shared__ uint32_t cnt[64];
-    const uint32_t w = blockIdx.y, c = tcounts[w], tid = threadIdx.x;
-    const uint64_t off = (uint64_t)w * n;
-    if (node_inst) {
-        for (uint32_t i = blockIdx.x * 256u + tid; i < c; i += gridDim.x * 256u) {
-            const uint32_t x = tnodes[off + i];
-            uint32_t *bins = cur + ((uint64_t)node_inst[x] * W + w) * 64;
-            for (uint64_t b = newly[off + x]; b; b &= b - 1)
-                src[atomicAdd(&bins[__ffsll((unsigned long long)b) - 1], 1u)] = x;
-        }
-        return;
-    }
-    for (uint32_t base = blockIdx.x * 256u; base < c; base += gridDim.x * 256u) {
-        if (tid < 64) cnt[tid] = 0;
-        __syncthreads();
-        const uint32_t i = base + tid;
-        const uint32_t x = i < c ? tnodes[off + i] : 0u;
-        const uint64_t bits = i < c ? newly[off + x] : 0ull;
-        for (uint64_t b = bits; b; b &= b - 1) atomicAdd(&cnt[__ffsll((unsigned long long)b) - 1], 1u);
-        __syncthreads();
-        if (tid < 64 && cnt[tid]) cnt[tid] = atomicAdd(&cur[w * 64 + tid], cnt[tid]);
-        __syncthreads();
-        for (uint64_t b = bits; b; b &= b - 1)
-            src[atomicAdd(&cnt[__ffsll((unsigned long long)b) - 1], 1u)] = x;
-        __syncthreads();
+    const uint32_t nt = (N + 63) / 64;
+    if (tid == 0) s_t0 = nt ? atomicAdd(a.ntasks, nt) : 0u;
+    trav = group_sum<FWS_NT>(trav, red);
+    relax = group_sum<FWS_NT>(relax, red);
+    pairs = group_sum<FWS_NT>(pairs, red);
+    for (uint32_t g = tid; g < nt; g += FWS_NT)
+        a.tasks[s_t0 + g] = rev_task((uint32_t)base + 64u * g, min(64u, N - 64u * g), b, w);
+    if (tid == 0 && N) {
+        stat_add(a.stats, ST_TRAV_FWD, trav);
+        stat_add(a.stats, ST_RELAX_FWD, relax);
+        stat_add(a.stats, ST_TASKS_REV, pairs);
     }
 }
