@@ -479,8 +479,8 @@ int im_autotune_lazy(const im_graph *g, uint32_t R, uint32_t k, uint64_t seed, c
  * Either output may be NULL (marg_out NULL: one search per word from all
  * seeds at once). S: device array of nS node ids, each < n, checked on the
  * host before any output is written. 1 <= R <= IM_SPREAD_R_MAX (R is not
- * bounded by IM_R_MAX: snapshot words are processed in chunks whose masks
- * and search state stay within a fixed device-memory budget). Synchronous
+ * bounded by IM_R_MAX: a fixed number of workgroups takes one snapshot after
+ * another, drawing the coins of reached nodes' arcs only). Synchronous
  * for the seed check, then asynchronous on `stream`. Errors: IM_EINVAL for
  * null pointers, R out of range, a seed >= n or a malformed graph. */
 int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uint32_t *S, uint32_t nS,

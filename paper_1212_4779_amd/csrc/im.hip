@@ -34,6 +34,7 @@
 #include "im_bfs.h"
 #include "im_rev.h"
 #include "im_lt.h"
+#include "im_spread.h"
 #include "im_host.h"
 #include "im_mlp.h"
 
@@ -333,15 +334,15 @@ __global__ void k_scan_add(uint32_t *out, uint64_t len, const uint32_t *sums)
 // are below floor(p_e * 2^32). One thread per (arc, word).
 // In a batch, arc e belongs to instance i and is arc e - arc_off[i] of it:
 // the instance's own seed and R apply (its words beyond R are all zero).
-// word w0 + blockIdx.y of every arc, stored at mask[blockIdx.y][e]
+// word blockIdx.y of every arc, stored at mask[blockIdx.y][e]
 // key_of (single graphs): the index arc e's coins are drawn under (one coin
 // per undirected pair: both directions use the canonical arc's index)
 __global__ __launch_bounds__(256) void k_mask_gen(const float *prob, uint64_t m, uint32_t R,
                                                   uint64_t seed, uint64_t *mask, Batch b,
-                                                  uint32_t w0 = 0, const uint32_t *key_of = nullptr)
+                                                  const uint32_t *key_of)
 {
     uint64_t e = blockIdx.x * 256ull + threadIdx.x;
-    uint32_t w = w0 + blockIdx.y;
+    uint32_t w = blockIdx.y;
     if (e >= m) return;
     uint64_t el = key_of ? key_of[e] : e;
     if (b.arc_off) {
@@ -1397,12 +1398,11 @@ struct im_workspace {
     uint64_t *e_reach = nullptr, *e_pend = nullptr, *e_fq0 = nullptr, *e_fq1 = nullptr,
              *e_vis = nullptr;
     uint32_t *e_cnt = nullptr;
-    // spread evaluator: one chunk of snapshot words at a time
-    uint32_t cap_sp_n = 0, cap_sp_words = 0;
-    uint64_t cap_sp_m = 0;
-    uint32_t *v_row32 = nullptr;
-    uint64_t *v_mask = nullptr, *v_reach = nullptr, *v_pend = nullptr, *v_cov = nullptr;
-    uint32_t *v_qa = nullptr, *v_qb = nullptr, *v_vis = nullptr;
+    // spread evaluator
+    uint32_t cap_sp_n = 0;
+    uint64_t cap_sp_m = 0, cap_sp_q = 0, cap_sp_b = 0;
+    uint32_t *v_row32 = nullptr, *v_queue = nullptr, *v_bits = nullptr;
+    ArcCoin *v_coin = nullptr;
     // linear-threshold snapshots
     int live_edge = 0;                   // 0: independent cascade, 1: linear threshold
     uint64_t *lt_start = nullptr;        // [m] start of each in-arc's draw interval
@@ -1606,8 +1606,7 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
     dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord); dfree(ws->lt_stamp); dfree(ws->lt_sc); dfree(ws->lt_pos);
     dfree(ws->a_reach); dfree(ws->a_pend); dfree(ws->a_qa); dfree(ws->a_qb); dfree(ws->a_vis);
     dfree(ws->a_mark); dfree(ws->a_list); dfree(ws->a_cnt); dfree(ws->a_ctrs);
-    dfree(ws->v_row32); dfree(ws->v_mask); dfree(ws->v_reach); dfree(ws->v_pend); dfree(ws->v_cov);
-    dfree(ws->v_qa); dfree(ws->v_qb); dfree(ws->v_vis);
+    dfree(ws->v_row32); dfree(ws->v_coin); dfree(ws->v_queue); dfree(ws->v_bits);
     dfree(ws->stats); dfree(ws->err);
     if (ws->host_err) (void)hipHostFree(ws->host_err);
     if (ws->host_stats) (void)hipHostFree(ws->host_stats);
@@ -1937,7 +1936,7 @@ static void build_masks(const im_graph *g, uint32_t R, uint64_t seed, im_workspa
     dim3 grid((unsigned)((m + 255) / 256), W);
     {
         PhaseTimer pt(ws, IM_PH_MASK_GEN, s);
-        k_mask_gen<<<grid, 256, 0, s>>>(g->prob, m, R, seed, mask_out, ws->batch, 0u,
+        k_mask_gen<<<grid, 256, 0, s>>>(g->prob, m, R, seed, mask_out, ws->batch,
                                         ws->pair_coins ? ws->pair : nullptr);
     }
     if (reverse) {
@@ -3622,105 +3621,59 @@ static int select_lazy(const im_graph *g, uint32_t R, uint32_t k, uint32_t B, co
 // C ABI
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
-// Spread evaluator: f(T) = sum_r |R_r(T)| (the snapshot estimator of Sec. 3.1,
-// times R) for the prefixes of a seed sequence, on snapshots of any seed, so
-// a seed set can be scored on snapshots independent of those that chose it
-// (the evaluation protocol of Sec. 5.2). One workgroup per snapshot word covers
-// the seeds group by group: each group's search is pruned at the nodes the
-// earlier groups covered, so its reach count is the group's marginal gain.
+// Spread evaluator (im_spread.h)
 // ---------------------------------------------------------------------------
-constexpr int SPR_NT = 1024, SPR_U = 8;
-constexpr uint64_t SPR_BUDGET = 8ull << 30;   // masks + search state of one chunk
-constexpr uint32_t SPR_MAX_WORDS = 256;
-
-struct SpreadArgs {
-    const uint32_t *row, *col;
-    const uint64_t *mask;          // [chunk words][m]
-    uint64_t m;
-    uint32_t n, R, W, w0;          // this launch: words w0 .. w0 + gridDim.x - 1
-    const uint32_t *S;
-    uint32_t nS, group;            // seeds per search
-    uint64_t *reach, *pend, *cov;  // [chunk words][n]; reach, pend zero at rest, cov zero on entry
-    uint32_t *qa, *qb, *vis;       // [chunk words][n]
-    unsigned long long *marg;      // [ceil(nS / group)] (accumulated over words) or nullptr
-    uint32_t *per_snapshot;        // [R] or nullptr
-};
-
-__global__ __launch_bounds__(SPR_NT) void k_spread(SpreadArgs a)
+constexpr uint64_t SPR_BUDGET = 4ull << 30;      // queues (and visit bits) of the workgroups
+constexpr uint32_t SPR_LDS_NODES = 1u << 18;     // visit bits in LDS up to this many nodes (32 KB)
+// Lanes per snapshot. A snapshot of a small graph fills a wavefront at best
+// (its searches are a chain of levels), and one wavefront needs no workgroup
+// barrier: 15,000 nodes, 50 seeds: 0.53 ms at R = 300 and 2.06 ms at 20,000,
+// against 0.61 / 4.8 with 128 lanes and 0.64 / 19.7 with 512. Larger graphs
+// have hubs whose arcs one wavefront would take long to draw: 60,000 nodes,
+// weighted cascade: R = 500 3.9 / 2.6 / 1.7 / 1.25 ms with 64 / 128 / 256 / 512
+// lanes, R = 2,000 4.2 / 2.8 / 2.9 / 4.1 ms; past the LDS visit bits, 10^6
+// nodes: R = 256 5.9 / 3.5 / 2.1 / 1.4 ms, R = 4,096 23 / 13.7 / 8.5 / 10.1 ms.
+static int spread_lanes(uint32_t n, uint32_t R)
 {
-    __shared__ BlockLds<SPR_NT> L;
-    __shared__ uint32_t bitcnt[64];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const uint32_t wl = blockIdx.x, w = a.w0 + wl;
-    const uint64_t off = (uint64_t)wl * a.n;
-    const uint64_t valid = im_valid_bits(a.R, w);
-    uint64_t *reach = a.reach + off, *pend = a.pend + off, *cov = a.cov + off;
-    uint32_t *qa = a.qa + off, *qb = a.qb + off, *vis = a.vis + off;
-    const uint64_t *mask = a.mask + (uint64_t)wl * a.m;
-    const HubLists nohub = {nullptr, nullptr, nullptr};
-    const SparseLists nosp = {nullptr, nullptr, nullptr};
-    if (tid < 64) bitcnt[tid] = 0;
-    __syncthreads();
-    uint32_t mine = 0;   // this lane's count of snapshot 64w + lane (per wavefront)
-    uint64_t arcs = 0;
-    for (uint32_t g0 = 0; g0 < a.nS; g0 += a.group) {
-        const uint32_t gn = min(a.group, a.nS - g0);
-        uint32_t src = 0;
-        uint64_t start = 0;
-        if ((uint32_t)tid < gn) {
-            src = a.S[g0 + tid];
-            start = valid & ~cov[src];
-        }
-        block_bfs_run<SPR_NT, SPR_U, true, false>(L, src, start, a.row, a.col, mask, nohub, nosp,
-                                                  a.n, a.W, w, cov, reach, pend, 0u, qa, qb, vis,
-                                                  arcs);
-        // fold the group's reach into the cover; wavefront-uniform tiles
-        const uint32_t nvis = L.nvis;
-        uint64_t cnt = 0;
-        for (uint32_t base = (uint32_t)(tid & ~63); base < nvis; base += SPR_NT) {
-            const uint32_t j = base + (uint32_t)lane;
-            uint64_t b = 0;
-            if (j < nvis) {
-                const uint32_t x = vis[j];
-                b = reach[x];
-                cov[x] |= b;
-                reach[x] = 0;
-            }
-            cnt += (uint64_t)__popcll(b);
-            if (a.per_snapshot && __ballot(b != 0) != 0ull) {
-                for (int t = 0; t < 64; t++) {
-                    const uint64_t bal = __ballot((b >> t) & 1ull);
-                    if (lane == t) mine += (uint32_t)__popcll(bal);
-                }
-            }
-        }
-        cnt = group_sum<SPR_NT>(cnt, L.red);
-        if (tid == 0 && a.marg && cnt) atomicAdd(&a.marg[g0 / a.group], (unsigned long long)cnt);
-        __syncthreads();
-    }
-    if (a.per_snapshot) {
-        atomicAdd(&bitcnt[lane], mine);
-        __syncthreads();
-        if (tid < 64 && w * 64u + (uint32_t)tid < a.R) a.per_snapshot[w * 64u + tid] = bitcnt[tid];
-    }
+    if (n <= 16384u) return 64;
+    if (R < 1024u) return 512;
+    return n <= SPR_LDS_NODES ? 128 : 256;
 }
 
-static int reserve_spread(im_workspace *ws, uint32_t n, uint64_t m, uint32_t words)
+static int reserve_spread(im_workspace *ws, uint32_t n, uint64_t m, uint32_t groups)
 {
     int rc;
-    if (n > ws->cap_sp_n || m > ws->cap_sp_m || words > ws->cap_sp_words || !ws->v_row32) {
-        const uint32_t cn = std::max(n, ws->cap_sp_n), cw = std::max(words, ws->cap_sp_words);
-        const uint64_t cm = std::max(m, ws->cap_sp_m), nw = (uint64_t)cn * cw;
-        if ((rc = dalloc(&ws->v_row32, (uint64_t)cn + 1)) || (rc = dalloc(&ws->v_mask, cm * cw)) ||
-            (rc = dalloc(&ws->v_reach, nw)) || (rc = dalloc(&ws->v_pend, nw)) ||
-            (rc = dalloc(&ws->v_cov, nw)) || (rc = dalloc(&ws->v_qa, nw)) ||
-            (rc = dalloc(&ws->v_qb, nw)) || (rc = dalloc(&ws->v_vis, nw)))
-            return rc;
-        HIPCHK(hipMemset(ws->v_reach, 0, nw * sizeof(uint64_t)));
-        HIPCHK(hipMemset(ws->v_pend, 0, nw * sizeof(uint64_t)));
-        ws->cap_sp_n = cn; ws->cap_sp_m = cm; ws->cap_sp_words = cw;
+    const uint64_t nq = (uint64_t)n * groups;
+    const uint64_t nb = n > SPR_LDS_NODES ? (uint64_t)((n + 31) / 32) * groups : 0;
+    if (n > ws->cap_sp_n || !ws->v_row32) {
+        if ((rc = dalloc(&ws->v_row32, (uint64_t)n + 1))) return rc;
+        ws->cap_sp_n = n;
+    }
+    if (m > ws->cap_sp_m || !ws->v_coin) {
+        if ((rc = dalloc(&ws->v_coin, m))) return rc;
+        ws->cap_sp_m = m;
+    }
+    if (nq > ws->cap_sp_q || !ws->v_queue) {
+        ws->cap_sp_q = 0;
+        if ((rc = dalloc(&ws->v_queue, nq))) return rc;
+        ws->cap_sp_q = nq;
+    }
+    if (nb > ws->cap_sp_b) {
+        ws->cap_sp_b = 0;
+        if ((rc = dalloc(&ws->v_bits, nb))) return rc;
+        HIPCHK(hipMemset(ws->v_bits, 0, nb * sizeof(uint32_t)));
+        ws->cap_sp_b = nb;
     }
     return IM_OK;
+}
+
+template <int NT>
+static unsigned spread_groups(const im_workspace *ws, uint32_t n, uint32_t R, unsigned lds)
+{
+    int b = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_spread<NT>, NT, lds) != hipSuccess || b < 1) b = 1;
+    const uint64_t fit = SPR_BUDGET / (4ull * n + 4ull * ((n + 31) / 32) + 1);
+    return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)b * ws->num_cu, R, fit}));
 }
 
 extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uint32_t *S,
@@ -3736,7 +3689,7 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
     if (ws->live_edge || ws->pair_coins)
         return im_fail(IM_EINVAL, "the spread evaluator draws one coin per stored arc");
     hipStream_t s = (hipStream_t)stream;
-    const uint32_t n = g->n, W = (R + 63) / 64;
+    const uint32_t n = g->n;
     const uint64_t m = g->m;
     // seeds are checked on the host before any output is touched
     std::vector<uint32_t> hs(nS);
@@ -3746,33 +3699,30 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
         for (uint32_t i = 0; i < nS; i++)
             if (hs[i] >= n) return im_fail(IM_EINVAL, "S[%u] = %u is not a node (n = %u)", i, hs[i], n);
     }
-    const uint64_t per_word = 8 * m + 36ull * n + 1;
-    const uint32_t cw = (uint32_t)std::max<uint64_t>(
-        1, std::min<uint64_t>({(uint64_t)W, SPR_MAX_WORDS, SPR_BUDGET / per_word}));
-    if ((rc = reserve_spread(ws, n, m, cw))) return rc;
+    const int lanes = spread_lanes(n, R);
+    const unsigned lds = n > SPR_LDS_NODES ? 0u : (n + 31) / 32 * 4u;
+    const unsigned groups = lanes == 64 ? spread_groups<64>(ws, n, R, lds)
+                            : lanes == 128 ? spread_groups<128>(ws, n, R, lds)
+                            : lanes == 256 ? spread_groups<256>(ws, n, R, lds)
+                                           : spread_groups<512>(ws, n, R, lds);
+    if ((rc = reserve_spread(ws, n, m, groups))) return rc;
     if ((rc = validate(g, ws, s, ws->v_row32))) return rc;
     if (marg_out && nS) fill<unsigned long long>((unsigned long long *)marg_out, nS, 0ull, s);
     if (per_snapshot_out) fill<uint32_t>(per_snapshot_out, R, 0u, s);
     if (nS && n) {
+        if (m) k_arc_coins<<<grid_for(m, 256), 256, 0, s>>>(g->col, g->prob, m, seed, ws->v_coin);
         SpreadArgs a;
-        a.row = ws->v_row32; a.col = g->col; a.mask = ws->v_mask; a.m = m;
-        a.n = n; a.R = R; a.W = W; a.S = S; a.nS = nS;
-        a.group = marg_out ? 1u : (uint32_t)SPR_NT;
-        a.reach = ws->v_reach; a.pend = ws->v_pend; a.cov = ws->v_cov;
-        a.qa = ws->v_qa; a.qb = ws->v_qb; a.vis = ws->v_vis;
+        a.row = ws->v_row32; a.coin = ws->v_coin;
+        a.n = n; a.R = R; a.S = S; a.nS = nS;
+        a.group = marg_out ? 1u : nS;
+        a.queue = ws->v_queue;
+        a.bits = n > SPR_LDS_NODES ? ws->v_bits : nullptr;
         a.marg = (unsigned long long *)marg_out;
         a.per_snapshot = per_snapshot_out;
-        Batch nob = {};
-        for (uint32_t w0 = 0; w0 < W; w0 += cw) {
-            const uint32_t c = std::min(cw, W - w0);
-            if (m) {
-                dim3 grid((unsigned)((m + 255) / 256), c);
-                k_mask_gen<<<grid, 256, 0, s>>>(g->prob, m, R, seed, ws->v_mask, nob, w0);
-            }
-            fill<uint64_t>(ws->v_cov, (uint64_t)c * n, 0ull, s);
-            a.w0 = w0;
-            k_spread<<<c, SPR_NT, 0, s>>>(a);
-        }
+        if (lanes == 64) k_spread<64><<<groups, 64, lds, s>>>(a);
+        else if (lanes == 128) k_spread<128><<<groups, 128, lds, s>>>(a);
+        else if (lanes == 256) k_spread<256><<<groups, 256, lds, s>>>(a);
+        else k_spread<512><<<groups, 512, lds, s>>>(a);
     }
     HIPCHK(hipGetLastError());
     ws->last_stream = s;
