@@ -33,6 +33,7 @@
 #include "im.h"
 #include "im_bfs.h"
 #include "im_rev.h"
+#include "im_bits.h"
 #include "im_lt.h"
 #include "im_spread.h"
 #include "im_host.h"
@@ -1403,6 +1404,11 @@ struct im_workspace {
     uint64_t cap_sp_m = 0, cap_sp_q = 0, cap_sp_b = 0;
     uint32_t *v_row32 = nullptr, *v_queue = nullptr, *v_bits = nullptr;
     ArcCoin *v_coin = nullptr;
+    // largest initial-count tasks by snapshot (im_bits.h)
+    uint64_t cap_cb = 0, cap_cb_any = 0;
+    uint32_t *cb_queue = nullptr, *cb_any = nullptr;
+    unsigned cb_waves = 0, cb_groups = 0;
+    bool cb_table = false;
     // linear-threshold snapshots
     int live_edge = 0;                   // 0: independent cascade, 1: linear threshold
     uint64_t *lt_start = nullptr;        // [m] start of each in-arc's draw interval
@@ -1603,6 +1609,7 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
     ws->und = nullptr;
     dfree(ws->pair);
     dfree(ws->lt_start); dfree(ws->lt_task);
+    dfree(ws->cb_queue); dfree(ws->cb_any);
     dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord); dfree(ws->lt_stamp); dfree(ws->lt_sc); dfree(ws->lt_pos);
     dfree(ws->a_reach); dfree(ws->a_pend); dfree(ws->a_qa); dfree(ws->a_qb); dfree(ws->a_vis);
     dfree(ws->a_mark); dfree(ws->a_list); dfree(ws->a_cnt); dfree(ws->a_ctrs);
@@ -1624,6 +1631,58 @@ static uint32_t slots_for(uint32_t n, uint32_t max_slots)
     if (s > max_slots) s = max_slots;
     if (s < 8) s = 8;
     return (uint32_t)s;
+}
+
+// Buffers of the initial counts by snapshot (im_bits.h) on instances of up to
+// nmax nodes: bitmaps with as many wavefronts per workgroup as have room for
+// theirs, at least four (up to 235,000 nodes), else tables (cb_groups = 0: the
+// dense tier alone)
+constexpr unsigned CB_LDS = 144u << 10;       // beside the kernel's own 10 KB
+
+static unsigned cb_lds(const im_workspace *ws, uint32_t nmax)
+{
+    return ws->cb_table ? ws->cb_waves * (unsigned)CB_CS * 4u : (ws->cb_waves + 1) * ((nmax + 31) / 32) * 4u;
+}
+
+template <bool TABLE>
+static unsigned cb_per_cu(const im_workspace *ws, uint32_t nmax)
+{
+    int b = 0;
+    if (hipFuncSetAttribute((const void *)k_cnt_bits<TABLE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)CB_LDS) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnt_bits<TABLE>, (int)ws->cb_waves * 64,
+                                                     cb_lds(ws, nmax)) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return (unsigned)b;
+}
+
+static void reserve_bits(im_workspace *ws, uint32_t nmax)
+{
+    constexpr uint64_t CB_BUDGET = 4ull << 30;
+    ws->cb_groups = 0;
+    if (!ws->sparse || t_arena || !nmax) return;
+    const uint64_t words = (nmax + 31) / 32;
+    ws->cb_waves = 9 * words * 4 <= CB_LDS ? 8 : 4;
+    ws->cb_table = 5 * words * 4 > CB_LDS;
+    if (ws->cb_table) ws->cb_waves = CB_WAVES;
+    const unsigned b = ws->cb_table ? cb_per_cu<true>(ws, nmax) : cb_per_cu<false>(ws, nmax);
+    const uint64_t per = (uint64_t)ws->cb_waves * (ws->cb_table ? (uint64_t)CB_CS : nmax);
+    const uint64_t fit = CB_BUDGET / 4 / (per + (ws->cb_table ? words : 0));
+    const uint64_t groups = std::min<uint64_t>((uint64_t)b * ws->num_cu, fit);
+    if (groups == 0) return;
+    if (groups * per > ws->cap_cb) {
+        ws->cap_cb = 0;
+        if (dalloc(&ws->cb_queue, groups * per)) return;
+        ws->cap_cb = groups * per;
+    }
+    if (ws->cb_table && groups * words > ws->cap_cb_any) {
+        ws->cap_cb_any = 0;
+        if (dalloc(&ws->cb_any, groups * words) || ws_memset(ws->cb_any, groups * words * 4)) return;
+        ws->cap_cb_any = groups * words;
+    }
+    ws->cb_groups = (unsigned)groups;
 }
 
 // tier-2 slot arrays of slot_len nodes each (the largest instance of a
@@ -1679,6 +1738,7 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
         ws->cap_n = cn;
     }
     if ((rc = reserve_slots(ws, slot_len))) return rc;
+    reserve_bits(ws, slot_len);
     if (grow_m) {
         if ((rc = dalloc(&ws->in_col, cm)) || (rc = dalloc(&ws->in2out, cm)) ||
             (rc = dalloc(&ws->mask_out, cm * cW)) || (rc = dalloc(&ws->mask_in, cm * cW)))
@@ -2022,6 +2082,32 @@ static unsigned per_cu(K kernel, int nt)
     return (unsigned)b;
 }
 
+// Last-tier initial counts by snapshot (im_bits.h). False: the dense tier takes
+// every task. Against the dense tier: weighted cascade, 60,000 nodes, R = 128:
+// 63 -> 31 ms (7 * 10^9 visited nodes/s; the lists' lines from beyond the L2 are
+// what bounds it, 1,024 dense slots instead of 256 took 45 ms); 16 uneven
+// instances 32 -> 12 ms; 15,000 nodes 1.8 -> 0.9 ms; 10^6 nodes, p = 0.01 (tables)
+// 6.0 -> 3.6 ms.
+static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, hipStream_t s)
+{
+    if (!ws->cb_groups || !t.sp.base || t.cand) return false;
+    BitsArgs a;
+    a.g.row = t.row; a.g.col = t.col; a.g.mask = t.mask; a.g.m = t.m; a.g.n = t.n; a.g.W = t.W;
+    a.g.hub = t.hub; a.g.sp = t.sp;
+    a.R = t.R;
+    a.node_inst = t.node_inst; a.inst_R = t.inst_R; a.inst_off = t.inst_off;
+    a.gain = t.gain;
+    a.in_q = t.in_q; a.in_n = t.in_n;
+    a.out_q = ws->ovf_q; a.out_n = ctr + 5; a.grab = ctr + 4;   // (ovf_q: tier 1 is done with it)
+    a.queue = ws->cb_queue; a.any = ws->cb_any; a.nmax = ws->slots_n;
+    a.stats = t.stats;
+    PhaseTimer pt(ws, ph, s);
+    const unsigned lds = cb_lds(ws, ws->slots_n);
+    if (ws->cb_table) k_cnt_bits<true><<<ws->cb_groups, ws->cb_waves * 64, lds, s>>>(a);
+    else k_cnt_bits<false><<<ws->cb_groups, ws->cb_waves * 64, lds, s>>>(a);
+    return true;
+}
+
 // Run every task of `a` through the three engine tiers. ctr: this phase's
 // zeroed counters. ph0: phase-timer id of tier 0 (ph0+1, ph0+2: tiers 1, 2).
 template <int MODE, bool PRUNE>
@@ -2063,6 +2149,10 @@ static void run_tiers(BfsArgs a, im_workspace *ws, uint32_t *ctr, int ph0, hipSt
     }
     a.in_q = ws->ovf_q2; a.in_n = ctr + 3;
     a.out_q = nullptr; a.out_n = nullptr; a.grab = ctr + 4; a.tier = 2;
+    if (MODE == MODE_COUNT && !PRUNE && cnt_bits(a, ws, ctr, ph0 + 2, s)) {
+        // only the tasks whose snapshots share their nodes are left
+        a.in_q = ws->ovf_q; a.in_n = ctr + 5; a.grab = ctr + 6;
+    }
     if (MODE == MODE_DEC) a.bsplit = ws->rev_split;
     {
         PhaseTimer pt(ws, ph0 + 2, s);
