@@ -3822,14 +3822,6 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
 // accessors for the other translation units
 UndState **im_ws_und(im_workspace *ws) { return &ws->und; }
 
-uint64_t im_scan_sums_len(uint64_t len) { return (len + SCAN_TILE - 1) / SCAN_TILE + 2; }
-
-void im_exclusive_scan(const uint32_t *in, uint32_t *out, uint64_t len, uint32_t *sums,
-                       hipStream_t s)
-{
-    if (len) exclusive_scan(in, out, len, sums, s);
-}
-
 int im_ws_validate(const im_graph *g, im_workspace *ws, hipStream_t s, uint32_t *row32)
 {
     return validate(g, ws, s, row32);
