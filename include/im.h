@@ -90,7 +90,11 @@ int im_workspace_destroy(im_workspace *ws);
  *     graph's round then runs one workgroup per word (same result), while
  *     batched selection, lazy engine 1 and a refusal during stream capture
  *     return IM_EHIP naming the cooperative kernel.
- *   IM_OPT_LAZY_ENGINE: exact evaluations of the lazy path run on the last
+ *   IM_OPT_LAZY_ENGINE: with engine 2 (default) and IM_OPT_EVAL_SPLIT 0, exact
+ *     evaluations of the lazy path run one workgroup per (candidate, snapshot)
+ *     where the batch's queues (4 bytes per node, candidate and snapshot) stay
+ *     within 16 GB and rounds run by snapshot (above); the round's seed is then
+ *     committed from its evaluation. Otherwise they run by word, on the last
  *     engine tier alone, one workgroup per (candidate, word) search (2,
  *     default: candidates are the nodes with the largest bounds, whose
  *     searches the smaller tiers would only hand on; when a batch's searches

@@ -406,8 +406,12 @@ struct FwdSnapArgs {
     uint8_t *sel;
     uint64_t *covered;               // [W][n]
     uint32_t *src;                   // a snapshot's queue: up to n (its instance's) nodes
-    uint2 *tasks;
+    uint2 *tasks;                    // nullptr: no reverse step follows
     uint32_t *ntasks;                // zero before the launch
+    // the lazy path's last evaluations (one graph; kept_n = 0: none), candidate
+    // j in snapshot r: kept_len[j R + r] nodes at kept_q + (j R + r) n
+    uint32_t kept_n;
+    const uint32_t *kept_src, *kept_len, *kept_q;
     uint32_t *stamp;                 // [W][n] last round (plus one) that newly covered the node
                                      // in any snapshot of the word, for the (node, word) counters
     unsigned long long *stats;
@@ -418,7 +422,7 @@ constexpr int FWS_NT = 512, FWS_Q = 4096;   // queue entries kept in LDS as well
 __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
 {
     __shared__ RevBig<FWS_NT> B;
-    __shared__ uint32_t q[FWS_Q], cnt, s_t0;
+    __shared__ uint32_t q[FWS_Q], cnt, s_t0, s_kept;
     __shared__ unsigned long long red[FWS_NT / 64];
     const uint32_t tid = threadIdx.x, inst = blockIdx.x / a.Rmax, r = blockIdx.x - inst * a.Rmax;
     const unsigned long long key = a.key[inst];
@@ -440,43 +444,54 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
     const unsigned long long bit = 1ull << b;
     unsigned long long *cov = (unsigned long long *)a.covered + (uint64_t)w * a.g.n;
     uint32_t *src = a.src + base;
-    if (tid == 0) {
-        const bool fresh = !(atomicOr(&cov[v], bit) & bit);
-        if (fresh) { q[0] = v; src[0] = v; }
-        cnt = fresh ? 1u : 0u;
-        B.n = 0;
-    }
+    if (tid == 0) { s_kept = IM_EMPTY; cnt = 0; B.n = 0; }
     __syncthreads();
-    uint64_t arcs = 0;
-    for (uint32_t head = 0;;) {
-        const uint32_t end = cnt;
-        __syncthreads();   // (cnt grows from here on)
-        if (head == end) break;
-        for (; head < end; head += FWS_NT) {
-            const uint32_t i = head + tid;
-            const bool take = i < end;
-            RevSpan sp = {0, 0, 0};
-            if (take) sp = rev_span(a.g, w, b, i < (uint32_t)FWS_Q ? q[i] : src[i]);
-            rev_expand<FWS_NT>(B, a.g, w, b, take, 0u, sp,
-                               [&](uint32_t, uint32_t y) {
-                                   if (atomicOr(&cov[y], bit) & bit) return;
-                                   const uint32_t p = atomicAdd(&cnt, 1u);
-                                   if (p < (uint32_t)FWS_Q) q[p] = y;
-                                   src[p] = y;
-                               },
-                               arcs);
+    for (uint32_t j = tid; j < a.kept_n; j += FWS_NT)
+        if (a.kept_src[j] == v) s_kept = j;   // candidates are distinct: one writer
+    __syncthreads();
+    const bool kept = s_kept != IM_EMPTY;
+    const uint32_t *list = src;   // queue entries past the first FWS_Q (kept: all)
+    uint32_t N;
+    if (kept) {
+        // the seed's own evaluation, pruned at covered, is its newly covered set
+        const uint64_t at = (uint64_t)s_kept * R + r;
+        list = a.kept_q + at * ni;
+        N = a.kept_len[at];
+        for (uint32_t i = tid; i < N; i += FWS_NT) atomicOr(&cov[list[i]], bit);
+    } else {
+        if (tid == 0 && !(atomicOr(&cov[v], bit) & bit)) { q[0] = v; src[0] = v; cnt = 1; }
+        __syncthreads();
+        uint64_t arcs = 0;
+        for (uint32_t head = 0;;) {
+            const uint32_t end = cnt;
+            __syncthreads();   // (cnt grows from here on)
+            if (head == end) break;
+            for (; head < end; head += FWS_NT) {
+                const uint32_t i = head + tid;
+                const bool take = i < end;
+                RevSpan sp = {0, 0, 0};
+                if (take) sp = rev_span(a.g, w, b, i < (uint32_t)FWS_Q ? q[i] : src[i]);
+                rev_expand<FWS_NT>(B, a.g, w, b, take, 0u, sp,
+                                   [&](uint32_t, uint32_t y) {
+                                       if (atomicOr(&cov[y], bit) & bit) return;
+                                       const uint32_t p = atomicAdd(&cnt, 1u);
+                                       if (p < (uint32_t)FWS_Q) q[p] = y;
+                                       src[p] = y;
+                                   },
+                                   arcs);
+            }
+            head = end;
         }
-        head = end;
+        N = cnt;
     }
-    const uint32_t N = cnt;
     uint64_t trav = 0, relax = 0, pairs = 0;
     for (uint32_t i = tid; i < N; i += FWS_NT) {
-        const uint32_t x = i < (uint32_t)FWS_Q ? q[i] : src[i];
+        const uint32_t x = !kept && i < (uint32_t)FWS_Q ? q[i] : list[i];
         const uint32_t od = a.g.row[x + 1] - a.g.row[x];
         trav += od;
         if (atomicExch(&a.stamp[(uint64_t)w * a.g.n + x], a.t + 1) != a.t + 1) { relax += od; pairs++; }
     }
-    const uint32_t nt = (N + 63) / 64;
+    const uint32_t nt = a.tasks ? (N + 63) / 64 : 0u;
     if (tid == 0) s_t0 = nt ? atomicAdd(a.ntasks, nt) : 0u;
     trav = group_sum<FWS_NT>(trav, red);
     relax = group_sum<FWS_NT>(relax, red);
@@ -487,5 +502,96 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
         stat_add(a.stats, ST_TRAV_FWD, trav);
         stat_add(a.stats, ST_RELAX_FWD, relax);
         stat_add(a.stats, ST_TASKS_REV, pairs);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Exact evaluations of the lazy path, one workgroup per (candidate, snapshot):
+// the number of nodes the candidate reaches in the snapshot that are not
+// covered. The queue stays where it is, for the commit of the round's seed.
+// A word's 64 snapshots in eight bit groups on dense slots (the engine this
+// stands in for) spend a level of about 17 us on atomics in memory; here it is
+// queue, list offsets, heads and covered, and a visit bit in LDS (in memory
+// past EVS_LDS_NODES nodes). Figures: select_lazy.
+// ---------------------------------------------------------------------------
+constexpr int EVS_NT = 256, EVS_Q = 2048;
+constexpr uint32_t EVS_LDS_NODES = 1u << 18;
+
+struct EvalSnapArgs {
+    SnapGraph g;
+    uint32_t R;
+    const uint32_t *cand, *ncand;    // [>= ncand], device count
+    const uint64_t *covered;         // [W][n]
+    uint32_t *ev;                    // [n], += per candidate (zero before)
+    uint32_t *kept_src, *kept_len, *kept_q;   // as in FwdSnapArgs
+    uint32_t *bits;                  // [grid][ceil(n / 32)], zero at rest; nullptr: LDS
+    unsigned long long *stats;
+};
+
+__global__ __launch_bounds__(EVS_NT) void k_eval_snap(EvalSnapArgs a)
+{
+    extern __shared__ uint32_t evs_bits[];
+    __shared__ RevBig<EVS_NT> B;
+    __shared__ uint32_t q[EVS_Q], cnt;
+    __shared__ unsigned long long red[EVS_NT / 64];
+    const uint32_t tid = threadIdx.x, j = blockIdx.x / a.R, r = blockIdx.x - j * a.R, n = a.g.n;
+    if (j >= *a.ncand) {
+        if (r == 0 && tid == 0) a.kept_src[j] = IM_EMPTY;
+        return;
+    }
+    const uint32_t v = a.cand[j], w = r / 64, b = r % 64, words = (n + 31) / 32;
+    const uint64_t bit = 1ull << b;
+    const uint64_t *cov = a.covered + (uint64_t)w * n;
+    uint32_t *list = a.kept_q + (uint64_t)blockIdx.x * n;
+    uint32_t *bits = a.bits ? a.bits + (uint64_t)blockIdx.x * words : evs_bits;
+    if (r == 0 && tid == 0) a.kept_src[j] = v;
+    if (cov[v] & bit) {   // uniform: covered in this snapshot
+        if (tid == 0) a.kept_len[blockIdx.x] = 0;
+        return;
+    }
+    if (!a.bits)
+        for (uint32_t i = tid; i < words; i += EVS_NT) bits[i] = 0;
+    if (tid == 0) { cnt = 0; B.n = 0; }
+    __syncthreads();
+    auto visit = [&](uint32_t y) {
+        if (cov[y] & bit) return;
+        const uint32_t m = 1u << (y & 31u);
+        if (atomicOr(&bits[y >> 5], m) & m) return;
+        const uint32_t p = atomicAdd(&cnt, 1u);
+        if (p < (uint32_t)EVS_Q) q[p] = y;
+        list[p] = y;
+    };
+    if (tid == 0) visit(v);
+    __syncthreads();
+    uint64_t arcs = 0, trav = 0;
+    for (uint32_t head = 0;;) {
+        const uint32_t end = cnt;
+        __syncthreads();   // (cnt grows from here on)
+        if (head == end) break;
+        for (; head < end; head += EVS_NT) {
+            const uint32_t i = head + tid;
+            const bool take = i < end;
+            RevSpan sp = {0, 0, 0};
+            if (take) {
+                const uint32_t x = i < (uint32_t)EVS_Q ? q[i] : list[i];
+                sp = rev_span(a.g, w, b, x);
+                trav += a.g.row[x + 1] - a.g.row[x];
+            }
+            rev_expand<EVS_NT>(B, a.g, w, b, take, 0u, sp, [&](uint32_t, uint32_t y) { visit(y); }, arcs);
+        }
+        head = end;
+    }
+    const uint32_t N = cnt;
+    if (a.bits)
+        for (uint32_t i = tid; i < N; i += EVS_NT) bits[(i < (uint32_t)EVS_Q ? q[i] : list[i]) >> 5] = 0;
+    trav = group_sum<EVS_NT>(trav, red);
+    arcs = group_sum<EVS_NT>(arcs, red);
+    if (tid == 0) {
+        a.kept_len[blockIdx.x] = N;
+        atomicAdd(&a.ev[v], N);
+        stat_add(a.stats, ST_TRAV_EVAL, trav);
+        stat_add(a.stats, st_tier(PASS_EVAL, 2, F_RELAX), trav);
+        stat_add(a.stats, st_tier(PASS_EVAL, 2, F_REACHED), N);
+        stat_add(a.stats, st_tier(PASS_EVAL, 2, F_ARCS), arcs);
     }
 }
