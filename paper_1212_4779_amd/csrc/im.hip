@@ -502,22 +502,22 @@ __global__ __launch_bounds__(HB_NT) void k_hub_fill(const uint32_t *row, const u
     }
 }
 
-// Per-snapshot live lists of the nodes below the hub threshold (degree >= 2;
-// see SparseLists). A workgroup takes 256 (node, word) pairs at a time and
-// spreads the arcs of its eligible pairs evenly over its lanes (node degrees
+// Per-snapshot live lists of the nodes below the hub threshold (see
+// SparseLists). A workgroup takes a tile of 256 nodes in one word at a time and
+// spreads the arcs of its eligible nodes evenly over its lanes (node degrees
 // are unrelated to node ids, so one row per lane would leave most lanes idle
-// behind the longest row); each arc's pair is found by a binary search over
-// the pairs' arc offsets, and consecutive lanes read consecutive mask words.
-// Every live (arc, snapshot) bit adds one to its pair's counter for that
-// snapshot (65 u16 counters per pair in LDS, updated by 32-bit atomics on the
-// half that holds them: a count stays below 2^16, so no carry crosses into
-// the neighbouring counter). Each lane then turns its pair's row into the 65
-// cumulative counts in place, the eligible rows are written out coalesced, one
-// atomic per workgroup reserves the heads, and the rows serve as each
-// snapshot's cursor while the heads are placed (so the heads of one
-// snapshot's list are in no particular order). Pairs of degree >= SP_MAXDEG,
-// and pairs whose lists do not fit the capacity, keep base = IM_EMPTY and are
-// expanded through the masks; their rows of cum are left unwritten.
+// behind the longest row); each arc's node is found by a binary search over
+// the nodes' arc offsets, and consecutive lanes read consecutive mask words.
+// Every live (arc, snapshot) bit adds one to its (snapshot, node) counter
+// (16-bit counters in LDS, updated by 32-bit atomics on the half that holds
+// them: a snapshot's row adds up to less than 2^16, so no carry crosses into
+// the neighbouring counter). Each wavefront turns 16 snapshots' rows into
+// exclusive prefixes in place, one atomic per workgroup reserves the heads,
+// the offsets go out coalesced, and the rows serve as cursors while the heads
+// are placed (so the heads of one list are in no particular order). Nodes of
+// degree >= SP_MAXDEG or the hub threshold, and tiles whose lists do not fit
+// the capacity, are marked SP_NONE and expanded through the hub lists or the
+// masks. The offsets are what bounds it: 4 bytes per (node, snapshot).
 constexpr uint32_t SP_MAXDEG = 256;
 
 __device__ __forceinline__ uint32_t sp_bump(uint32_t *cnt32, uint32_t i)
@@ -528,39 +528,35 @@ __device__ __forceinline__ uint32_t sp_bump(uint32_t *cnt32, uint32_t i)
 
 __global__ __launch_bounds__(256) void k_sparse_build(const uint32_t *row, const uint32_t *col,
                                                       const uint64_t *mask, uint64_t m, uint32_t n,
-                                                      uint32_t W, uint32_t hub_deg, uint32_t *base,
-                                                      uint16_t *cum, uint32_t *adj,
+                                                      uint32_t R, uint32_t W, uint32_t hub_deg,
+                                                      uint32_t *off, uint64_t stride, uint32_t *adj,
                                                       unsigned long long *alloc, uint64_t cap)
 {
     constexpr int U = 4;
     __shared__ uint32_t s_w[256 / 64 + 1];
     __shared__ unsigned long long s_base;
-    __shared__ uint32_t s_pre[256], s_e0[256], s_word[256], s_b0[256];
-    __shared__ uint8_t s_elig[256];
-    __shared__ __attribute__((aligned(16))) uint16_t s_cum[256 * 65];
-    uint32_t *cnt32 = (uint32_t *)s_cum;
-    const uint64_t P = (uint64_t)W * n;
-    const uint32_t t = threadIdx.x;
-    for (uint64_t p0 = (uint64_t)blockIdx.x * 256; p0 < P; p0 += (uint64_t)gridDim.x * 256) {
-        const uint64_t p = p0 + t;
-        uint32_t w = 0, e0 = 0, deg = 0;
-        bool elig = false;
-        if (p < P) {
-            w = (uint32_t)(p / n);
-            const uint32_t x = (uint32_t)(p - (uint64_t)w * n);
+    __shared__ uint32_t s_pre[256], s_e0[256], s_tot[64], s_row[64];
+    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64 * 256];   // [snapshot][node]
+    uint32_t *cnt32 = (uint32_t *)s_cnt;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
+    const uint32_t tiles = (n + 255) / 256;
+    for (uint64_t p = blockIdx.x; p < (uint64_t)W * tiles; p += gridDim.x) {
+        const uint32_t w = (uint32_t)(p / tiles), tile = (uint32_t)(p - (uint64_t)w * tiles);
+        const uint64_t x = (uint64_t)tile * 256u + t;
+        const uint64_t *mw = mask + (uint64_t)w * m;
+        uint32_t e0 = 0, deg = 0;
+        bool elig = true;
+        if (x < n) {
             e0 = row[x];
             deg = row[x + 1] - e0;
-            elig = deg >= 2 && deg < SP_MAXDEG && (hub_deg == 0 || deg < hub_deg);
+            elig = deg < SP_MAXDEG && (hub_deg == 0 || deg < hub_deg);
         }
-        for (uint32_t j = t; j < 256 * 65 / 2; j += 256) cnt32[j] = 0u;
+        for (uint32_t j = t; j < 64 * 256 / 2; j += 256) cnt32[j] = 0u;
         uint32_t T;
         const uint32_t pre = block_excl_scan<256>(elig ? deg : 0u, s_w, &T);
         s_pre[t] = pre;
         s_e0[t] = e0;
-        s_word[t] = w;
-        s_elig[t] = elig ? 1 : 0;
         __syncthreads();
-        // count: the pair's counter b+1 for every live bit b
         for (uint32_t j0 = t; j0 < T; j0 += 256 * U) {
             uint64_t b[U];
             uint32_t q[U];
@@ -571,48 +567,43 @@ __global__ __launch_bounds__(256) void k_sparse_build(const uint32_t *row, const
                 q[u] = 0;
                 if (j < T) {
                     q[u] = (uint32_t)upper_index<256>(s_pre, j);
-                    b[u] = mask[(uint64_t)s_word[q[u]] * m + s_e0[q[u]] + (j - s_pre[q[u]])];
+                    b[u] = mw[s_e0[q[u]] + (j - s_pre[q[u]])];
                 }
             }
 #pragma unroll
             for (int u = 0; u < U; u++)
                 for (uint64_t v = b[u]; v; v &= v - 1)
-                    sp_bump(cnt32, q[u] * 65 + (uint32_t)__ffsll((unsigned long long)v));
+                    sp_bump(cnt32, ((uint32_t)__ffsll((unsigned long long)v) - 1) * 256u + q[u]);
         }
         __syncthreads();
-        // inclusive prefix over the row: cp[b] = heads live in snapshots before b
-        uint16_t *cp = s_cum + t * 65;
-        uint32_t total = 0;
-        if (elig) {
-            for (uint32_t bb = 1; bb < 65; bb++) cp[bb] = (uint16_t)(cp[bb] + cp[bb - 1]);
-            total = cp[64];
+        // exclusive prefix over each snapshot's row, four nodes per lane
+        for (uint32_t b = wv * 16; b < wv * 16 + 16; b++) {
+            uint2 *r = (uint2 *)(s_cnt + b * 256) + lane;
+            const uint2 v = *r;
+            const uint32_t c0 = v.x & 0xFFFFu, c1 = v.x >> 16, c2 = v.y & 0xFFFFu, c3 = v.y >> 16;
+            const uint32_t sum = c0 + c1 + c2 + c3, incl = wave_incl_scan(sum), ex = incl - sum;
+            *r = make_uint2(ex | ((ex + c0) << 16), (ex + c0 + c1) | ((ex + c0 + c1 + c2) << 16));
+            if (lane == 63) s_tot[b] = incl;
         }
-        uint32_t blk;
-        const uint32_t ex = block_excl_scan<256>(total, s_w, &blk);   // syncs: rows complete
-        {
-            // eligible rows out, as aligned 32-bit words (p0 is a multiple of 256);
-            // a word shared by two rows is written when either row is eligible
-            const uint64_t npair = min((uint64_t)256, P - p0);
-            const uint32_t nu16 = (uint32_t)(npair * 65), nwords = (nu16 + 1) / 2;
-            uint32_t *dst = (uint32_t *)(cum + p0 * 65);
-            for (uint32_t j = t; j < nwords; j += 256) {
-                const uint32_t qa = 2 * j / 65, qb = (2 * j + 1) / 65;
-                if (2 * j + 1 < nu16) {
-                    if (s_elig[qa] | s_elig[qb]) dst[j] = cnt32[j];
-                } else if (s_elig[qa]) {
-                    cum[p0 * 65 + 2 * j] = s_cum[2 * j];   // odd tail: one u16
-                }
-            }
+        __syncthreads();
+        if (wv == 0) {
+            const uint32_t incl = wave_incl_scan(s_tot[lane]);
+            s_row[lane] = incl - s_tot[lane];
+            if (lane == 63) s_base = incl ? atomicAdd(alloc, (unsigned long long)incl) : 0ull;
         }
-        if (t == 0) s_base = blk ? atomicAdd(alloc, (unsigned long long)blk) : 0ull;
         __syncthreads();
-        const unsigned long long b0 = s_base + ex;
-        const bool fits = elig && b0 + total <= cap;
-        if (p < P) base[p] = fits ? (uint32_t)b0 : IM_EMPTY;
-        s_b0[t] = fits ? (uint32_t)b0 : IM_EMPTY;
+        const bool fits = s_base + s_row[63] + s_tot[63] <= cap;
+        const uint32_t base = fits ? (uint32_t)s_base : 0u, none = fits && elig ? 0u : SP_NONE;
+        const uint32_t rows = min(64u, R - w * 64u);
+        uint32_t *dst = off + (uint64_t)w * 64u * stride + (uint64_t)tile * 257u;
+        for (uint32_t b = 0; b < rows; b++) {
+            uint32_t *d = dst + (uint64_t)b * stride;
+            d[t] = (base + s_row[b] + s_cnt[b * 256 + t]) | none;
+            if (t == 0) d[256] = base + s_row[b] + s_tot[b];
+        }
         __syncthreads();
-        // place: the row now serves as each snapshot's cursor
-        for (uint32_t j0 = t; j0 < T; j0 += 256 * U) {
+        // place: the rows now serve as cursors
+        for (uint32_t j0 = t; fits && j0 < T; j0 += 256 * U) {
             uint64_t b[U];
             uint32_t q[U], e[U];
 #pragma unroll
@@ -624,20 +615,20 @@ __global__ __launch_bounds__(256) void k_sparse_build(const uint32_t *row, const
                 if (j < T) {
                     q[u] = (uint32_t)upper_index<256>(s_pre, j);
                     e[u] = s_e0[q[u]] + (j - s_pre[q[u]]);
-                    if (s_b0[q[u]] != IM_EMPTY) b[u] = mask[(uint64_t)s_word[q[u]] * m + e[u]];
+                    b[u] = mw[e[u]];
                 }
             }
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 if (!b[u]) continue;
-                const uint32_t v = col[e[u]], hb = s_b0[q[u]];
+                const uint32_t v = col[e[u]];
                 for (uint64_t bits = b[u]; bits; bits &= bits - 1) {
                     const uint32_t bit = (uint32_t)__ffsll((unsigned long long)bits) - 1;
-                    adj[hb + sp_bump(cnt32, q[u] * 65 + bit)] = v;
+                    adj[base + s_row[bit] + sp_bump(cnt32, bit * 256u + q[u])] = v;
                 }
             }
         }
-        __syncthreads();   // the LDS arrays and s_base are rewritten by the next chunk
+        __syncthreads();   // the LDS arrays and s_base are rewritten by the next tile
     }
 }
 
@@ -1004,7 +995,7 @@ __global__ __launch_bounds__(FWD_NT) void k_forward_coop(FwdArgs a)
                 } else {
                     uint32_t work, srs, saux;
                     uint64_t sdel;
-                    if (deg >= 2 && sparse_use(sparse_fetch(a.sp, a.n, w, x, d), deg, work, srs, sdel, saux)) {
+                    if (deg >= 2 && sparse_use(sparse_fetch(a.sp, w, x, d), deg, work, srs, sdel, saux)) {
                         deg = work; rs = srs; d = sdel; aux = saux;
                     }
                 }
@@ -1164,7 +1155,7 @@ __global__ __launch_bounds__(FWB_NT) void k_forward_block(FwdArgs a)
         return;
     }
     uint64_t arcs = 0;
-    const SparseLists no_lists = {nullptr, nullptr, nullptr};
+    const SparseLists no_lists = {nullptr, nullptr, 0};
     block_bfs_run<FWB_NT, 8, true, false>(L, v, tid == 0 ? start : 0ull, a.row, a.col, a.mask + (uint64_t)w * a.m, a.hub,
                                    no_lists, a.n, a.W, w, a.covered + off, a.newly + off, a.pend + off, 0u,
                                    a.bq0 + off, a.bq1 + off, a.tnodes + off, arcs);
@@ -1369,9 +1360,8 @@ struct im_workspace {
     uint32_t *hnum = nullptr;            // [2] hub counts
     // per-snapshot live lists of the other nodes, per direction
     int sparse = 1;
-    uint64_t sp_nW = 0, sp_cap = 0;
-    uint32_t *sp_base[2] = {}, *sp_adj[2] = {};
-    uint16_t *sp_cum[2] = {};
+    uint64_t sp_len = 0, sp_cap = 0;
+    uint32_t *sp_off[2] = {}, *sp_adj[2] = {};
     unsigned long long *sp_alloc = nullptr;  // [2]
     unsigned long long *halloc = nullptr;  // [2] allocation counters
     // block engine slots
@@ -1597,7 +1587,7 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
         dfree(ws->hadj[d]); dfree(ws->hbase[d]);
     }
     dfree(ws->hnum); dfree(ws->halloc);
-    for (int d = 0; d < 2; d++) { dfree(ws->sp_base[d]); dfree(ws->sp_cum[d]); dfree(ws->sp_adj[d]); }
+    for (int d = 0; d < 2; d++) { dfree(ws->sp_off[d]); dfree(ws->sp_adj[d]); }
     dfree(ws->sp_alloc);
     dfree(ws->b_node_inst); dfree(ws->b_mcol); dfree(ws->b_mprob); dfree(ws->b_u32);
     dfree(ws->b_u64); dfree(ws->b_desc);
@@ -1710,6 +1700,8 @@ static int reserve_slots(im_workspace *ws, uint32_t slot_len)
     return IM_OK;
 }
 
+static uint64_t sparse_stride(uint32_t n) { return ((uint64_t)n + 255) / 256 * 257; }
+
 // grow the workspace to hold a graph with n nodes, m arcs, W words, k rounds
 static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint32_t k,
                       uint32_t slot_len)
@@ -1766,13 +1758,12 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
         ws->cap_hub = ch;
     }
     if (ws->sparse) {
-        const uint64_t nW = (uint64_t)ws->cap_n * cW;
-        if (nW > ws->sp_nW) {
+        const uint64_t len = sparse_stride(ws->cap_n) * 64u * cW;
+        if (len > ws->sp_len) {
             for (int d = 0; d < 2; d++)
-                if ((rc = dalloc(&ws->sp_base[d], nW)) || (rc = dalloc(&ws->sp_cum[d], nW * 65)))
-                    return rc;
+                if ((rc = dalloc(&ws->sp_off[d], len))) return rc;
             if ((rc = dalloc(&ws->sp_alloc, 2))) return rc;
-            ws->sp_nW = nW;
+            ws->sp_len = len;
         }
         const uint64_t cap = std::min<uint64_t>(16ull * ws->cap_m * cW, 0x7FFFFFFFull);
         if (cap > ws->sp_cap) {
@@ -2029,23 +2020,23 @@ static void build_hubs(int d, const uint32_t *row, const uint32_t *col, const ui
 
 // A2c: per-snapshot live lists of the non-hub nodes for one direction
 static void build_sparse(int d, const uint32_t *row, const uint32_t *col, const uint64_t *mask,
-                         uint32_t n, uint64_t m, uint32_t W, im_workspace *ws, hipStream_t s)
+                         uint32_t n, uint64_t m, uint32_t R, im_workspace *ws, hipStream_t s)
 {
     if (!ws->sparse || n == 0) return;
     fill<unsigned long long>(ws->sp_alloc + d, 1, 0ull, s);
-    const uint64_t P = (uint64_t)W * n;
-    const unsigned grid = (unsigned)std::min<uint64_t>((P + 255) / 256, 8192);
-    k_sparse_build<<<grid, 256, 0, s>>>(row, col, mask, m, n, W, ws->hub_deg, ws->sp_base[d],
-                                        ws->sp_cum[d], ws->sp_adj[d], ws->sp_alloc + d, ws->sp_cap);
+    const uint32_t W = (R + 63) / 64;
+    const unsigned grid = (unsigned)std::min<uint64_t>((uint64_t)W * ((n + 255) / 256), 8192);
+    k_sparse_build<<<grid, 256, 0, s>>>(row, col, mask, m, n, R, W, ws->hub_deg, ws->sp_off[d],
+                                        sparse_stride(n), ws->sp_adj[d], ws->sp_alloc + d, ws->sp_cap);
 }
 
-static SparseLists sparse_lists(im_workspace *ws, int d)
+static SparseLists sparse_lists(im_workspace *ws, int d, uint32_t n)
 {
-    SparseLists l = {nullptr, nullptr, nullptr};
+    SparseLists l = {nullptr, nullptr, 0};
     if (ws->sparse) {
-        l.base = ws->sp_base[d];
-        l.cum = ws->sp_cum[d];
+        l.off = ws->sp_off[d];
         l.adj = ws->sp_adj[d];
+        l.stride = sparse_stride(n);
     }
     return l;
 }
@@ -2093,7 +2084,7 @@ static unsigned per_cu(K kernel, int nt)
 // 6.0 -> 3.6 ms.
 static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, hipStream_t s)
 {
-    if (!ws->cb_groups || !t.sp.base || t.cand) return false;
+    if (!ws->cb_groups || !t.sp.off || t.cand) return false;
     BitsArgs a;
     a.g.row = t.row; a.g.col = t.col; a.g.mask = t.mask; a.g.m = t.m; a.g.n = t.n; a.g.W = t.W;
     a.g.hub = t.hub; a.g.sp = t.sp;
@@ -2197,7 +2188,7 @@ static void initial_gains(const im_graph *g, uint32_t R, im_workspace *ws, uint3
     BfsArgs a = bfs_args(ws, ws->row32, g->col, ws->mask_out, g->m, n, R, W);
     a.ntasks = n * W;
     a.hub = hub_lists(ws, 0);
-    a.sp = sparse_lists(ws, 0);
+    a.sp = sparse_lists(ws, 0, g->n);
     a.pass = PASS_INIT;
     a.st_trav = ST_TRAV_INIT;
     run_tiers<MODE_COUNT, false>(a, ws, ctr, IM_PH_INIT_T0, s);
@@ -2288,7 +2279,7 @@ static void affected_update(const im_graph *g, uint32_t R, uint32_t t, im_worksp
         AffArgs f;
         f.key = ws->keys + t; f.aff_gain = ws->aff_gain;
         f.row = ws->in_row; f.col = ws->in_col; f.mask = ws->mask_in; f.m = g->m;
-        f.hub = hub_lists(ws, 1); f.sp = sparse_lists(ws, 1);
+        f.hub = hub_lists(ws, 1); f.sp = sparse_lists(ws, 1, g->n);
         f.n = n; f.W = W;
         f.tnodes = ws->tnodes; f.tcounts = ws->tcounts; f.newly = ws->newly;
         f.reach = ws->a_reach; f.pend = ws->a_pend;
@@ -2304,7 +2295,7 @@ static void affected_update(const im_graph *g, uint32_t R, uint32_t t, im_worksp
     a.gain = ws->gain;
     a.prune = ws->covered;
     a.hub = hub_lists(ws, 0);
-    a.sp = sparse_lists(ws, 0);
+    a.sp = sparse_lists(ws, 0, g->n);
     a.pass = PASS_EVAL;
     a.st_trav = ST_TRAV_EVAL;
     run_tiers<MODE_COUNT, true>(a, ws, ws->a_ctrs + (uint64_t)t * PH_CTRS, IM_PH_EVAL_T0, s);
@@ -2404,7 +2395,7 @@ static SnapGraph snap_graph(const im_graph *g, uint32_t W, int d, im_workspace *
     s.mask = d ? ws->mask_in : ws->mask_out;
     s.m = g->m; s.n = g->n; s.W = W;
     s.hub = hub_lists(ws, d);
-    s.sp = sparse_lists(ws, d);
+    s.sp = sparse_lists(ws, d, g->n);
     return s;
 }
 
@@ -2491,7 +2482,7 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
     f.skip = nullptr;
     f.row = ws->row32; f.col = g->col; f.mask = ws->mask_out; f.m = g->m;
     f.hub = hub_lists(ws, 0);
-    f.sp = sparse_lists(ws, 0);
+    f.sp = sparse_lists(ws, 0, g->n);
     f.n = n; f.R = R; f.W = W;
     f.covered = ws->covered; f.newly = ws->newly; f.pend = ws->fpend;
     f.fq0 = ws->fqa; f.fq1 = ws->fqb; f.cnt = ws->fctr + (uint64_t)t * FWD_CTRS;
@@ -2523,7 +2514,7 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
     a.gcnt = gcnt; a.mcnt = mcnt; a.bcnt = bcnt; a.boff = ws->boff;
     a.plist = ws->plist; a.mlist = ws->mlist; a.tbits = ws->newly;
     a.hub = hub_lists(ws, 1);
-    a.sp = sparse_lists(ws, 1);
+    a.sp = sparse_lists(ws, 1, g->n);
     a.pass = PASS_REV;
     a.st_trav = ST_TRAV_REV;
     run_tiers<MODE_DEC, false>(a, ws, ctr, IM_PH_REV_T0, s);
@@ -2632,10 +2623,10 @@ static int enqueue_prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_
     {
         PhaseTimer pt(ws, IM_PH_HUBS, s);
         build_hubs(0, ws->row32, g->col, ws->mask_out, n, g->m, W, ws, s);
-        build_sparse(0, ws->row32, g->col, ws->mask_out, n, g->m, W, ws, s);
+        build_sparse(0, ws->row32, g->col, ws->mask_out, n, g->m, R, ws, s);
         if (rev) {
             build_hubs(1, ws->in_row, ws->in_col, ws->mask_in, n, g->m, W, ws, s);
-            build_sparse(1, ws->in_row, ws->in_col, ws->mask_in, n, g->m, W, ws, s);
+            build_sparse(1, ws->in_row, ws->in_col, ws->mask_in, n, g->m, R, ws, s);
         }
     }
     initial_gains(g, R, ws, ws->ctrs, s);
@@ -3263,7 +3254,7 @@ __global__ __launch_bounds__(FWD_NT) void k_eval_coop(EvalArgs a)
                 } else {
                     uint32_t work, srs, saux;
                     uint64_t sdel;
-                    if (deg >= 2 && sparse_use(sparse_fetch(a.sp, a.n, vw % a.W, x, d), deg, work, srs, sdel, saux)) {
+                    if (deg >= 2 && sparse_use(sparse_fetch(a.sp, vw % a.W, x, d), deg, work, srs, sdel, saux)) {
                         deg = work; rs = srs; d = sdel; aux = saux;
                     }
                 }
@@ -3430,7 +3421,7 @@ static int eval_coop(const im_graph *g, uint32_t R, uint32_t ncand, uint32_t vma
     const uint32_t n = g->n, W = (R + 63) / 64, per = vmax / W;
     EvalArgs e;
     e.row = ws->row32; e.col = g->col; e.mask = ws->mask_out; e.hub = hub_lists(ws, 0);
-    e.sp = sparse_lists(ws, 0);
+    e.sp = sparse_lists(ws, 0, g->n);
     e.m = g->m; e.n = n; e.R = R; e.W = W;
     e.covered = ws->covered; e.reach = ws->e_reach; e.pend = ws->e_pend;
     e.fq0 = ws->e_fq0; e.fq1 = ws->e_fq1; e.vis = ws->e_vis; e.cnt = ws->e_cnt;
@@ -3486,7 +3477,7 @@ static int commit_seed(const im_graph *g, uint32_t R, uint32_t t, uint32_t *seed
     f.skip = skip;
     f.row = ws->row32; f.col = g->col; f.mask = ws->mask_out; f.m = g->m;
     f.hub = hub_lists(ws, 0);
-    f.sp = sparse_lists(ws, 0);
+    f.sp = sparse_lists(ws, 0, g->n);
     f.n = n; f.R = R; f.W = W;
     f.covered = ws->covered; f.newly = ws->newly; f.pend = ws->fpend;
     f.fq0 = ws->fqa; f.fq1 = ws->fqb; f.cnt = ws->fctr + (uint64_t)t * FWD_CTRS;
@@ -3764,7 +3755,7 @@ static int select_lazy(const im_graph *g, uint32_t R, uint32_t k, uint32_t B, co
                 a.gain = ws->c_ev;
                 a.prune = ws->covered;
                 a.hub = hub_lists(ws, 0);
-                a.sp = sparse_lists(ws, 0);
+                a.sp = sparse_lists(ws, 0, g->n);
                 a.pass = PASS_EVAL;
                 a.st_trav = ST_TRAV_EVAL;
                 if (ws->lazy_engine == 2 && ws->batch.count == 1 && ncand * W <= ws->slots) {

@@ -70,18 +70,30 @@ struct HubLists {
     uint32_t min_deg;       // nodes with fewer arcs have no lists (slot[x] is IM_EMPTY)
 };
 
-// Per-snapshot live lists of the other nodes (degree >= 2, below the hub
-// threshold): for node x and word w (p = w*n + x) the heads live in snapshot
-// 64w+b are adj[base[p] + cum[p*65+b] .. base[p] + cum[p*65+b+1]);
-// base[p] = IM_EMPTY: x has no lists in word w. A frontier entry whose delta
-// has at most SP_BITS bits is expanded through them when they hold no more
-// heads than x has arcs: the heads carry their single snapshot bit, so only
-// arcs live in the delta's snapshots are read.
+// Per-snapshot live lists of the other nodes (below the hub threshold and
+// SP_MAXDEG). off is snapshot-major, tiles of 256 nodes with one closing entry
+// each: with i = (64w+b) stride + x + x / 256, the heads of x's arcs live in
+// snapshot 64w+b are adj[off[i] .. off[i+1]) (closing entries and SP_NONE
+// aside). SP_NONE set in off[i]: x has no lists in word w. One snapshot's
+// offsets and heads lie together, and both ends of a list in one line: word-
+// major counts (a base and 65 16-bit counts per (node, word)) took three lines
+// a list. A frontier entry whose delta has at most SP_BITS bits is expanded
+// through them when they hold no more heads than x has arcs: the heads carry
+// their single snapshot bit, so only arcs live in the delta's snapshots are
+// read.
 struct SparseLists {
-    const uint32_t *base;   // [W][n], nullptr: no lists
-    const uint16_t *cum;    // [W][n][65]
+    const uint32_t *off;    // [64 W][stride], nullptr: no lists
     const uint32_t *adj;
+    uint64_t stride;        // 257 ceil(n / 256)
 };
+constexpr uint32_t SP_NONE = 0x80000000u;
+
+// where the list of x in snapshot r starts in off
+__device__ __forceinline__ uint64_t sparse_at(const SparseLists &sp, uint32_t r, uint32_t x)
+{
+    return (uint64_t)r * sp.stride + x + (x >> 8);
+}
+
 constexpr int SP_BITS = 2;
 
 // Plan the sparse expansion of x with delta d in word w. On success the
@@ -89,30 +101,26 @@ constexpr int SP_BITS = 2;
 // two ranges: rs = start of the first, del = start of the second | len0 << 32
 // | len1 << 48, aux = bit0 | bit1 << 8 | 1 << 16 (aux = 0: dense entry).
 // The plan is split in two so that its loads can be issued together with the
-// entry's row and hub-slot loads: sparse_fetch reads the list base and the
-// four cumulative counts that the delta's bits select (in bounds for every
-// x < n, w < W; the counts are unused when the base is empty), sparse_use
-// decides once the degree is known.
+// entry's row and hub-slot loads: sparse_fetch reads the list bounds that the
+// delta's bits select, sparse_use decides once the degree is known.
 struct SparsePre {
-    uint32_t b0, c00, c01, c10, c11, i0, i1;
+    uint32_t s0, e0, s1, e1, i0, i1;
     bool ok, two;
 };
 
-__device__ __forceinline__ SparsePre sparse_fetch(const SparseLists &sp, uint32_t n, uint32_t w,
-                                                  uint32_t x, uint64_t d)
+__device__ __forceinline__ SparsePre sparse_fetch(const SparseLists &sp, uint32_t w, uint32_t x, uint64_t d)
 {
     SparsePre q;
-    q.ok = sp.base && d != 0 && __popcll(d) <= SP_BITS;
-    q.b0 = IM_EMPTY; q.c00 = q.c01 = q.c10 = q.c11 = 0; q.i0 = q.i1 = 0; q.two = false;
+    q.ok = sp.off && d != 0 && __popcll(d) <= SP_BITS;
+    q.s0 = q.e0 = q.s1 = q.e1 = 0; q.i0 = q.i1 = 0; q.two = false;
     if (q.ok) {
-        const uint64_t p = (uint64_t)w * n + x;
         const uint64_t d1 = d & (d - 1);
         q.two = d1 != 0;
         q.i0 = (uint32_t)__ffsll((unsigned long long)d) - 1;
         q.i1 = q.two ? (uint32_t)__ffsll((unsigned long long)d1) - 1 : q.i0;
-        const uint16_t *c = sp.cum + p * 65;
-        q.b0 = sp.base[p];
-        q.c00 = c[q.i0]; q.c01 = c[q.i0 + 1]; q.c10 = c[q.i1]; q.c11 = c[q.i1 + 1];
+        const uint32_t *o0 = sp.off + sparse_at(sp, w * 64u + q.i0, x);
+        const uint32_t *o1 = sp.off + sparse_at(sp, w * 64u + q.i1, x);
+        q.s0 = o0[0]; q.e0 = o0[1]; q.s1 = o1[0]; q.e1 = o1[1];
     }
     return q;
 }
@@ -120,12 +128,12 @@ __device__ __forceinline__ SparsePre sparse_fetch(const SparseLists &sp, uint32_
 __device__ __forceinline__ bool sparse_use(const SparsePre &q, uint32_t deg, uint32_t &work,
                                            uint32_t &rs, uint64_t &del, uint32_t &aux)
 {
-    if (!q.ok || deg < 2 || q.b0 == IM_EMPTY) return false;
-    const uint32_t l0 = q.c01 - q.c00, l1 = q.two ? q.c11 - q.c10 : 0u;
+    if (!q.ok || deg < 2 || (q.s0 & SP_NONE)) return false;
+    const uint32_t l0 = (q.e0 & ~SP_NONE) - q.s0, l1 = q.two ? (q.e1 & ~SP_NONE) - q.s1 : 0u;
     if (l0 + l1 > deg) return false;
     work = l0 + l1;
-    rs = q.b0 + q.c00;
-    del = (uint64_t)(q.b0 + q.c10) | ((uint64_t)l0 << 32) | ((uint64_t)l1 << 48);
+    rs = q.s0;
+    del = (uint64_t)q.s1 | ((uint64_t)l0 << 32) | ((uint64_t)l1 << 48);
     aux = q.i0 | (q.i1 << 8) | (1u << 16);
     return true;
 }
@@ -599,7 +607,7 @@ __global__ __launch_bounds__(NT) void k_lds_bfs(BfsArgs a)
                     uint32_t hs = a.hub.slot ? a.hub.slot[x] : IM_EMPTY;
                     rs = a.row[x];
                     const uint32_t re = a.row[x + 1];
-                    const SparsePre sq = sparse_fetch(a.sp, a.n, L.s_word[s], x, delta);
+                    const SparsePre sq = sparse_fetch(a.sp, L.s_word[s], x, delta);
                     deg = re - rs;
                     L.deg[idx] = deg;
                     if (hs != IM_EMPTY) {
@@ -875,7 +883,7 @@ __device__ void block_bfs_run(BlockLds<NT> &L, uint32_t src, uint64_t start,
                 } else if (SPARSE && deg >= 2) {   // (no lists below 2 arcs: skip their loads)
                     uint32_t work, srs, saux;
                     uint64_t sdel;
-                    if (sparse_use(sparse_fetch(sp, n, w, x, d), deg, work, srs, sdel, saux)) {
+                    if (sparse_use(sparse_fetch(sp, w, x, d), deg, work, srs, sdel, saux)) {
                         deg = work; rs = srs; d = sdel; aux = saux;
                     }
                 }

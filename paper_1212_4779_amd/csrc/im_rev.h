@@ -73,16 +73,14 @@ struct RevSpan {
 
 __device__ __forceinline__ RevSpan rev_span(const SnapGraph &a, uint32_t w, uint32_t b, uint32_t x)
 {
-    const uint64_t p = (uint64_t)w * a.n + x;
-    // independent loads; the counts of a node without lists are not used
-    const uint16_t *c = a.sp.cum + p * 65 + b;
-    const uint32_t rs = a.row[x], re = a.row[x + 1], base = a.sp.base[p];
-    const uint32_t c0 = c[0], c1 = c[1], deg = re - rs;
+    const uint32_t *o = a.sp.off + sparse_at(a.sp, w * 64u + b, x);
+    const uint32_t first = o[0], end = o[1];
     RevSpan s;
-    if (base != IM_EMPTY) {
-        s.start = base + c0; s.len = c1 - c0; s.kind = 0;
+    if (!(first & SP_NONE)) {
+        s.start = first; s.len = (end & ~SP_NONE) - first; s.kind = 0;
         return s;
     }
+    const uint32_t rs = a.row[x], deg = a.row[x + 1] - rs;
     const uint32_t hs = deg >= a.hub.min_deg ? a.hub.slot[x] : IM_EMPTY;
     if (hs != IM_EMPTY) {
         const uint32_t *o = a.hub.off + ((uint64_t)hs * a.W + w) * 65 + b;
