@@ -1700,6 +1700,12 @@ static int reserve_slots(im_workspace *ws, uint32_t slot_len)
     return IM_OK;
 }
 
+// Covered nodes: by word, [W][n] 64-bit words; rounds by snapshot take the same
+// memory as one bit per node, [R][cov_words]
+static uint64_t cov_words(uint32_t n) { return ((uint64_t)n + 31) / 32; }
+
+static uint64_t cov_len(uint32_t n, uint32_t W) { return std::max((uint64_t)n * W, cov_words(n) * 32u * W); }
+
 static uint64_t sparse_stride(uint32_t n) { return ((uint64_t)n + 255) / 256 * 257; }
 
 // grow the workspace to hold a graph with n nodes, m arcs, W words, k rounds
@@ -1716,7 +1722,7 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
         if ((rc = dalloc(&ws->row32, nn)) || (rc = dalloc(&ws->in_row, nn)) ||
             (rc = dalloc(&ws->cnt, nn)) || (rc = dalloc(&ws->scan_sums, nn / SCAN_TILE + 2)) ||
             (rc = dalloc(&ws->gain, cn)) || (rc = dalloc(&ws->sel, cn)) ||
-            (rc = dalloc(&ws->covered, nW)) || (rc = dalloc(&ws->newly, nW)) ||
+            (rc = dalloc(&ws->covered, t_arena ? nW : cov_len(cn, cW))) || (rc = dalloc(&ws->newly, nW)) ||
             (rc = dalloc(&ws->fpend, nW)) ||
             (rc = dalloc(&ws->fqa, nW)) || (rc = dalloc(&ws->fqb, nW)) || (rc = dalloc(&ws->fvis, nW)) ||
             (rc = dalloc(&ws->bqa, nW)) || (rc = dalloc(&ws->bqb, nW)) ||
@@ -2409,12 +2415,16 @@ static FwdSnapArgs fwd_snap_args(const im_graph *g, uint32_t R, uint32_t t, uint
     f.R = R; f.Rmax = R; f.t = t;
     f.key = ws->keys + (uint64_t)t * ws->batch.count;
     f.seeds_out = seeds_out; f.gains_out = gains_out; f.sel = ws->sel;
-    f.covered = ws->covered;
+    f.cov = (uint32_t *)ws->covered; f.cwords = cov_words(g->n);
+    f.nlds = ws->slots_n <= FWS_LDS_NODES ? ws->slots_n : 0u;
     f.src = ws->rv_src; f.tasks = nullptr; f.ntasks = nullptr; f.stamp = ws->rv_stamp;
     f.kept_n = 0; f.kept_src = nullptr; f.kept_len = nullptr; f.kept_q = nullptr;
     f.stats = ws->stats;
     return f;
 }
+
+// (an instance's bits may begin and end inside a word)
+static unsigned fws_lds(const FwdSnapArgs &f) { return f.nlds ? (f.nlds + 31) / 32 * 4u + 4u : 0u; }
 
 static void rev_search(const im_graph *g, uint32_t R, uint32_t t, uint32_t *seeds_out,
                        uint64_t *gains_out, im_workspace *ws, uint32_t *ctr, hipStream_t s)
@@ -2425,7 +2435,7 @@ static void rev_search(const im_graph *g, uint32_t R, uint32_t t, uint32_t *seed
         FwdSnapArgs f = fwd_snap_args(g, R, t, seeds_out, gains_out, ws);
         f.tasks = ws->rv_tasks; f.ntasks = ntasks;
         PhaseTimer pt(ws, IM_PH_FORWARD, s);
-        k_fwd_snap<<<ws->batch.count * R, FWS_NT, 0, s>>>(f);
+        k_fwd_snap<<<ws->batch.count * R, FWS_NT, fws_lds(f), s>>>(f);
     }
     RevArgs a;
     a.g = snap_graph(g, W, 1, ws);
@@ -2608,7 +2618,7 @@ static int enqueue_prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_
     if (ws->aff_gain && ws->batch.count == 1) fill<uint32_t>(ws->a_ctrs, (uint64_t)(k + 1) * PH_CTRS, 0u, s);
     fill<uint32_t>(ws->gain, n, 0u, s);
     fill<uint8_t>(ws->sel, n, (uint8_t)0, s);
-    fill<uint64_t>(ws->covered, (uint64_t)n * W, 0ull, s);
+    fill<uint64_t>(ws->covered, ws->sparse ? cov_len(n, W) : (uint64_t)n * W, 0ull, s);
     if (ws->rv_on) fill<uint32_t>(ws->rv_stamp, (uint64_t)n * W, 0u, s);
     const bool rev = need == PREP_REVERSE || ws->live_edge == 1;
     if (ws->lt_on) {
@@ -3623,7 +3633,7 @@ static void eval_snap(const im_graph *g, uint32_t R, uint32_t B, im_workspace *w
     a.g = snap_graph(g, (R + 63) / 64, 0, ws);
     a.R = R;
     a.cand = ws->c_cand; a.ncand = ws->c_ctl + CC_NCAND;
-    a.covered = ws->covered; a.ev = ws->c_ev;
+    a.cov = (const uint32_t *)ws->covered; a.cwords = cov_words(n); a.ev = ws->c_ev;
     a.kept_src = ws->lz_src; a.kept_len = ws->lz_len; a.kept_q = ws->lz_q;
     a.bits = n > EVS_LDS_NODES ? ws->lz_bits : nullptr;
     a.stats = ws->stats;
@@ -3694,7 +3704,7 @@ static int select_lazy(const im_graph *g, uint32_t R, uint32_t k, uint32_t B, co
             FwdSnapArgs f = fwd_snap_args(g, R, t, seeds_out, gains_out, ws);
             f.kept_n = kept; f.kept_src = ws->lz_src; f.kept_len = ws->lz_len; f.kept_q = ws->lz_q;
             PhaseTimer pt(ws, IM_PH_FORWARD, s);
-            k_fwd_snap<<<R, FWS_NT, 0, s>>>(f);
+            k_fwd_snap<<<R, FWS_NT, fws_lds(f), s>>>(f);
         };
         fill<uint32_t>(ws->rv_stamp, (uint64_t)n * W, 0u, s);
         commit(0, 0);

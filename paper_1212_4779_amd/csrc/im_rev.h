@@ -391,8 +391,9 @@ __global__ __launch_bounds__(NT) void k_rev_search(RevArgs a)
 // as the reverse step's sources, 64 to a task.
 // A word of 64 snapshots searched together needs many workgroups, and a grid
 // barrier per level, to be as wide; the snapshots' searches are independent,
-// so a level here costs its four dependent accesses (queue, list offsets,
-// listed heads, covered) and three workgroup barriers. Figures: rev_search.
+// so a level here costs list offsets, listed heads and an LDS bit per head (the
+// snapshot's covered bits are taken into LDS, up to FWS_LDS_NODES nodes) and
+// three workgroup barriers. Figures: rev_search.
 // ---------------------------------------------------------------------------
 struct FwdSnapArgs {
     SnapGraph g;                     // forward arcs
@@ -402,7 +403,12 @@ struct FwdSnapArgs {
     uint32_t *seeds_out;
     uint64_t *gains_out;
     uint8_t *sel;
-    uint64_t *covered;               // [W][n]
+    // covered nodes of each snapshot, [R][cwords] (one bit per node of the
+    // graph, or of the batch); nlds: nodes of the largest instance if its bits
+    // are taken into LDS for the search, else 0
+    uint32_t *cov;
+    uint64_t cwords;
+    uint32_t nlds;
     uint32_t *src;                   // a snapshot's queue: up to n (its instance's) nodes
     uint2 *tasks;                    // nullptr: no reverse step follows
     uint32_t *ntasks;                // zero before the launch
@@ -415,10 +421,12 @@ struct FwdSnapArgs {
     unsigned long long *stats;
 };
 
+constexpr uint32_t FWS_LDS_NODES = 1u << 18;
 constexpr int FWS_NT = 512, FWS_Q = 4096;   // queue entries kept in LDS as well
 
 __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
 {
+    extern __shared__ uint32_t fws_bits[];
     __shared__ RevBig<FWS_NT> B;
     __shared__ uint32_t q[FWS_Q], cnt, s_t0, s_kept;
     __shared__ unsigned long long red[FWS_NT / 64];
@@ -428,9 +436,9 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
     const uint32_t R = single ? a.R : a.b.R[inst];
     if (key == 0 || r >= R) return;   // the instance has its k seeds
     const uint32_t v = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
-    uint32_t ni = a.g.n;
+    uint32_t ni = a.g.n, n0 = 0;
     uint64_t base = 0;
-    if (!single) { ni = a.b.node_off[inst + 1] - a.b.node_off[inst]; base = a.b.pair_off[inst]; }
+    if (!single) { n0 = a.b.node_off[inst]; ni = a.b.node_off[inst + 1] - n0; base = a.b.pair_off[inst]; }
     base += (uint64_t)r * ni;
     if (r == 0 && tid == 0) {
         const uint32_t out = (single ? 0u : a.b.kpre[inst]) + a.t;
@@ -439,8 +447,8 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
         a.sel[v] = 1;
     }
     const uint32_t w = r / 64, b = r % 64;
-    const unsigned long long bit = 1ull << b;
-    unsigned long long *cov = (unsigned long long *)a.covered + (uint64_t)w * a.g.n;
+    uint32_t *cov = a.cov + (uint64_t)r * a.cwords, *seen = cov;
+    uint32_t w0 = 0;   // first word of `seen`
     uint32_t *src = a.src + base;
     if (tid == 0) { s_kept = IM_EMPTY; cnt = 0; B.n = 0; }
     __syncthreads();
@@ -455,9 +463,22 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
         const uint64_t at = (uint64_t)s_kept * R + r;
         list = a.kept_q + at * ni;
         N = a.kept_len[at];
-        for (uint32_t i = tid; i < N; i += FWS_NT) atomicOr(&cov[list[i]], bit);
     } else {
-        if (tid == 0 && !(atomicOr(&cov[v], bit) & bit)) { q[0] = v; src[0] = v; cnt = 1; }
+        if (a.nlds) {
+            w0 = n0 / 32;
+            const uint32_t words = (n0 + ni + 31) / 32 - w0;
+            for (uint32_t i = tid; i < words; i += FWS_NT) fws_bits[i] = cov[w0 + i];
+            seen = fws_bits;
+            __syncthreads();
+        }
+        auto visit = [&](uint32_t y) {
+            const uint32_t bit = 1u << (y & 31u);
+            if (atomicOr(&seen[(y >> 5) - w0], bit) & bit) return;
+            const uint32_t p = atomicAdd(&cnt, 1u);
+            if (p < (uint32_t)FWS_Q) q[p] = y;
+            src[p] = y;
+        };
+        if (tid == 0) visit(v);
         __syncthreads();
         uint64_t arcs = 0;
         for (uint32_t head = 0;;) {
@@ -469,14 +490,7 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
                 const bool take = i < end;
                 RevSpan sp = {0, 0, 0};
                 if (take) sp = rev_span(a.g, w, b, i < (uint32_t)FWS_Q ? q[i] : src[i]);
-                rev_expand<FWS_NT>(B, a.g, w, b, take, 0u, sp,
-                                   [&](uint32_t, uint32_t y) {
-                                       if (atomicOr(&cov[y], bit) & bit) return;
-                                       const uint32_t p = atomicAdd(&cnt, 1u);
-                                       if (p < (uint32_t)FWS_Q) q[p] = y;
-                                       src[p] = y;
-                                   },
-                                   arcs);
+                rev_expand<FWS_NT>(B, a.g, w, b, take, 0u, sp, [&](uint32_t, uint32_t y) { visit(y); }, arcs);
             }
             head = end;
         }
@@ -487,6 +501,7 @@ __global__ __launch_bounds__(FWS_NT) void k_fwd_snap(FwdSnapArgs a)
         const uint32_t x = !kept && i < (uint32_t)FWS_Q ? q[i] : list[i];
         const uint32_t od = a.g.row[x + 1] - a.g.row[x];
         trav += od;
+        if (seen != cov || kept) atomicOr(&cov[x >> 5], 1u << (x & 31u));
         if (atomicExch(&a.stamp[(uint64_t)w * a.g.n + x], a.t + 1) != a.t + 1) { relax += od; pairs++; }
     }
     const uint32_t nt = a.tasks ? (N + 63) / 64 : 0u;
@@ -519,7 +534,8 @@ struct EvalSnapArgs {
     SnapGraph g;
     uint32_t R;
     const uint32_t *cand, *ncand;    // [>= ncand], device count
-    const uint64_t *covered;         // [W][n]
+    const uint32_t *cov;             // as in FwdSnapArgs
+    uint64_t cwords;
     uint32_t *ev;                    // [n], += per candidate (zero before)
     uint32_t *kept_src, *kept_len, *kept_q;   // as in FwdSnapArgs
     uint32_t *bits;                  // [grid][ceil(n / 32)], zero at rest; nullptr: LDS
@@ -538,21 +554,21 @@ __global__ __launch_bounds__(EVS_NT) void k_eval_snap(EvalSnapArgs a)
         return;
     }
     const uint32_t v = a.cand[j], w = r / 64, b = r % 64, words = (n + 31) / 32;
-    const uint64_t bit = 1ull << b;
-    const uint64_t *cov = a.covered + (uint64_t)w * n;
+    const uint32_t *cov = a.cov + (uint64_t)r * a.cwords;
+    auto covered = [&](uint32_t y) { return (cov[y >> 5] >> (y & 31u)) & 1u; };
     uint32_t *list = a.kept_q + (uint64_t)blockIdx.x * n;
     uint32_t *bits = a.bits ? a.bits + (uint64_t)blockIdx.x * words : evs_bits;
     if (r == 0 && tid == 0) a.kept_src[j] = v;
-    if (cov[v] & bit) {   // uniform: covered in this snapshot
+    if (covered(v)) {   // uniform over the workgroup
         if (tid == 0) a.kept_len[blockIdx.x] = 0;
         return;
     }
     if (!a.bits)
-        for (uint32_t i = tid; i < words; i += EVS_NT) bits[i] = 0;
+        for (uint32_t i = tid; i < words; i += EVS_NT) bits[i] = cov[i];   // covered counts as seen
     if (tid == 0) { cnt = 0; B.n = 0; }
     __syncthreads();
     auto visit = [&](uint32_t y) {
-        if (cov[y] & bit) return;
+        if (a.bits && covered(y)) return;
         const uint32_t m = 1u << (y & 31u);
         if (atomicOr(&bits[y >> 5], m) & m) return;
         const uint32_t p = atomicAdd(&cnt, 1u);
