@@ -60,18 +60,7 @@ __device__ __forceinline__ void wave_expand(WaveBig &B, const SnapGraph &a, uint
     const uint32_t lane = threadIdx.x & 63u;
     const bool big = sp.len > (uint32_t)REV_SMALL;
     const uint64_t bal = __ballot(big);
-    if (!big) {
-        uint32_t v[REV_SMALL];
-        bool live[REV_SMALL];
-#pragma unroll
-        for (int u = 0; u < REV_SMALL; u++) {
-            v[u] = 0;
-            live[u] = (uint32_t)u < sp.len && rev_head(a, w, b, sp.kind, sp.start + (uint32_t)u, v[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < REV_SMALL; u++)
-            if (live[u]) visit(v[u]);
-    }
+    rev_small(a, w, b, big ? 0u : sp.len, sp, visit);
     arcs += sp.len;
     if (!bal) return;
     const uint32_t nb = (uint32_t)__popcll(bal);
@@ -111,7 +100,8 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     __shared__ WaveBig B[CB_WAVES];
     __shared__ uint32_t q[CB_WAVES][CB_Q], cnt[CB_WAVES], s_task, s_sum, s_union, s_next, s_over;
     __shared__ unsigned long long red[CB_WAVES];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6, nw = blockDim.x >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, nw = blockDim.x >> 6;
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t words = (a.nmax + 31) / 32;
     const uint32_t per = TABLE ? (uint32_t)CB_CS : words;          // words per wavefront
     uint32_t *mine = maps + (uint64_t)wv * per;
@@ -126,7 +116,8 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     uint32_t ran = 0;
     __syncthreads();
     for (uint32_t t = blockIdx.x; t < nt;) {
-        const uint32_t task = a.in_q[t], w = task / a.g.n, src = task - w * a.g.n;
+        const uint32_t task = __builtin_amdgcn_readfirstlane(a.in_q[t]);
+        const uint32_t w = task / a.g.n, src = task - w * a.g.n;
         const uint32_t inst = a.node_inst ? a.node_inst[src] : 0u;
         const uint32_t base = a.node_inst ? a.inst_off[inst] : 0u;
         const uint64_t valid = im_valid_bits(a.node_inst ? a.inst_R[inst] : a.R, w);
@@ -202,7 +193,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                 if (over) break;
             }
             if (lane == 0) b = atomicAdd(&s_next, 1u);
-            b = __shfl(b, 0, 64);
+            b = __builtin_amdgcn_readfirstlane(b);   // (scalar: list and mask bases are, too)
         }
         __syncthreads();
         over = over || s_over != 0;

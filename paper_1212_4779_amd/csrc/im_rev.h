@@ -101,6 +101,35 @@ __device__ __forceinline__ bool rev_head(const SnapGraph &a, uint32_t w, uint32_
 }
 
 constexpr int REV_SMALL = 4;   // spans up to this length are expanded by one lane
+
+// Heads 0 .. len - 1 (at most REV_SMALL) of the lane's span, loaded together.
+// A level of a thin search is mostly instructions: steps that no lane of the
+// wavefront needs are skipped, and listed heads (kind 0) take a path of their
+// own, without the choice of array and mask.
+template <typename Visit>
+__device__ __forceinline__ void rev_small(const SnapGraph &a, uint32_t w, uint32_t b, uint32_t len,
+                                          const RevSpan &sp, Visit visit)
+{
+    uint32_t v[REV_SMALL];
+    bool live[REV_SMALL];
+    if (!__any(len != 0 && sp.kind != 0)) {
+#pragma unroll
+        for (int u = 0; u < REV_SMALL; u++) {
+            v[u] = 0;
+            live[u] = (uint32_t)u < len;
+            if (live[u]) v[u] = a.sp.adj[sp.start + (uint32_t)u];
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < REV_SMALL; u++) {
+            v[u] = 0;
+            live[u] = (uint32_t)u < len && rev_head(a, w, b, sp.kind, sp.start + (uint32_t)u, v[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < REV_SMALL; u++)
+        if (live[u]) visit(v[u]);
+}
 constexpr int REV_U = 4;       // heads in flight per lane in the longer ones
 
 template <int NT>
@@ -121,19 +150,8 @@ __device__ __forceinline__ void rev_expand(RevBig<NT> &B, const SnapGraph &a, ui
 {
     const int tid = threadIdx.x;
     const bool small = take && sp.len <= (uint32_t)REV_SMALL, big = take && !small;
-    if (small) {
-        uint32_t v[REV_SMALL];
-        bool live[REV_SMALL];
-#pragma unroll
-        for (int u = 0; u < REV_SMALL; u++) {
-            v[u] = 0;
-            live[u] = (uint32_t)u < sp.len && rev_head(a, w, b, sp.kind, sp.start + (uint32_t)u, v[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < REV_SMALL; u++)
-            if (live[u]) relax(own, v[u]);
-        arcs += sp.len;
-    }
+    rev_small(a, w, b, small ? sp.len : 0u, sp, [&](uint32_t v) { relax(own, v); });
+    if (small) arcs += sp.len;
     const uint32_t q = wave_append(big, &B.n);
     if (big) { B.start[q] = sp.start; B.ex[q] = sp.len; B.own[q] = own | (sp.kind << 30); }
     __syncthreads();
@@ -365,7 +383,10 @@ __global__ __launch_bounds__(NT) void k_rev_search(RevArgs a)
     // the first task is the workgroup's own, further ones come from a counter
     for (uint32_t t = blockIdx.x; t < nt;) {
         const uint32_t id = a.in_q ? a.in_q[t] : t;
-        const uint2 tk = a.tasks[id];
+        uint2 tk = a.tasks[id];
+        // the same in every lane: snapshot, list and mask bases stay scalar
+        tk.x = __builtin_amdgcn_readfirstlane(tk.x);
+        tk.y = __builtin_amdgcn_readfirstlane(tk.y);
         if (!rev_run_lds<NT, CS, LIM>(L, a, tk, c)) {
             if (DENSE) {
                 rev_run_dense<NT>(L.B, ctr, a, tk, blockIdx.x, c);
