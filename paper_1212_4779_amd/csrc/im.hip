@@ -1399,7 +1399,7 @@ struct im_workspace {
     // largest initial-count tasks by snapshot (im_bits.h)
     uint64_t cap_cb = 0, cap_cb_any = 0;
     uint32_t *cb_queue = nullptr, *cb_any = nullptr;
-    unsigned cb_waves = 0, cb_groups = 0;
+    unsigned cb_waves = 0, cb_tasks = 0, cb_groups = 0;
     bool cb_table = false;
     // linear-threshold snapshots
     int live_edge = 0;                   // 0: independent cascade, 1: linear threshold
@@ -1627,14 +1627,21 @@ static uint32_t slots_for(uint32_t n, uint32_t max_slots)
 }
 
 // Buffers of the initial counts by snapshot (im_bits.h) on instances of up to
-// nmax nodes: bitmaps with as many wavefronts per workgroup as have room for
-// theirs, at least four (up to 235,000 nodes), else tables (cb_groups = 0: the
-// dense tier alone)
-constexpr unsigned CB_LDS = 144u << 10;       // beside the kernel's own 10 KB
+// nmax nodes: bitmaps up to 250,000 nodes, where four wavefronts still have room
+// for theirs, else tables (cb_groups = 0: the dense tier alone). Up to six
+// tasks in progress (60,000 nodes: 25.5 ms with two, 21.4 with four, 19.3 with
+// six, although six leave room for two wavefronts less), at most a third of the
+// bitmaps. As many workgroups per CU as leave each at least eight wavefronts, so
+// that few wavefronts share a task (instances of up to 20,000 nodes: 7.4 ms with
+// three of eight, 10.8 with one of sixteen).
+constexpr unsigned CB_LDS = 159u << 10;       // beside the kernel's own 640 bytes
+constexpr unsigned CB_RESIDENT = 28;          // wavefronts per CU, seven per SIMD (registers)
 
 static unsigned cb_lds(const im_workspace *ws, uint32_t nmax)
 {
-    return ws->cb_table ? ws->cb_waves * (unsigned)CB_CS * 4u : (ws->cb_waves + 1) * ((nmax + 31) / 32) * 4u;
+    const unsigned map = (nmax + 31) / 32 * 4;
+    return ws->cb_waves * ((ws->cb_table ? (unsigned)CB_CS * 4u : map) + (unsigned)sizeof(WaveLds)) +
+           (ws->cb_table ? 0u : ws->cb_tasks * map);
 }
 
 template <bool TABLE>
@@ -1657,12 +1664,24 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
     ws->cb_groups = 0;
     if (!ws->sparse || t_arena || !nmax) return;
     const uint64_t words = (nmax + 31) / 32;
-    ws->cb_waves = 9 * words * 4 <= CB_LDS ? 8 : 4;
-    ws->cb_table = 5 * words * 4 > CB_LDS;
-    if (ws->cb_table) ws->cb_waves = CB_WAVES;
+    const unsigned map = (unsigned)std::min<uint64_t>(words * 4, CB_LDS), own = sizeof(WaveLds);
+    ws->cb_table = 4 * (map + own) + map > CB_LDS;
+    ws->cb_tasks = 4;
+    if (ws->cb_table) {
+        ws->cb_waves = CB_LDS / (CB_CS * 4 + own);
+    } else {
+        for (unsigned k = CB_RESIDENT / 8; k >= 1; k--) {
+            const unsigned share = CB_LDS / k, all = share / (map + own);
+            ws->cb_tasks = std::min(std::max(all / 3, 1u), 6u);
+            ws->cb_waves = std::min((share - ws->cb_tasks * map) / (map + own),
+                                    std::min(CB_RESIDENT / (4 * k) * 4, (unsigned)CB_WAVES));
+            if (ws->cb_waves >= 8) break;
+        }
+    }
     const unsigned b = ws->cb_table ? cb_per_cu<true>(ws, nmax) : cb_per_cu<false>(ws, nmax);
     const uint64_t per = (uint64_t)ws->cb_waves * (ws->cb_table ? (uint64_t)CB_CS : nmax);
-    const uint64_t fit = CB_BUDGET / 4 / (per + (ws->cb_table ? words : 0));
+    const uint64_t marks = ws->cb_table ? ws->cb_tasks * words : 0;
+    const uint64_t fit = CB_BUDGET / 4 / (per + marks);
     const uint64_t groups = std::min<uint64_t>((uint64_t)b * ws->num_cu, fit);
     if (groups == 0) return;
     if (groups * per > ws->cap_cb) {
@@ -1670,10 +1689,10 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
         if (dalloc(&ws->cb_queue, groups * per)) return;
         ws->cap_cb = groups * per;
     }
-    if (ws->cb_table && groups * words > ws->cap_cb_any) {
+    if (ws->cb_table && groups * marks > ws->cap_cb_any) {
         ws->cap_cb_any = 0;
-        if (dalloc(&ws->cb_any, groups * words) || ws_memset(ws->cb_any, groups * words * 4)) return;
-        ws->cap_cb_any = groups * words;
+        if (dalloc(&ws->cb_any, groups * marks) || ws_memset(ws->cb_any, groups * marks * 4)) return;
+        ws->cap_cb_any = groups * marks;
     }
     ws->cb_groups = (unsigned)groups;
 }
@@ -2083,11 +2102,11 @@ static unsigned per_cu(K kernel, int nt)
 }
 
 // Last-tier initial counts by snapshot (im_bits.h). False: the dense tier takes
-// every task. Against the dense tier: weighted cascade, 60,000 nodes, R = 128:
-// 63 -> 31 ms (7 * 10^9 visited nodes/s; the lists' lines from beyond the L2 are
-// what bounds it, 1,024 dense slots instead of 256 took 45 ms); 16 uneven
-// instances 32 -> 12 ms; 15,000 nodes 1.8 -> 0.9 ms; 10^6 nodes, p = 0.01 (tables)
-// 6.0 -> 3.6 ms.
+// every task. Dense tier -> one task per workgroup at a time -> now, ms:
+//   weighted cascade, 60,000 nodes, R = 128   63 -> 27 -> 19.3
+//   16 uneven instances                       32 -> 10.2 -> 7.4
+//   weighted cascade, 15,000 nodes, R = 100   1.8 -> 0.81 -> 0.71
+//   10^6 nodes, p = 0.01, R = 256 (tables)    6.0 -> 3.5 -> 3.4
 static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, hipStream_t s)
 {
     if (!ws->cb_groups || !t.sp.off || t.cand) return false;
@@ -2099,7 +2118,7 @@ static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, 
     a.gain = t.gain;
     a.in_q = t.in_q; a.in_n = t.in_n;
     a.out_q = ws->ovf_q; a.out_n = ctr + 5; a.grab = ctr + 4;   // (ovf_q: tier 1 is done with it)
-    a.queue = ws->cb_queue; a.any = ws->cb_any; a.nmax = ws->slots_n;
+    a.queue = ws->cb_queue; a.any = ws->cb_any; a.nmax = ws->slots_n; a.tasks = ws->cb_tasks;
     a.stats = t.stats;
     PhaseTimer pt(ws, ph, s);
     const unsigned lds = cb_lds(ws, ws->slots_n);

@@ -8,22 +8,28 @@
 // memory that no cache holds. Here each wavefront searches one snapshot over
 // its live lists with the visited nodes as a bitmap in LDS (n / 8 bytes; on
 // graphs too large for that as a table of CB_CS nodes, with which a hub's
-// snapshots fit and a task that outgrows it goes to the dense tier), and the
-// workgroup's wavefronts mark what any of them reached in a shared bitmap (LDS
-// or memory), which gives the task's (node, word) counts. Per level: list offsets, listed
-// heads, two LDS atomics. Bound: those two dependent loads, times the levels
-// of 64 / (wavefronts per workgroup) searches.
+// snapshots fit and a task that outgrows it goes to the dense tier), and marks
+// what any snapshot of the task reached in a bitmap of the task (LDS or
+// memory), which gives its (node, word) counts.
+// Bound: the two dependent loads of a level (list offsets, listed heads), times
+// the levels, over the searches that the bitmaps leave room for (13 per CU at
+// 60,000 nodes): the wavefronts wait nine tenths of their time, and taking the
+// L2 misses out (lists of eight snapshots per XCD) did not change it while a
+// workgroup still ended its tasks one by one. All 64 frontiers of a task in one
+// LDS table, level by level, were slower too (27 -> 28 to 46 ms).
 // Where the snapshots do share their nodes (supercritical graphs), one search
-// of the word does less: after the first search of every wavefront the task is
-// handed to the dense tier if they reached more than twice the nodes of their
-// union (the source aside).
-// Measured (tier 2 of the initial counts): see run_tiers.
+// of the word does less: the task is handed to the dense tier if its first
+// CB_PROBE searches reached more than twice the nodes that the task had marked
+// by then (the sources aside).
+// Measured (tier 2 of the initial counts): see cnt_bits.
 #pragma once
 
 #include "im_rev.h"
 
-constexpr int CB_WAVES = 8;      // most wavefronts (bits at a time) per workgroup
-constexpr int CB_Q = 128;        // queue entries per wavefront kept in LDS as well
+constexpr int CB_WAVES = 16;     // most wavefronts (bits at a time) per workgroup
+constexpr int CB_Q = 64;         // queue entries per wavefront kept in LDS as well
+constexpr int CB_TASKS = 8;      // most tasks in progress per workgroup
+constexpr uint32_t CB_PROBE = 8; // searches after which a task's snapshots are compared
 constexpr int CB_CS = 4096, CB_LIM = 3072;   // table entries per wavefront, most nodes in it
 
 struct BitsArgs {
@@ -35,8 +41,9 @@ struct BitsArgs {
     uint32_t *out_q, *out_n;     // tasks for the dense tier
     uint32_t *grab;
     uint32_t *queue;             // [workgroups][wavefronts][nmax] (bitmaps) or [..][CB_CS] (tables)
-    uint32_t *any;               // tables: [workgroups][words of the largest instance], zero at rest
+    uint32_t *any;               // tables: [workgroups][tasks][words of the largest instance], zero at rest
     uint32_t nmax;               // nodes of the largest instance
+    uint32_t tasks;              // in progress per workgroup (1 .. CB_TASKS)
     unsigned long long *stats;
 };
 
@@ -48,6 +55,22 @@ __device__ __forceinline__ void wave_order()
     __builtin_amdgcn_wave_barrier();
 }
 
+// sum over the wavefront (all lanes active), in registers: a search of a few
+// nodes is shorter than the shuffles of wave_sum_u64
+__device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t x)
+{
+    auto from = [&](auto ctrl, auto rows) {
+        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl.value, rows.value, 0xF, false);
+    };
+    from(std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xF>());   // row_shr:1
+    from(std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xF>());
+    from(std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xF>());
+    from(std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xF>());
+    from(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xA>());   // row_bcast:15
+    from(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xC>());   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 struct WaveBig {
     uint32_t ex[64], start[64], kind[64];
 };
@@ -55,7 +78,7 @@ struct WaveBig {
 // rev_expand for one wavefront: visit(v) for every live head of the lanes' spans
 template <typename Visit>
 __device__ __forceinline__ void wave_expand(WaveBig &B, const SnapGraph &a, uint32_t w, uint32_t b,
-                                            const RevSpan &sp, Visit visit, uint64_t &arcs)
+                                            const RevSpan &sp, Visit visit, uint32_t &arcs)
 {
     const uint32_t lane = threadIdx.x & 63u;
     const bool big = sp.len > (uint32_t)REV_SMALL;
@@ -91,129 +114,171 @@ __device__ __forceinline__ void wave_expand(WaveBig &B, const SnapGraph &a, uint
     wave_order();
 }
 
+struct WaveLds {
+    WaveBig B;
+    uint32_t q[CB_Q];
+};
+
+// A task in progress. Its number among the workgroup's tasks is `ord`: free is
+// the number that may take the place next, open that of the task in it plus one.
+struct CntTask {
+    uint32_t free, open, task, done, over, sum, reached;
+    unsigned long long relax, trav, arcs;
+};
+
+// The wavefronts take (task, bit) pairs in order, without a barrier: the sizes
+// of a task's searches differ by two orders of magnitude, and a workgroup that
+// ended each task together waited for its largest. The wavefront that finishes a
+// task's last search adds up the task and opens its place. A wavefront waits
+// only for an older task (a place that is still taken) or for the one that is
+// reading the task in, never for a younger one, and takes one pair at a time.
 template <bool TABLE>
 __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
 {
-    // bitmaps: [wavefronts + 1][words of the largest instance]; tables:
-    // [wavefronts][CB_CS] nodes
+    // bitmaps: [wavefronts + tasks][words of the largest instance]; tables:
+    // [wavefronts][CB_CS] nodes; then [wavefronts] of WaveLds
     extern __shared__ uint32_t maps[];
-    __shared__ WaveBig B[CB_WAVES];
-    __shared__ uint32_t q[CB_WAVES][CB_Q], cnt[CB_WAVES], s_task, s_sum, s_union, s_next, s_over;
+    __shared__ uint32_t cnt[CB_WAVES], s_item;
+    __shared__ CntTask T[CB_TASKS];
     __shared__ unsigned long long red[CB_WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, nw = blockDim.x >> 6;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t words = (a.nmax + 31) / 32;
     const uint32_t per = TABLE ? (uint32_t)CB_CS : words;          // words per wavefront
     uint32_t *mine = maps + (uint64_t)wv * per;
-    uint32_t *any = TABLE ? a.any + (uint64_t)blockIdx.x * words : maps + (uint64_t)nw * words;
+    uint32_t *any0 = TABLE ? a.any + (uint64_t)blockIdx.x * a.tasks * words : maps + (uint64_t)nw * words;
     uint32_t *queue = a.queue + ((uint64_t)blockIdx.x * nw + wv) * (TABLE ? (uint32_t)CB_CS : a.nmax);
     const uint32_t nt = *a.in_n;
     if (blockIdx.x >= nt) return;
-    for (uint32_t i = tid; i < (TABLE ? nw * per : (nw + 1) * words); i += blockDim.x)
+    const uint32_t nmaps = TABLE ? nw * per : (nw + a.tasks) * words;
+    WaveLds &L = ((WaveLds *)(maps + nmaps))[wv];
+    for (uint32_t i = tid; i < nmaps; i += blockDim.x)
         maps[i] = TABLE ? IM_EMPTY : 0u;
-    if (tid == 0) { s_sum = 0; s_union = 0; s_next = nw; s_over = 0; }
-    uint64_t t_relax = 0, t_reached = 0, t_trav = 0, t_arcs = 0;   // of the finished tasks
-    uint32_t ran = 0;
+    if (tid == 0) s_item = 0;
+    if (tid < CB_TASKS) {
+        CntTask &t = T[tid];
+        t.free = tid; t.open = 0; t.task = 0; t.done = 0; t.over = 0; t.sum = 0; t.reached = 0;
+        t.relax = 0; t.trav = 0; t.arcs = 0;
+    }
+    // lane 0: of the tasks that this wavefront finished
+    unsigned long long t_relax = 0, t_reached = 0, t_trav = 0, t_arcs = 0;
     __syncthreads();
-    for (uint32_t t = blockIdx.x; t < nt;) {
-        const uint32_t task = __builtin_amdgcn_readfirstlane(a.in_q[t]);
+    auto peek = [](uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    auto post = [](uint32_t *p, uint32_t v) {
+        __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    for (;;) {
+        uint32_t item = 0;
+        if (lane == 0) item = atomicAdd(&s_item, 1u);
+        item = __builtin_amdgcn_readfirstlane(item);   // (scalar: list and mask bases are, too)
+        const uint32_t ord = item >> 6, b = item & 63u, place = ord % a.tasks;
+        CntTask &tk = T[place];
+        uint32_t *any = any0 + (uint64_t)place * words;
+        if (b == 0) {
+            while (peek(&tk.free) != ord) __builtin_amdgcn_s_sleep(1);
+            if (lane == 0) {
+                const uint32_t i = ord == 0 ? blockIdx.x : gridDim.x + atomicAdd(a.grab, 1u);
+                tk.task = i < nt ? a.in_q[i] : IM_EMPTY;
+                post(&tk.open, ord + 1);
+            }
+        }
+        while (peek(&tk.open) != ord + 1) __builtin_amdgcn_s_sleep(1);
+        const uint32_t task = __builtin_amdgcn_readfirstlane(tk.task);
+        if (task == IM_EMPTY) break;   // (the others find it before its 64 bits are taken)
         const uint32_t w = task / a.g.n, src = task - w * a.g.n;
         const uint32_t inst = a.node_inst ? a.node_inst[src] : 0u;
         const uint32_t base = a.node_inst ? a.inst_off[inst] : 0u;
         const uint64_t valid = im_valid_bits(a.node_inst ? a.inst_R[inst] : a.R, w);
-        uint64_t relax = 0, reached = 0, trav = 0, arcs = 0;
-        uint32_t sum = 0;
-        // queue entries are nodes (bitmaps) or table positions
-        auto entry = [&](uint32_t i) { return i < (uint32_t)CB_Q ? q[wv][i] : queue[i]; };
-        auto push = [&](uint32_t x) {
-            const uint32_t p = atomicAdd(&cnt[wv], 1u);
-            if (p < (uint32_t)CB_Q) q[wv][p] = x;
-            else queue[p] = x;
-        };
-        auto visit = [&](uint32_t v) {
-            if constexpr (TABLE) {
-                uint32_t h = slot_hash(v) >> (32 - __builtin_ctz(CB_CS));
-                // (a full table is left as it is: the task is handed over)
-                if (*(volatile uint32_t *)&cnt[wv] >= (uint32_t)CB_LIM) { s_over = 1; return; }
-                for (;;) {
-                    const uint32_t key = atomicCAS(&mine[h], IM_EMPTY, v);
-                    if (key == v) return;
-                    if (key == IM_EMPTY) break;
-                    h = (h + 1) & (CB_CS - 1);
-                }
-                push(h);
-            } else {
-                const uint32_t i = v - base, bit = 1u << (i & 31u);
-                if (!(atomicOr(&mine[i >> 5], bit) & bit)) push(v);
-            }
-        };
-        bool over = false;
-        for (uint32_t b = wv; b < 64;) {
-            if ((valid >> b) & 1ull) {
-                if (lane == 0) {
-                    cnt[wv] = 0;
-                    visit(src);
-                }
-                wave_order();
-                uint32_t head = 0;
-                for (;;) {
-                    const uint32_t end = cnt[wv];
-                    if (head == end) break;
-                    for (; head < end; head += 64) {
-                        RevSpan sp = {0, 0, 0};
-                        if (head + lane < end) {
-                            const uint32_t e = entry(head + lane), x = TABLE ? mine[e] : e;
-                            sp = rev_span(a.g, w, b, x);
-                            const uint32_t dg = a.g.row[x + 1] - a.g.row[x];
-                            const uint32_t i = x - base, bit = 1u << (i & 31u);
-                            trav += dg;
-                            if (!(atomicOr(&any[i >> 5], bit) & bit)) { relax += dg; reached++; }
-                        }
-                        wave_expand(B[wv], a.g, w, b, sp, visit, arcs);
+        if (((valid >> b) & 1ull) && !peek(&tk.over)) {
+            // (of one search, each below 2^32: nodes, arcs, degrees of distinct nodes)
+            uint32_t relax = 0, trav = 0, arcs = 0, reached = 0;
+            // queue entries are nodes (bitmaps) or table positions
+            auto entry = [&](uint32_t i) { return i < (uint32_t)CB_Q ? L.q[i] : queue[i]; };
+            auto push = [&](uint32_t x) {
+                const uint32_t p = atomicAdd(&cnt[wv], 1u);
+                if (p < (uint32_t)CB_Q) L.q[p] = x;
+                else queue[p] = x;
+            };
+            auto visit = [&](uint32_t v) {
+                if constexpr (TABLE) {
+                    uint32_t h = slot_hash(v) >> (32 - __builtin_ctz(CB_CS));
+                    // (a full table is left as it is: the task is handed over)
+                    if (*(volatile uint32_t *)&cnt[wv] >= (uint32_t)CB_LIM) { tk.over = 1; return; }
+                    for (;;) {
+                        const uint32_t key = atomicCAS(&mine[h], IM_EMPTY, v);
+                        if (key == v) return;
+                        if (key == IM_EMPTY) break;
+                        h = (h + 1) & (CB_CS - 1);
                     }
-                    head = end;
-                    wave_order();
+                    push(h);
+                } else {
+                    const uint32_t i = v - base, bit = 1u << (i & 31u);
+                    if (!(atomicOr(&mine[i >> 5], bit) & bit)) push(v);
                 }
-                sum += head;
-                for (uint32_t i = lane; i < head; i += 64) {
-                    if (TABLE) mine[entry(i)] = IM_EMPTY;
-                    else mine[(entry(i) - base) >> 5] = 0;
+            };
+            if (lane == 0) {
+                cnt[wv] = 0;
+                visit(src);
+            }
+            wave_order();
+            uint32_t head = 0;
+            for (;;) {
+                const uint32_t end = cnt[wv];
+                if (head == end) break;
+                for (; head < end; head += 64) {
+                    RevSpan sp = {0, 0, 0};
+                    if (head + lane < end) {
+                        const uint32_t e = entry(head + lane), x = TABLE ? mine[e] : e;
+                        sp = rev_span(a.g, w, b, x);
+                        const uint32_t dg = a.g.row[x + 1] - a.g.row[x];
+                        const uint32_t i = x - base, bit = 1u << (i & 31u);
+                        trav += dg;
+                        if (!(atomicOr(&any[i >> 5], bit) & bit)) { relax += dg; reached++; }
+                    }
+                    wave_expand(L.B, a.g, w, b, sp, visit, arcs);
                 }
+                head = end;
                 wave_order();
             }
-            if (b == wv) {   // the first searches: do the snapshots share their nodes?
-                const uint64_t r = wave_sum_u64(reached);
-                if (lane == 0) {
-                    atomicAdd(&s_sum, sum - ((valid >> b) & 1ull ? 1u : 0u));
-                    atomicAdd(&s_union, (uint32_t)r);
-                }
-                __syncthreads();
-                over = s_sum > 2u * s_union + 64u;
-                __syncthreads();
-                if (over) break;
+            for (uint32_t i = lane; i < head; i += 64) {
+                if (TABLE) mine[entry(i)] = IM_EMPTY;
+                else mine[(entry(i) - base) >> 5] = 0;
             }
-            if (lane == 0) b = atomicAdd(&s_next, 1u);
-            b = __builtin_amdgcn_readfirstlane(b);   // (scalar: list and mask bases are, too)
+            wave_order();
+            relax = wave_sum_dpp(relax); trav = wave_sum_dpp(trav);
+            arcs = wave_sum_dpp(arcs); reached = wave_sum_dpp(reached);
+            if (lane == 0) {
+                atomicAdd(&tk.sum, head - 1);
+                atomicAdd(&tk.reached, reached);
+                atomicAdd(&tk.relax, (unsigned long long)relax);
+                atomicAdd(&tk.trav, (unsigned long long)trav);
+                atomicAdd(&tk.arcs, (unsigned long long)arcs);
+            }
         }
-        __syncthreads();
-        over = over || s_over != 0;
-        __syncthreads();
-        if (tid == 0) { s_sum = 0; s_union = 0; s_next = nw; s_over = 0; }
-        for (uint32_t i = tid; i < words; i += blockDim.x) any[i] = 0;
-        if (over) {
-            if (tid == 0) a.out_q[atomicAdd(a.out_n, 1u)] = task;
-        } else {
-            if (lane == 0) atomicAdd(&a.gain[src], sum);
-            t_relax += relax; t_reached += reached; t_trav += trav; t_arcs += arcs;
-            ran = 1;
+        uint32_t done = 0;
+        if (lane == 0)
+            done = __hip_atomic_fetch_add(&tk.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) + 1;
+        done = __builtin_amdgcn_readfirstlane(done);
+        // the first searches: do the snapshots share their nodes?
+        if (done == CB_PROBE && lane == 0 && tk.sum > 2u * tk.reached + 64u) post(&tk.over, 1u);
+        if (done < 64) continue;
+        for (uint32_t i = lane; i < words; i += 64) any[i] = 0;
+        if (lane == 0) {
+            if (tk.over) {
+                a.out_q[atomicAdd(a.out_n, 1u)] = task;
+            } else {
+                atomicAdd(&a.gain[src], tk.sum + (uint32_t)__popcll(valid));
+                t_relax += tk.relax; t_reached += tk.reached; t_trav += tk.trav; t_arcs += tk.arcs;
+            }
+            tk.done = 0; tk.over = 0; tk.sum = 0; tk.reached = 0;
+            tk.relax = 0; tk.trav = 0; tk.arcs = 0;
         }
-        if (tid == 0) s_task = gridDim.x + atomicAdd(a.grab, 1u);
-        __syncthreads();
-        t = s_task;
-        __syncthreads();
+        wave_order();
+        if (TABLE) __builtin_amdgcn_s_waitcnt(0);   // the marks are gone before the place is open
+        if (lane == 0) post(&tk.free, ord + a.tasks);
     }
-    auto total = [&](uint64_t v) -> unsigned long long {
-        v = wave_sum_u64(v);
+    __syncthreads();
+    auto total = [&](unsigned long long v) -> unsigned long long {
         if (lane == 0) red[wv] = v;
         __syncthreads();
         unsigned long long s = 0;
@@ -222,7 +287,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
         return s;
     };
     const unsigned long long r0 = total(t_relax), r1 = total(t_reached), r2 = total(t_trav), r3 = total(t_arcs);
-    if (tid == 0 && ran) {
+    if (tid == 0 && r1) {
         stat_add(a.stats, st_tier(PASS_INIT, 2, F_RELAX), r0);
         stat_add(a.stats, st_tier(PASS_INIT, 2, F_REACHED), r1);
         stat_add(a.stats, ST_TRAV_INIT, r2);
