@@ -15,9 +15,9 @@
 //                   interval and by cur[r][v*] on the ancestors of v*
 //                   (k_lt_round).
 // That is O(n) per snapshot and O(newly covered + depth) per round and
-// snapshot, where the general engines follow every ancestor chain: 200,000
-// nodes, 2*10^6 arcs, R = 256, k = 50: see the launch code (lt_prepare).
-// The kernels are bound by random accesses to per-snapshot arrays of n words.
+// snapshot, where the general engines follow every ancestor chain (measured:
+// see lt_forest). The kernels are bound by random accesses to per-snapshot
+// arrays of n words.
 #pragma once
 
 #include "im_bfs.h"
@@ -190,6 +190,25 @@ struct LtForest {
     unsigned long long *sc, *pos;
 };
 
+// A grid of lt_grid(nb, rows) workgroups walks the rows eight at a time, each on
+// one XCD (consecutive workgroups go to consecutive XCDs), so that a row's
+// scattered accesses meet in one L2 (k_lt_up 6.7 -> 5.7 ms, k_lt_parent 3.2 ->
+// 2.8, 200,000 nodes, R = 256). False: past the last row.
+constexpr uint32_t LT_XCDS = 8;
+
+__host__ __device__ __forceinline__ uint32_t lt_grid(uint32_t nb, uint32_t rows)
+{
+    return nb * ((rows + LT_XCDS - 1) / LT_XCDS * LT_XCDS);
+}
+
+__device__ __forceinline__ bool lt_place(uint32_t nb, uint32_t rows, uint32_t &block, uint32_t &row)
+{
+    const uint32_t i = blockIdx.x / LT_XCDS;
+    block = i % nb;
+    row = i / nb * LT_XCDS + blockIdx.x % LT_XCDS;
+    return row < rows;
+}
+
 // Each thread draws its node's kept in-arc in LTP_R snapshots: the largest j
 // with start[j] <= draw (an arc of length zero shares its start with the next
 // one, which comes later), if the draw lies in that arc's interval.
@@ -200,7 +219,9 @@ __global__ __launch_bounds__(256) void k_lt_parent(const uint32_t *row, const ui
                                                    const float *prob, const uint64_t *start,
                                                    uint64_t seed, LtForest f)
 {
-    const uint32_t v = blockIdx.x * 256u + threadIdx.x, r0 = blockIdx.y * LTP_R;
+    uint32_t block, rows;
+    if (!lt_place((f.n + 255) / 256, (f.R + LTP_R - 1) / LTP_R, block, rows)) return;
+    const uint32_t v = block * 256u + threadIdx.x, r0 = rows * LTP_R;
     if (v >= f.n) return;
     const uint32_t a = in_row[v], b = in_row[v + 1], dg = row[v + 1] - row[v];
     const uint64_t key = sm64_finalise(seed + ((uint64_t)v + 1ull) * IM_GOLDEN);
@@ -229,9 +250,11 @@ __global__ __launch_bounds__(256) void k_lt_parent(const uint32_t *row, const ui
 // was the last child.
 __global__ __launch_bounds__(256) void k_lt_up(LtForest f)
 {
-    const uint32_t u = blockIdx.x * 256u + threadIdx.x;
+    uint32_t block, r;
+    if (!lt_place((f.n + 255) / 256, f.R, block, r)) return;
+    const uint32_t u = block * 256u + threadIdx.x;
     if (u >= f.n) return;
-    const uint64_t off = (uint64_t)blockIdx.y * f.n;
+    const uint64_t off = (uint64_t)r * f.n;
     if (f.sc[off + u] != 1ull) return;
     uint32_t v = u, size = 1, degs = f.cur[off + v];
     for (;;) {
@@ -352,13 +375,16 @@ __global__ __launch_bounds__(LTO_NT) void k_lt_order(LtForest f)
 // gain[v] = sum over r of the sizes (before k_lt_order takes over cur)
 constexpr int LTG_R = 16;   // snapshots per workgroup
 
-__global__ __launch_bounds__(256) void k_lt_gain(LtForest f, uint32_t *gain, unsigned long long *stats)
+// ... and both degrees of a node in one word pair, for the rounds
+__global__ __launch_bounds__(256) void k_lt_gain(LtForest f, const uint32_t *row, const uint32_t *in_row,
+                                                 uint32_t *gain, uint2 *deg, unsigned long long *stats)
 {
     __shared__ unsigned long long red[4];
     const uint32_t v = blockIdx.x * 256u + threadIdx.x, r0 = blockIdx.y * LTG_R;
     uint64_t trav = 0;
     uint32_t g = 0;
     if (v < f.n) {
+        if (r0 == 0) deg[v] = make_uint2(row[v + 1] - row[v], in_row[v + 1] - in_row[v]);
 #pragma unroll 4
         for (uint32_t r = r0; r < min(r0 + (uint32_t)LTG_R, f.R); r++) {
             const uint64_t at = (uint64_t)r * f.n + v;
@@ -375,18 +401,22 @@ __global__ __launch_bounds__(256) void k_lt_gain(LtForest f, uint32_t *gain, uns
 
 // One round in one snapshot per workgroup: commit the argmax, bring cur and
 // the gains up to date. stamp[W][n]: the last round (plus one) that newly
-// covered the node in the word, for the (node, word) counters.
+// covered the node in the word, for the (node, word) counters. Bound: early
+// rounds by the scattered accesses of each newly covered node (its degrees in
+// one load instead of four, and four nodes' loads and exchanges in flight: 7.4 ->
+// 6.4 ms for 50 rounds on 200,000 nodes), late ones by the chain of parents
+// (followed beside the interval, not before it: 1.07 -> 0.79 ms for 50 rounds on
+// 15,000 nodes).
 constexpr int LTR_NT = 1024, LTR_U = 4;
 
-__global__ __launch_bounds__(LTR_NT) void k_lt_round(LtForest f, const uint32_t *row,
-                                                     const uint32_t *in_row,
+__global__ __launch_bounds__(LTR_NT) void k_lt_round(LtForest f, const uint2 *deg,
                                                      const unsigned long long *key, uint32_t t,
                                                      uint32_t *seeds_out, uint64_t *gains_out,
                                                      uint8_t *sel, uint32_t *gain, uint32_t *stamp,
                                                      unsigned long long *stats)
 {
     __shared__ unsigned long long red[LTR_NT / 64];
-    __shared__ uint32_t s_first, s_len;
+    __shared__ uint32_t s_first;
     const int tid = threadIdx.x;
     const unsigned long long k = *key;
     if (k == 0) return;
@@ -401,55 +431,79 @@ __global__ __launch_bounds__(LTR_NT) void k_lt_round(LtForest f, const uint32_t 
     const uint32_t c = f.cur[off + at];
     if (c == 0) return;   // covered in this snapshot
     uint64_t trav_fwd = 0, relax_fwd = 0, tasks = 0, trav_rev = 0, dec = 0;
-    if (tid == 0) {
-        const unsigned long long s = f.sc[off + v];
-        uint32_t first = at;
-        auto shrink = [&](uint32_t y) {   // an ancestor of v reaches all that v newly covers
-            f.cur[off + (uint32_t)f.pos[off + y]] -= c;
-            atomicSub(&gain[y], c);
-            dec += c;
-            trav_rev += (uint64_t)c * (in_row[y + 1] - in_row[y]);
-        };
-        if (s >> 32) {
-            // on a cycle: the whole component, whose root has the first position
+    const unsigned long long own = f.sc[off + v];
+    uint32_t first = at;
+    if (own >> 32) {
+        // on a cycle: the whole component, whose root has the first position
+        if (tid == 0) {
             for (uint32_t y = f.par[off + v]; y != v; y = f.par[off + y])
                 first = min(first, (uint32_t)f.pos[off + y]);
-        } else {
-            uint32_t y = f.par[off + v];
-            while (y != LT_NONE && (f.sc[off + y] >> 32) == 0) { shrink(y); y = f.par[off + y]; }
-            if (y != LT_NONE) {   // once round the cycle
-                const uint32_t y0 = y;
-                do { shrink(y); y = f.par[off + y]; } while (y != y0);
-            }
+            s_first = first;
         }
-        s_first = first;
-        s_len = (uint32_t)s;
+        __syncthreads();
+        first = s_first;
+    } else if (tid < 64) {
+        // an ancestor of v reaches all that v newly covers: the first wavefront
+        // follows the parents, one load after the other, and takes 64 of them at
+        // a time, while the others pass over the interval (no ancestor is in it)
+        uint32_t mine = 0, cnt = 0, y0 = LT_NONE;
+        auto shrink = [&]() {
+            if ((uint32_t)tid < cnt) {
+                f.cur[off + (uint32_t)f.pos[off + mine]] -= c;
+                atomicSub(&gain[mine], c);
+                dec += c;
+                trav_rev += (uint64_t)c * deg[mine].y;
+            }
+            cnt = 0;
+        };
+        for (uint32_t y = f.par[off + v]; y != LT_NONE;) {
+            const uint32_t p = f.par[off + y];
+            if (f.sc[off + y] >> 32) {   // once round the cycle
+                if (y == y0) break;
+                if (y0 == LT_NONE) y0 = y;
+            }
+            if ((uint32_t)tid == cnt) mine = y;
+            if (++cnt == 64) shrink();
+            y = p;
+        }
+        shrink();
     }
-    __syncthreads();
-    const uint32_t first = s_first, len = s_len, w = r / 64;
+    const uint32_t len = (uint32_t)own, w = r / 64;
     // most of a later seed's interval is covered already: cur is kept by
     // position, so passing over it reads consecutive words
-    for (uint32_t i0 = tid; i0 < len; i0 += LTR_NT * LTR_U) {
+    constexpr uint32_t ST = LTR_NT - 64;
+    for (uint32_t i0 = (uint32_t)tid - 64u; tid >= 64 && i0 < len; i0 += ST * LTR_U) {
         uint32_t cx[LTR_U], x[LTR_U];
 #pragma unroll
         for (int u = 0; u < LTR_U; u++) {
-            const uint32_t i = i0 + (uint32_t)u * LTR_NT;
+            const uint32_t i = i0 + (uint32_t)u * ST;
             cx[u] = i < len && i >= i0 ? f.cur[off + first + i] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < LTR_U; u++)
-            x[u] = cx[u] ? f.ord[off + first + i0 + (uint32_t)u * LTR_NT] : 0u;
+            x[u] = cx[u] ? f.ord[off + first + i0 + (uint32_t)u * ST] : 0u;
+        uint32_t last[LTR_U];
+        uint2 dg[LTR_U];
+#pragma unroll
+        for (int u = 0; u < LTR_U; u++) {
+            last[u] = t + 1;
+            dg[u] = make_uint2(0, 0);
+            if (cx[u] == 0) continue;
+            last[u] = atomicExch(&stamp[(uint64_t)w * f.n + x[u]], t + 1);
+            dg[u] = deg[x[u]];
+        }
 #pragma unroll
         for (int u = 0; u < LTR_U; u++) {
             if (cx[u] == 0) continue;
-            f.cur[off + first + i0 + (uint32_t)u * LTR_NT] = 0;
+            f.cur[off + first + i0 + (uint32_t)u * ST] = 0;
             atomicSub(&gain[x[u]], cx[u]);
-            const bool fresh = atomicExch(&stamp[(uint64_t)w * f.n + x[u]], t + 1) != t + 1;
-            const uint32_t od = row[x[u] + 1] - row[x[u]];
-            trav_fwd += od;
+        }
+#pragma unroll
+        for (int u = 0; u < LTR_U; u++) {
+            trav_fwd += dg[u].x;
             dec += cx[u];
-            trav_rev += (uint64_t)cx[u] * (in_row[x[u] + 1] - in_row[x[u]]);
-            if (fresh) { relax_fwd += od; tasks++; }
+            trav_rev += (uint64_t)cx[u] * dg[u].y;
+            if (last[u] != t + 1) { relax_fwd += dg[u].x; tasks++; }
         }
     }
     trav_fwd = group_sum<LTR_NT>(trav_fwd, red);
