@@ -53,9 +53,9 @@ def kernel_bytes(st, n, W):
 
 KERNEL_NAMES = {
     "init_t0": "k_lds_bfs<COUNT,64,...>", "init_t1": "k_lds_bfs<COUNT,256,...>",
-    "init_t2": "k_block_bfs<COUNT,...>", "forward": "k_forward",
-    "rev_t0": "k_lds_bfs<DEC,64,...>", "rev_t1": "k_lds_bfs<DEC,256,...>",
-    "rev_t2": "k_block_bfs<DEC,...>",
+    "init_t2": "k_cnt_bits", "forward": "k_fwd_snap",
+    "rev_t0": "k_lds_bfs<DEC,64,...>", "rev_t1": "k_rev_search<256,...>",
+    "rev_t2": "k_rev_search<512,...>",
 }
 
 
