@@ -57,6 +57,9 @@ KERNEL_NAMES = {
     "rev_t0": "k_lds_bfs<DEC,64,...>", "rev_t1": "k_rev_search<256,...>",
     "rev_t2": "k_rev_search<512,...>",
 }
+# linear threshold: the same phases on the snapshots' forests
+KERNEL_NAMES_LT = {"init_t0": "k_lt_up", "init_t1": "k_lt_gain", "init_t2": "k_lt_order",
+                   "forward": "k_lt_round"}
 
 
 def source_digest(files):
@@ -425,7 +428,7 @@ def run_lt(args, log):
         "phase_ms": {p: round(prof[p][0], 4) for p in prof},
         "roofline": {"bound": "hbm", "achieved": round(ach, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None,
-                     "kernel": KERNEL_NAMES[dom], "phase": dom,
+                     "kernel": KERNEL_NAMES_LT.get(dom, KERNEL_NAMES[dom]), "phase": dom,
                      "algorithmic_bytes_per_launch": int(bpl), "avg_launch_ms": round(avg_ms, 4)},
         "schedule": tuning, "cpu_baseline": cpu, "parity_vs_oracle_golden": parity,
     }

@@ -2410,10 +2410,10 @@ static void lt_prepare(const im_graph *g, uint32_t R, uint64_t seed, im_workspac
 // graphs of 60,000 nodes (27 against 23 ms), whose tasks visit about 1,900
 // nodes. Rounds by snapshot against rounds by word, ms per selection:
 //                                        forward and packing     reverse
-//   10^6 nodes, p = 0.01, R = 256        8.5 -> 1.7              22 -> 5.6
-//   weighted cascade, 15,000, R = 100    9.8 -> 3.0              13.2 -> 3.8
-//   weighted cascade, 60,000, R = 128    11.1 -> 3.5             157 -> 15.6
-//   16 uneven instances                  12.6 -> 2.8             177 -> 7.3
+//   10^6 nodes, p = 0.01, R = 256        8.5 -> 1.5              22 -> 5.2
+//   weighted cascade, 15,000, R = 100    9.8 -> 2.0              13.2 -> 3.3
+//   weighted cascade, 60,000, R = 128    11.1 -> 2.3             157 -> 14.0
+//   16 uneven instances                  12.6 -> 1.9             177 -> 6.2
 constexpr int REVA_NT = 256, REVA_CS = 2048, REVA_LIM = 1640;
 constexpr int REVB_NT = 512, REVB_CS = 4096, REVB_LIM = 3200;
 
