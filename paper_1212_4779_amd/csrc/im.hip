@@ -1301,7 +1301,7 @@ constexpr int T2_NT = 256, T2_U = 8;
 constexpr int T2W_NT = 1024;   // the wide variant: more lanes per task
 constexpr int T2S_NT = 64;     // the narrow variant: more tasks at once (long, thin searches)
 // per-phase device counters: grab0, n1, grab1, n2, grab2
-constexpr int PH_CTRS = 8;
+constexpr int PH_CTRS = 9;
 
 // ---------------------------------------------------------------------------
 // workspace
@@ -1639,21 +1639,27 @@ static uint32_t slots_for(uint32_t n, uint32_t max_slots)
 constexpr unsigned CB_LDS = 159u << 10;       // beside the kernel's own 640 bytes
 constexpr unsigned CB_RESIDENT = 28;          // wavefronts per CU, seven per SIMD (registers)
 
+// Tables: most tasks fit 512 entries, 24 wavefronts per CU, the hubs' need 4,096,
+// nine per CU (10^6 nodes, p = 0.01: 1.5 + 1.4 ms; 4,096 alone 3.45; 1,024 or 2,048
+// first 1.7 or 2.3 + 1.4; the second launch is as long as its longest task).
+constexpr unsigned CB_TABLE_WAVES = CB_LDS / (CB_CS2 * 4 + sizeof(WaveLds));   // second launch
+constexpr unsigned CB_FIRST_WAVES = 8;
+constexpr unsigned CB_FIRST_LDS = CB_FIRST_WAVES * (unsigned)(CB_CS1 * 4 + sizeof(WaveLds));
+
 static unsigned cb_lds(const im_workspace *ws, uint32_t nmax)
 {
     const unsigned map = (nmax + 31) / 32 * 4;
-    return ws->cb_waves * ((ws->cb_table ? (unsigned)CB_CS * 4u : map) + (unsigned)sizeof(WaveLds)) +
-           (ws->cb_table ? 0u : ws->cb_tasks * map);
+    return ws->cb_table ? CB_TABLE_WAVES * (unsigned)(CB_CS2 * 4 + sizeof(WaveLds))
+                        : ws->cb_waves * (map + (unsigned)sizeof(WaveLds)) + ws->cb_tasks * map;
 }
 
-template <bool TABLE>
-static unsigned cb_per_cu(const im_workspace *ws, uint32_t nmax)
+template <int CS>
+static unsigned cb_per_cu(unsigned waves, unsigned lds)
 {
     int b = 0;
-    if (hipFuncSetAttribute((const void *)k_cnt_bits<TABLE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void *)k_cnt_bits<CS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)CB_LDS) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnt_bits<TABLE>, (int)ws->cb_waves * 64,
-                                                     cb_lds(ws, nmax)) != hipSuccess) {
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_cnt_bits<CS>, (int)waves * 64, lds) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
@@ -1670,7 +1676,7 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
     ws->cb_table = 4 * (map + own) + map > CB_LDS;
     ws->cb_tasks = 4;
     if (ws->cb_table) {
-        ws->cb_waves = CB_LDS / (CB_CS * 4 + own);
+        ws->cb_waves = CB_FIRST_WAVES;
     } else {
         for (unsigned k = CB_RESIDENT / 8; k >= 1; k--) {
             const unsigned share = CB_LDS / k, all = share / (map + own);
@@ -1680,8 +1686,11 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
             if (ws->cb_waves >= 8) break;
         }
     }
-    const unsigned b = ws->cb_table ? cb_per_cu<true>(ws, nmax) : cb_per_cu<false>(ws, nmax);
-    const uint64_t per = (uint64_t)ws->cb_waves * (ws->cb_table ? (uint64_t)CB_CS : nmax);
+    const unsigned b = ws->cb_table ? cb_per_cu<CB_CS1>(CB_FIRST_WAVES, CB_FIRST_LDS)
+                                    : cb_per_cu<0>(ws->cb_waves, cb_lds(ws, nmax));
+    if (ws->cb_table && !cb_per_cu<CB_CS2>(CB_TABLE_WAVES, cb_lds(ws, nmax))) return;
+    // (the second launch's workgroups, one per CU, need no more than the first's)
+    const uint64_t per = ws->cb_table ? (uint64_t)CB_TABLE_WAVES * CB_CS2 : (uint64_t)ws->cb_waves * nmax;
     const uint64_t marks = ws->cb_table ? ws->cb_tasks * words : 0;
     const uint64_t fit = CB_BUDGET / 4 / (per + marks);
     const uint64_t groups = std::min<uint64_t>((uint64_t)b * ws->num_cu, fit);
@@ -2109,7 +2118,7 @@ static unsigned per_cu(K kernel, int nt)
 //   weighted cascade, 60,000 nodes, R = 128   63 -> 27 -> 19.3
 //   16 uneven instances                       32 -> 10.2 -> 7.4
 //   weighted cascade, 15,000 nodes, R = 100   1.8 -> 0.81 -> 0.71
-//   10^6 nodes, p = 0.01, R = 256 (tables)    6.0 -> 3.5 -> 3.4
+//   10^6 nodes, p = 0.01, R = 256 (tables)    6.0 -> 3.5 -> 2.9
 static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, hipStream_t s)
 {
     if (!ws->cb_groups || !t.sp.off || t.cand) return false;
@@ -2125,8 +2134,15 @@ static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, 
     a.stats = t.stats;
     PhaseTimer pt(ws, ph, s);
     const unsigned lds = cb_lds(ws, ws->slots_n);
-    if (ws->cb_table) k_cnt_bits<true><<<ws->cb_groups, ws->cb_waves * 64, lds, s>>>(a);
-    else k_cnt_bits<false><<<ws->cb_groups, ws->cb_waves * 64, lds, s>>>(a);
+    if (!ws->cb_table) {
+        k_cnt_bits<0><<<ws->cb_groups, ws->cb_waves * 64, lds, s>>>(a);
+        return true;
+    }
+    a.out_q = ws->ovf_q; a.out_n = ctr + 7; a.grab = ctr + 8;
+    k_cnt_bits<CB_CS1><<<ws->cb_groups, CB_FIRST_WAVES * 64, CB_FIRST_LDS, s>>>(a);
+    a.in_q = a.out_q; a.in_n = a.out_n;
+    a.out_q = ws->ovf_q2; a.out_n = ctr + 5; a.grab = ctr + 4;
+    k_cnt_bits<CB_CS2><<<std::min(ws->cb_groups, (unsigned)ws->num_cu), CB_TABLE_WAVES * 64, lds, s>>>(a);
     return true;
 }
 
@@ -2173,7 +2189,7 @@ static void run_tiers(BfsArgs a, im_workspace *ws, uint32_t *ctr, int ph0, hipSt
     a.out_q = nullptr; a.out_n = nullptr; a.grab = ctr + 4; a.tier = 2;
     if (MODE == MODE_COUNT && !PRUNE && cnt_bits(a, ws, ctr, ph0 + 2, s)) {
         // only the tasks whose snapshots share their nodes are left
-        a.in_q = ws->ovf_q; a.in_n = ctr + 5; a.grab = ctr + 6;
+        a.in_q = ws->cb_table ? ws->ovf_q2 : ws->ovf_q; a.in_n = ctr + 5; a.grab = ctr + 6;
     }
     if (MODE == MODE_DEC) a.bsplit = ws->rev_split;
     {

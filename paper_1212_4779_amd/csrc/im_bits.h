@@ -7,8 +7,9 @@
 // state (16 bytes per node and task) makes every relaxation an atomic on
 // memory that no cache holds. Here each wavefront searches one snapshot over
 // its live lists with the visited nodes as a bitmap in LDS (n / 8 bytes; on
-// graphs too large for that as a table of CB_CS nodes, with which a hub's
-// snapshots fit and a task that outgrows it goes to the dense tier), and marks
+// graphs too large for that in a table, of CB_CS1 entries in a first launch and
+// of CB_CS2, with which a hub's snapshots fit, in a second for the tasks that
+// outgrew it; the dense tier takes what is left), and marks
 // what any snapshot of the task reached in a bitmap of the task (LDS or
 // memory), which gives its (node, word) counts.
 // Bound: the two dependent loads of a level (list offsets, listed heads), times
@@ -30,7 +31,7 @@ constexpr int CB_WAVES = 16;     // most wavefronts (bits at a time) per workgro
 constexpr int CB_Q = 64;         // queue entries per wavefront kept in LDS as well
 constexpr int CB_TASKS = 8;      // most tasks in progress per workgroup
 constexpr uint32_t CB_PROBE = 8; // searches after which a task's snapshots are compared
-constexpr int CB_CS = 4096, CB_LIM = 3072;   // table entries per wavefront, most nodes in it
+constexpr int CB_CS1 = 512, CB_CS2 = 4096;  // table entries per wavefront: first launch, second
 
 struct BitsArgs {
     SnapGraph g;
@@ -40,7 +41,7 @@ struct BitsArgs {
     const uint32_t *in_q, *in_n;
     uint32_t *out_q, *out_n;     // tasks for the dense tier
     uint32_t *grab;
-    uint32_t *queue;             // [workgroups][wavefronts][nmax] (bitmaps) or [..][CB_CS] (tables)
+    uint32_t *queue;             // [workgroups][wavefronts][nmax] (bitmaps) or [..][CS] (tables)
     uint32_t *any;               // tables: [workgroups][tasks][words of the largest instance], zero at rest
     uint32_t nmax;               // nodes of the largest instance
     uint32_t tasks;              // in progress per workgroup (1 .. CB_TASKS)
@@ -132,11 +133,13 @@ struct CntTask {
 // task's last search adds up the task and opens its place. A wavefront waits
 // only for an older task (a place that is still taken) or for the one that is
 // reading the task in, never for a younger one, and takes one pair at a time.
-template <bool TABLE>
+template <int CS>   // table entries per wavefront (0: bitmaps)
 __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
 {
+    constexpr bool TABLE = CS != 0;
+    constexpr int LIM = CS / 4 * 3;   // most nodes in a table
     // bitmaps: [wavefronts + tasks][words of the largest instance]; tables:
-    // [wavefronts][CB_CS] nodes; then [wavefronts] of WaveLds
+    // [wavefronts][CS] nodes; then [wavefronts] of WaveLds
     extern __shared__ uint32_t maps[];
     __shared__ uint32_t cnt[CB_WAVES], s_item;
     __shared__ CntTask T[CB_TASKS];
@@ -144,10 +147,10 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     const uint32_t tid = threadIdx.x, lane = tid & 63u, nw = blockDim.x >> 6;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t words = (a.nmax + 31) / 32;
-    const uint32_t per = TABLE ? (uint32_t)CB_CS : words;          // words per wavefront
+    const uint32_t per = TABLE ? (uint32_t)CS : words;          // words per wavefront
     uint32_t *mine = maps + (uint64_t)wv * per;
     uint32_t *any0 = TABLE ? a.any + (uint64_t)blockIdx.x * a.tasks * words : maps + (uint64_t)nw * words;
-    uint32_t *queue = a.queue + ((uint64_t)blockIdx.x * nw + wv) * (TABLE ? (uint32_t)CB_CS : a.nmax);
+    uint32_t *queue = a.queue + ((uint64_t)blockIdx.x * nw + wv) * (TABLE ? (uint32_t)CS : a.nmax);
     const uint32_t nt = *a.in_n;
     if (blockIdx.x >= nt) return;
     const uint32_t nmaps = TABLE ? nw * per : (nw + a.tasks) * words;
@@ -201,14 +204,14 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
             };
             auto visit = [&](uint32_t v) {
                 if constexpr (TABLE) {
-                    uint32_t h = slot_hash(v) >> (32 - __builtin_ctz(CB_CS));
+                    uint32_t h = slot_hash(v) >> (32 - __builtin_ctz(TABLE ? CS : 2));
                     // (a full table is left as it is: the task is handed over)
-                    if (*(volatile uint32_t *)&cnt[wv] >= (uint32_t)CB_LIM) { tk.over = 1; return; }
+                    if (*(volatile uint32_t *)&cnt[wv] >= (uint32_t)LIM) { tk.over = 1; return; }
                     for (;;) {
                         const uint32_t key = atomicCAS(&mine[h], IM_EMPTY, v);
                         if (key == v) return;
                         if (key == IM_EMPTY) break;
-                        h = (h + 1) & (CB_CS - 1);
+                        h = (h + 1) & (CS - 1);
                     }
                     push(h);
                 } else {

@@ -42,3 +42,22 @@ def test_tasks_in_progress(im, core, n):
         assert gs["relax_init"] == st["word_reach_deg"]
         assert gs["reached_init"] == st["word_reach_nodes"] + 3 * (n - g.n)   # 130 snapshots: 3 words
     assert gs["reached_init_t2"] > 0
+
+
+@pytest.mark.parametrize("leaves", [383, 384, 3071, 3072, 5000])
+def test_table_limits(im, leaves):
+    """Hubs of exactly the nodes that the tables of the first and second launch hold, and past them."""
+    n = 260000
+    row_ptr = np.concatenate([[0], np.full(n, leaves)]).astype(np.uint64)
+    g = gg.Graph(n, row_ptr, np.arange(1, leaves + 1, dtype=np.uint32), np.ones(leaves, np.float32))
+    ref, st = oracle.initial_gains(g.row_ptr, g.col, g.prob, 2, 5)
+    d = im.Graph.from_numpy(g.row_ptr, g.col, g.prob, device="cuda:0")
+    ws = im.Workspace()
+    for _ in range(2):   # the second call finds the marks as the first left them
+        got = im.initial_gains(d, 2, 5, ws=ws).cpu().numpy()
+        assert np.array_equal(got, ref.astype(np.int64))
+        gs = ws.stats()
+        assert gs["trav_init"] == st["trav_init"]
+        assert gs["relax_init"] == st["word_reach_deg"]
+        assert gs["reached_init"] == st["word_reach_nodes"]
+    assert gs["reached_init_t2"] == leaves + 1
