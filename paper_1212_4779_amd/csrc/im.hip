@@ -1640,7 +1640,7 @@ constexpr unsigned CB_LDS = 159u << 10;       // beside the kernel's own 640 byt
 constexpr unsigned CB_RESIDENT = 28;          // wavefronts per CU, seven per SIMD (registers)
 
 // Tables: most tasks fit 512 entries, 24 wavefronts per CU, the hubs' need 4,096,
-// nine per CU (10^6 nodes, p = 0.01: 1.5 + 1.4 ms; 4,096 alone 3.45; 1,024 or 2,048
+// nine per CU (10^6 nodes, p = 0.01: 1.35 + 1.45 ms; 4,096 alone 3.45; 1,024 or 2,048
 // first 1.7 or 2.3 + 1.4; the second launch is as long as its longest task).
 constexpr unsigned CB_TABLE_WAVES = CB_LDS / (CB_CS2 * 4 + sizeof(WaveLds));   // second launch
 constexpr unsigned CB_FIRST_WAVES = 8;
@@ -1690,7 +1690,8 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
                                     : cb_per_cu<0>(ws->cb_waves, cb_lds(ws, nmax));
     if (ws->cb_table && !cb_per_cu<CB_CS2>(CB_TABLE_WAVES, cb_lds(ws, nmax))) return;
     // (the second launch's workgroups, one per CU, need no more than the first's)
-    const uint64_t per = ws->cb_table ? (uint64_t)CB_TABLE_WAVES * CB_CS2 : (uint64_t)ws->cb_waves * nmax;
+    const uint64_t per = ws->cb_table ? (uint64_t)CB_TABLE_WAVES * CB_CS2 + ws->cb_tasks * (uint64_t)CB_LIST
+                                      : (uint64_t)ws->cb_waves * nmax;
     const uint64_t marks = ws->cb_table ? ws->cb_tasks * words : 0;
     const uint64_t fit = CB_BUDGET / 4 / (per + marks);
     const uint64_t groups = std::min<uint64_t>((uint64_t)b * ws->num_cu, fit);
@@ -2118,7 +2119,7 @@ static unsigned per_cu(K kernel, int nt)
 //   weighted cascade, 60,000 nodes, R = 128   63 -> 27 -> 19.3
 //   16 uneven instances                       32 -> 10.2 -> 7.4
 //   weighted cascade, 15,000 nodes, R = 100   1.8 -> 0.81 -> 0.71
-//   10^6 nodes, p = 0.01, R = 256 (tables)    6.0 -> 3.5 -> 2.9
+//   10^6 nodes, p = 0.01, R = 256 (tables)    6.0 -> 3.5 -> 2.8
 static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, hipStream_t s)
 {
     if (!ws->cb_groups || !t.sp.off || t.cand) return false;
@@ -2131,6 +2132,7 @@ static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, 
     a.in_q = t.in_q; a.in_n = t.in_n;
     a.out_q = ws->ovf_q; a.out_n = ctr + 5; a.grab = ctr + 4;   // (ovf_q: tier 1 is done with it)
     a.queue = ws->cb_queue; a.any = ws->cb_any; a.nmax = ws->slots_n; a.tasks = ws->cb_tasks;
+    a.list = ws->cb_table ? ws->cb_queue + (uint64_t)ws->cb_groups * CB_TABLE_WAVES * CB_CS2 : nullptr;
     a.stats = t.stats;
     PhaseTimer pt(ws, ph, s);
     const unsigned lds = cb_lds(ws, ws->slots_n);

@@ -29,6 +29,7 @@
 
 constexpr int CB_WAVES = 16;     // most wavefronts (bits at a time) per workgroup
 constexpr int CB_Q = 64;         // queue entries per wavefront kept in LDS as well
+constexpr uint32_t CB_LIST = 4096;   // tables: words of a task's marks that are listed
 constexpr int CB_TASKS = 8;      // most tasks in progress per workgroup
 constexpr uint32_t CB_PROBE = 8; // searches after which a task's snapshots are compared
 constexpr int CB_CS1 = 512, CB_CS2 = 4096;  // table entries per wavefront: first launch, second
@@ -43,6 +44,7 @@ struct BitsArgs {
     uint32_t *grab;
     uint32_t *queue;             // [workgroups][wavefronts][nmax] (bitmaps) or [..][CS] (tables)
     uint32_t *any;               // tables: [workgroups][tasks][words of the largest instance], zero at rest
+    uint32_t *list;              // tables: [workgroups][tasks][CB_LIST]
     uint32_t nmax;               // nodes of the largest instance
     uint32_t tasks;              // in progress per workgroup (1 .. CB_TASKS)
     unsigned long long *stats;
@@ -123,7 +125,7 @@ struct WaveLds {
 // A task in progress. Its number among the workgroup's tasks is `ord`: free is
 // the number that may take the place next, open that of the task in it plus one.
 struct CntTask {
-    uint32_t free, open, task, done, over, sum, reached;
+    uint32_t free, open, task, done, over, sum, reached, words;
     unsigned long long relax, trav, arcs;
 };
 
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     if (tid == 0) s_item = 0;
     if (tid < CB_TASKS) {
         CntTask &t = T[tid];
-        t.free = tid; t.open = 0; t.task = 0; t.done = 0; t.over = 0; t.sum = 0; t.reached = 0;
+        t.free = tid; t.open = 0; t.task = 0; t.done = 0; t.over = 0; t.sum = 0; t.reached = 0; t.words = 0;
         t.relax = 0; t.trav = 0; t.arcs = 0;
     }
     // lane 0: of the tasks that this wavefront finished
@@ -177,6 +179,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
         const uint32_t ord = item >> 6, b = item & 63u, place = ord % a.tasks;
         CntTask &tk = T[place];
         uint32_t *any = any0 + (uint64_t)place * words;
+        uint32_t *list = a.list + ((uint64_t)blockIdx.x * a.tasks + place) * CB_LIST;
         if (b == 0) {
             while (peek(&tk.free) != ord) __builtin_amdgcn_s_sleep(1);
             if (lane == 0) {
@@ -236,7 +239,12 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                         const uint32_t dg = a.g.row[x + 1] - a.g.row[x];
                         const uint32_t i = x - base, bit = 1u << (i & 31u);
                         trav += dg;
-                        if (!(atomicOr(&any[i >> 5], bit) & bit)) { relax += dg; reached++; }
+                        const uint32_t before = atomicOr(&any[i >> 5], bit);
+                        if (!(before & bit)) { relax += dg; reached++; }
+                        if (TABLE && before == 0) {
+                            const uint32_t p = atomicAdd(&tk.words, 1u);
+                            if (p < CB_LIST) list[p] = i >> 5;
+                        }
                     }
                     wave_expand(L.B, a.g, w, b, sp, visit, arcs);
                 }
@@ -259,13 +267,21 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
             }
         }
         uint32_t done = 0;
+        if (TABLE) __builtin_amdgcn_s_waitcnt(0);   // the listed words are in place
         if (lane == 0)
             done = __hip_atomic_fetch_add(&tk.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) + 1;
         done = __builtin_amdgcn_readfirstlane(done);
         // the first searches: do the snapshots share their nodes?
         if (done == CB_PROBE && lane == 0 && tk.sum > 2u * tk.reached + 64u) post(&tk.over, 1u);
         if (done < 64) continue;
-        for (uint32_t i = lane; i < words; i += 64) any[i] = 0;
+        // (marks in memory can be far more than the task reached: clearing the
+        // words that it touched, not n / 32, took the first launch on 10^6 nodes
+        // from 1.48 to 1.35 ms, and keeps larger graphs from paying for n)
+        if (TABLE && tk.words <= CB_LIST)
+            for (uint32_t i = lane; i < tk.words; i += 64) any[list[i]] = 0;
+        else
+            for (uint32_t i = lane; i < words; i += 64) any[i] = 0;
+        wave_order();
         if (lane == 0) {
             if (tk.over) {
                 a.out_q[atomicAdd(a.out_n, 1u)] = task;
@@ -273,7 +289,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                 atomicAdd(&a.gain[src], tk.sum + (uint32_t)__popcll(valid));
                 t_relax += tk.relax; t_reached += tk.reached; t_trav += tk.trav; t_arcs += tk.arcs;
             }
-            tk.done = 0; tk.over = 0; tk.sum = 0; tk.reached = 0;
+            tk.done = 0; tk.over = 0; tk.sum = 0; tk.reached = 0; tk.words = 0;
             tk.relax = 0; tk.trav = 0; tk.arcs = 0;
         }
         wave_order();

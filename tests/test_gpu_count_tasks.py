@@ -61,3 +61,20 @@ def test_table_limits(im, leaves):
         assert gs["relax_init"] == st["word_reach_deg"]
         assert gs["reached_init"] == st["word_reach_nodes"]
     assert gs["reached_init_t2"] == leaves + 1
+
+
+@pytest.mark.parametrize("leaves", [131040, 131104, 250000])
+def test_marks_in_memory(im, leaves):
+    """A hub whose 64 snapshots together touch fewer and more words of marks than are listed."""
+    n = 260000
+    row_ptr = np.concatenate([[0], np.full(n, leaves)]).astype(np.uint64)
+    g = gg.Graph(n, row_ptr, np.arange(1, leaves + 1, dtype=np.uint32), np.full(leaves, 0.01, np.float32))
+    ref, st = oracle.initial_gains(g.row_ptr, g.col, g.prob, 64, 5)
+    d = im.Graph.from_numpy(g.row_ptr, g.col, g.prob, device="cuda:0")
+    ws = im.Workspace()
+    for _ in range(2):   # the second call finds the marks as the first left them
+        got = im.initial_gains(d, 64, 5, ws=ws).cpu().numpy()
+        assert np.array_equal(got, ref.astype(np.int64))
+        gs = ws.stats()
+        assert gs["relax_init"] == st["word_reach_deg"]
+        assert gs["reached_init"] == st["word_reach_nodes"]
