@@ -430,6 +430,10 @@ __global__ __launch_bounds__(LTR_NT) void k_lt_round(LtForest f, const uint2 *de
     const uint32_t at = (uint32_t)f.pos[off + v];
     const uint32_t c = f.cur[off + at];
     if (c == 0) return;   // covered in this snapshot
+    // every wavefront has read c before one of them clears it: it is the first
+    // word of the interval, and a wavefront that found it cleared would leave
+    // its share of the interval, or the ancestors, as they are
+    __syncthreads();
     uint64_t trav_fwd = 0, relax_fwd = 0, tasks = 0, trav_rev = 0, dec = 0;
     const unsigned long long own = f.sc[off + v];
     uint32_t first = at;
