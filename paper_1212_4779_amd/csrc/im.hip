@@ -4443,6 +4443,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     int rc;
     uint64_t N = 0, M = 0, K = 0, pairs = 0;
     uint32_t Rmax = 0, kmax = 0, nmax = 0;
+    ws->rv_on = ws->lt_on = false;   // (the workspace's last call may have set them)
     if (ws->live_edge || ws->pair_coins)
         return im_fail(IM_EINVAL, "batches draw one coin per stored arc (independent cascade)");
     for (uint32_t i = 0; i < count; i++) {
