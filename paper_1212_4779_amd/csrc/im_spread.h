@@ -59,7 +59,8 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
 {
     extern __shared__ uint32_t lds_bits[];   // [ceil(n / 32)] unless a.bits
     __shared__ uint32_t q[SPR_Q], ex[NT], rs[NT], wsum[NT / 64 + 1], cnt;
-    __shared__ uint32_t acc[SPR_ACC];
+    // (64 bits: a workgroup adds up n times its share of R, up to 2^20)
+    __shared__ unsigned long long acc[SPR_ACC];
     const uint32_t tid = threadIdx.x, words = (a.n + 31) / 32;
     uint32_t *bits = a.bits ? a.bits + (uint64_t)blockIdx.x * words : lds_bits;
     uint32_t *queue = a.queue + (uint64_t)blockIdx.x * a.n;
@@ -134,5 +135,5 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
     }
     if (sum_here)
         for (uint32_t i = tid; i < a.nS; i += NT)
-            if (acc[i]) atomicAdd(&a.marg[i], (unsigned long long)acc[i]);
+            if (acc[i]) atomicAdd(&a.marg[i], acc[i]);
 }
