@@ -1827,15 +1827,16 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
 // Buffers of the rounds by snapshot: `pairs` (node, snapshot) pairs (n R,
 // summed over a batch's instances) can be newly covered in one round. Without
 // the sparse lists the searches would read every arc's masks for a single bit,
-// past 2^32 pairs the source positions do not fit 32 bits, and the
-// affected-set recompute takes the newly covered nodes by word: such calls,
-// and those whose buffers do not fit the device, run the rounds by word
-// (k_forward_coop and the three tiers of im_bfs.h).
+// past 2^32 pairs the source positions do not fit 32 bits, a launch takes
+// fewer than 2^32 lanes (the forward step: FWS_NT per instance and snapshot of
+// a batch), and the affected-set recompute takes the newly covered nodes by
+// word: such calls, and those whose buffers do not fit the device, run the
+// rounds by word (k_forward_coop and the three tiers of im_bfs.h).
 static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W)
 {
     ws->rv_on = false;
     const uint64_t bins = (uint64_t)ws->batch.count * W * 64;
-    if (!ws->sparse || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins >= 0x40000000ull) return;
+    if (!ws->sparse || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins * FWS_NT >= (1ull << 32)) return;
     if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins || nW > ws->cap_rv_nW) {
         const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
         const uint64_t ct = cs / 64 + cb, cw = std::max(nW, ws->cap_rv_nW);   // (one partial task per bin)
