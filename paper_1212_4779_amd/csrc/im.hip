@@ -1854,11 +1854,14 @@ static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t 
 }
 
 // Buffers of the linear-threshold forests: 28 bytes per (node, snapshot).
-// Calls whose forests do not fit the device keep the general engines.
-static void reserve_lt(im_workspace *ws, uint64_t nR, uint64_t nW)
+// Calls whose forests do not fit the device keep the general engines, and so do
+// those of more lanes than one launch holds (2^32; the snapshots are rounded up
+// to LT_XCDS, so at few snapshots that is n = 2^29).
+static void reserve_lt(im_workspace *ws, uint32_t n, uint32_t R)
 {
+    const uint64_t nR = (uint64_t)n * R, nW = (uint64_t)n * ((R + 63) / 64);
     ws->lt_on = false;
-    if (t_arena) return;
+    if (t_arena || lt_grid((uint32_t)(((uint64_t)n + 255) / 256), R) * 256u >= (1ull << 32)) return;
     if (nR > ws->cap_lt_nR || nW > ws->cap_lt_nW) {
         const uint64_t cR = std::max(nR, ws->cap_lt_nR), cW = std::max(nW, ws->cap_lt_nW);
         ws->cap_lt_nR = ws->cap_lt_nW = 0;
@@ -2405,12 +2408,12 @@ static void lt_prepare(const im_graph *g, uint32_t R, uint64_t seed, im_workspac
     {
         PhaseTimer pt(ws, IM_PH_MASK_GEN, s);
         lt_rows(g, ws, s);
-        k_lt_parent<<<lt_grid(nb, (R + LTP_R - 1) / LTP_R), 256, 0, s>>>(
+        k_lt_parent<<<(unsigned)lt_grid(nb, (R + LTP_R - 1) / LTP_R), 256, 0, s>>>(
             ws->row32, ws->in_row, ws->in2out, ws->in_col, g->prob, ws->lt_start, seed, f);
     }
     {
         PhaseTimer pt(ws, IM_PH_INIT_T0, s);
-        k_lt_up<<<lt_grid(nb, R), 256, 0, s>>>(f);
+        k_lt_up<<<(unsigned)lt_grid(nb, R), 256, 0, s>>>(f);
         k_lt_cycle<<<dim3(nb, R), 256, 0, s>>>(f);
     }
     {
@@ -2613,7 +2616,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
             ws->cap_aff_k = k + 1;
         }
     }
-    if (rounds && k && ws->live_edge == 1) reserve_lt(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64));
+    if (rounds && k && ws->live_edge == 1) reserve_lt(ws, g->n, R);
     if (rounds && k && !ws->lt_on) reserve_rev(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64), (R + 63) / 64);
     if ((rc = validate(g, ws, s, ws->row32))) return rc;
     if (ws->live_edge == 1) {

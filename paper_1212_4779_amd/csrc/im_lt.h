@@ -193,12 +193,13 @@ struct LtForest {
 // A grid of lt_grid(nb, rows) workgroups walks the rows eight at a time, each on
 // one XCD (consecutive workgroups go to consecutive XCDs), so that a row's
 // scattered accesses meet in one L2 (k_lt_up 6.7 -> 5.7 ms, k_lt_parent 3.2 ->
-// 2.8, 200,000 nodes, R = 256). False: past the last row.
+// 2.8, 200,000 nodes, R = 256). False: past the last row. (64 bits: the launches'
+// lanes stay below 2^32, see reserve_lt.)
 constexpr uint32_t LT_XCDS = 8;
 
-__host__ __device__ __forceinline__ uint32_t lt_grid(uint32_t nb, uint32_t rows)
+__host__ __device__ __forceinline__ uint64_t lt_grid(uint32_t nb, uint32_t rows)
 {
-    return nb * ((rows + LT_XCDS - 1) / LT_XCDS * LT_XCDS);
+    return (uint64_t)nb * ((rows + LT_XCDS - 1) / LT_XCDS * LT_XCDS);
 }
 
 __device__ __forceinline__ bool lt_place(uint32_t nb, uint32_t rows, uint32_t &block, uint32_t &row)
