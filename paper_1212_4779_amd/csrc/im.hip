@@ -1358,9 +1358,11 @@ struct im_workspace {
     uint32_t *hslot[2] = {}, *hlist[2] = {}, *hcnt[2] = {}, *hoff[2] = {}, *hadj[2] = {};
     unsigned long long *hbase[2] = {};
     uint32_t *hnum = nullptr;            // [2] hub counts
-    // per-snapshot live lists of the other nodes, per direction
+    // per-snapshot live lists of the other nodes, per direction; sp_on: this
+    // call's are in place
     int sparse = 1;
-    uint64_t sp_len = 0, sp_cap = 0;
+    bool sp_on[2] = {};
+    uint64_t sp_len[2] = {}, sp_cap[2] = {};
     uint32_t *sp_off[2] = {}, *sp_adj[2] = {};
     unsigned long long *sp_alloc = nullptr;  // [2]
     unsigned long long *halloc = nullptr;  // [2] allocation counters
@@ -1670,7 +1672,7 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
 {
     constexpr uint64_t CB_BUDGET = 4ull << 30;
     ws->cb_groups = 0;
-    if (!ws->sparse || t_arena || !nmax) return;
+    if (!ws->sp_on[0] || t_arena || !nmax) return;
     const uint64_t words = (nmax + 31) / 32;
     const unsigned map = (unsigned)std::min<uint64_t>(words * 4, CB_LDS), own = sizeof(WaveLds);
     ws->cb_table = 4 * (map + own) + map > CB_LDS;
@@ -1770,7 +1772,6 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
         ws->cap_n = cn;
     }
     if ((rc = reserve_slots(ws, slot_len))) return rc;
-    reserve_bits(ws, slot_len);
     if (grow_m) {
         if ((rc = dalloc(&ws->in_col, cm)) || (rc = dalloc(&ws->in2out, cm)) ||
             (rc = dalloc(&ws->mask_out, cm * cW)) || (rc = dalloc(&ws->mask_in, cm * cW)))
@@ -1794,21 +1795,7 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
                 return rc;
         ws->cap_hub = ch;
     }
-    if (ws->sparse) {
-        const uint64_t len = sparse_stride(ws->cap_n) * 64u * cW;
-        if (len > ws->sp_len) {
-            for (int d = 0; d < 2; d++)
-                if ((rc = dalloc(&ws->sp_off[d], len))) return rc;
-            if ((rc = dalloc(&ws->sp_alloc, 2))) return rc;
-            ws->sp_len = len;
-        }
-        const uint64_t cap = std::min<uint64_t>(16ull * ws->cap_m * cW, 0x7FFFFFFFull);
-        if (cap > ws->sp_cap) {
-            for (int d = 0; d < 2; d++)
-                if ((rc = dalloc(&ws->sp_adj[d], cap))) return rc;
-            ws->sp_cap = cap;
-        }
-    }
+    if (!ws->sp_alloc && (rc = dalloc(&ws->sp_alloc, 2))) return rc;
     const uint64_t nkeys = (uint64_t)(k + 1) * ws->batch.count;
     if (nkeys > ws->cap_keys) {
         if ((rc = dalloc(&ws->keys, nkeys))) return rc;
@@ -1824,19 +1811,46 @@ static int ws_reserve(im_workspace *ws, uint32_t n, uint64_t m, uint32_t W, uint
     return IM_OK;
 }
 
+// The live lists of one direction, as large as this call needs: 4 bytes per
+// (node, snapshot) and the heads. A call whose lists do not fit the device goes
+// without (as with IM_OPT_SPARSE_LISTS 0).
+static void reserve_sparse(im_workspace *ws, int d, uint32_t n, uint64_t m, uint32_t R)
+{
+    ws->sp_on[d] = false;
+    if (!ws->sparse || t_arena) return;
+    const uint64_t len = sparse_stride(n) * R;
+    const uint64_t cap = std::min<uint64_t>(16ull * m * ((R + 63) / 64), 0x7FFFFFFFull);
+    bool ok = true;
+    if (len > ws->sp_len[d] || !ws->sp_off[d]) {
+        ws->sp_len[d] = 0;
+        ok = dalloc(&ws->sp_off[d], len) == IM_OK;
+        if (ok) ws->sp_len[d] = len;
+    }
+    if (ok && (cap > ws->sp_cap[d] || !ws->sp_adj[d])) {
+        ws->sp_cap[d] = 0;
+        ok = dalloc(&ws->sp_adj[d], cap) == IM_OK;
+        if (ok) ws->sp_cap[d] = cap;
+    }
+    if (!ok) {
+        dfree(ws->sp_off[d]); dfree(ws->sp_adj[d]);
+        ws->sp_len[d] = ws->sp_cap[d] = 0;
+    }
+    ws->sp_on[d] = ok;
+}
+
 // Buffers of the rounds by snapshot: `pairs` (node, snapshot) pairs (n R,
 // summed over a batch's instances) can be newly covered in one round. Without
-// the sparse lists the searches would read every arc's masks for a single bit,
+// the sparse lists (`lists`: of the directions searched) the searches would read every arc's masks for a single bit,
 // past 2^32 pairs the source positions do not fit 32 bits, a launch takes
 // fewer than 2^32 lanes (the forward step: FWS_NT per instance and snapshot of
 // a batch), and the affected-set recompute takes the newly covered nodes by
 // word: such calls, and those whose buffers do not fit the device, run the
 // rounds by word (k_forward_coop and the three tiers of im_bfs.h).
-static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W)
+static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W, bool lists)
 {
     ws->rv_on = false;
     const uint64_t bins = (uint64_t)ws->batch.count * W * 64;
-    if (!ws->sparse || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins * FWS_NT >= (1ull << 32)) return;
+    if (!lists || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins * FWS_NT >= (1ull << 32)) return;
     if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins || nW > ws->cap_rv_nW) {
         const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
         const uint64_t ct = cs / 64 + cb, cw = std::max(nW, ws->cap_rv_nW);   // (one partial task per bin)
@@ -2064,18 +2078,18 @@ static void build_hubs(int d, const uint32_t *row, const uint32_t *col, const ui
 static void build_sparse(int d, const uint32_t *row, const uint32_t *col, const uint64_t *mask,
                          uint32_t n, uint64_t m, uint32_t R, im_workspace *ws, hipStream_t s)
 {
-    if (!ws->sparse || n == 0) return;
+    if (!ws->sp_on[d] || n == 0) return;
     fill<unsigned long long>(ws->sp_alloc + d, 1, 0ull, s);
     const uint32_t W = (R + 63) / 64;
     const unsigned grid = (unsigned)std::min<uint64_t>((uint64_t)W * ((n + 255) / 256), 8192);
     k_sparse_build<<<grid, 256, 0, s>>>(row, col, mask, m, n, R, W, ws->hub_deg, ws->sp_off[d],
-                                        sparse_stride(n), ws->sp_adj[d], ws->sp_alloc + d, ws->sp_cap);
+                                        sparse_stride(n), ws->sp_adj[d], ws->sp_alloc + d, ws->sp_cap[d]);
 }
 
 static SparseLists sparse_lists(im_workspace *ws, int d, uint32_t n)
 {
     SparseLists l = {nullptr, nullptr, 0};
-    if (ws->sparse) {
+    if (ws->sp_on[d]) {
         l.off = ws->sp_off[d];
         l.adj = ws->sp_adj[d];
         l.stride = sparse_stride(n);
@@ -2582,13 +2596,30 @@ static int greedy_round(const im_graph *g, uint32_t R, uint32_t t, uint32_t *see
     return IM_OK;
 }
 
-// workspace growth and input validation (synchronous)
-// (rounds: the call runs greedy rounds of the dynamic update)
+// What a path reads of the reverse direction: the dynamic update's reverse
+// searches need all of it (reverse CSR, reverse-order masks, reverse hub and
+// sparse lists); the lazy path and the initial counts alone need none of it,
+// or only the in-degrees (the learned policy's node features). Linear
+// threshold snapshots are drawn per in-row and always build the reverse CSR.
+// PREP_MASKS: no searches at all.
+enum { PREP_FORWARD = 0, PREP_INDEG = 1, PREP_REVERSE = 2, PREP_MASKS = 3 };
+
+static int reserve_lazy(im_workspace *ws, uint32_t n, uint32_t W);
+
+// none of a call's optional buffers is in place yet
+static void optional_off(im_workspace *ws)
+{
+    ws->rv_on = ws->lt_on = ws->sp_on[0] = ws->sp_on[1] = false;
+    ws->cb_groups = 0;
+}
+
+// workspace growth and input validation (synchronous); the buffers that a call
+// can do without come last, out of what the others leave
 static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_workspace *ws,
-                             hipStream_t s, bool rounds = true)
+                             hipStream_t s, int need = PREP_REVERSE)
 {
     int rc;
-    ws->rv_on = ws->lt_on = false;
+    optional_off(ws);
     if ((rc = ws_reserve(ws, g->n, g->m, (R + 63) / 64, k, g->n))) return rc;
     if (ws->aff_gain && ws->batch.count == 1) {
         const uint64_t nW = (uint64_t)g->n * ((R + 63) / 64);
@@ -2616,8 +2647,9 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
             ws->cap_aff_k = k + 1;
         }
     }
-    if (rounds && k && ws->live_edge == 1) reserve_lt(ws, g->n, R);
-    if (rounds && k && !ws->lt_on) reserve_rev(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64), (R + 63) / 64);
+    if (k && g->n && (need == PREP_FORWARD || need == PREP_INDEG) &&
+        (rc = reserve_lazy(ws, g->n, (R + 63) / 64)))
+        return rc;
     if ((rc = validate(g, ws, s, ws->row32))) return rc;
     if (ws->live_edge == 1) {
         if (ws->batch.count > 1) return im_fail(IM_EINVAL, "linear-threshold snapshots apply to single graphs only");
@@ -2640,15 +2672,18 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
         }
         if ((rc = und_pair_ids(g, ws->row32, ws->pair, ws, s))) return rc;
     }
+    if (need == PREP_MASKS) return IM_OK;
+    const bool rounds = need == PREP_REVERSE && k;
+    if (rounds && ws->live_edge == 1) reserve_lt(ws, g->n, R);
+    if (ws->lt_on) return IM_OK;
+    reserve_sparse(ws, 0, g->n, g->m, R);
+    if (need == PREP_REVERSE) reserve_sparse(ws, 1, g->n, g->m, R);
+    if (rounds)
+        reserve_rev(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64), (R + 63) / 64,
+                    ws->sp_on[0] && ws->sp_on[1]);
+    reserve_bits(ws, g->n);
     return IM_OK;
 }
-
-// What a path reads of the reverse direction: the dynamic update's reverse
-// searches need all of it (reverse CSR, reverse-order masks, reverse hub and
-// sparse lists); the lazy path and the initial counts alone need none of it,
-// or only the in-degrees (the learned policy's node features). Linear
-// threshold snapshots are drawn per in-row and always build the reverse CSR.
-enum { PREP_FORWARD = 0, PREP_INDEG = 1, PREP_REVERSE = 2 };
 
 // everything after validation up to (and including) the initial gains:
 // kernel launches only (no host synchronisation, no memset), so that the
@@ -2664,7 +2699,7 @@ static int enqueue_prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_
     if (ws->aff_gain && ws->batch.count == 1) fill<uint32_t>(ws->a_ctrs, (uint64_t)(k + 1) * PH_CTRS, 0u, s);
     fill<uint32_t>(ws->gain, n, 0u, s);
     fill<uint8_t>(ws->sel, n, (uint8_t)0, s);
-    fill<uint64_t>(ws->covered, ws->sparse ? cov_len(n, W) : (uint64_t)n * W, 0ull, s);
+    fill<uint64_t>(ws->covered, ws->sp_on[0] ? cov_len(n, W) : (uint64_t)n * W, 0ull, s);
     if (ws->rv_on) fill<uint32_t>(ws->rv_stamp, (uint64_t)n * W, 0u, s);
     const bool rev = need == PREP_REVERSE || ws->live_edge == 1;
     if (ws->lt_on) {
@@ -2695,7 +2730,7 @@ static int prepare(const im_graph *g, uint32_t R, uint64_t seed, uint32_t k, im_
                    hipStream_t s, int need = PREP_REVERSE)
 {
     int rc;
-    if ((rc = check_and_reserve(g, R, k, ws, s, need == PREP_REVERSE))) return rc;
+    if ((rc = check_and_reserve(g, R, k, ws, s, need))) return rc;
     return enqueue_prepare(g, R, seed, k, ws, s, need);
 }
 
@@ -3470,6 +3505,14 @@ static int reserve_eval(im_workspace *ws, uint32_t n, uint32_t V)
     return IM_OK;
 }
 
+// what select_lazy cannot do without
+static int reserve_lazy(im_workspace *ws, uint32_t n, uint32_t W)
+{
+    const int rc = reserve_celf(ws, n);
+    const uint32_t vmax = ws->lazy_engine == 1 ? eval_vmax(n, W) : 0u;
+    return rc || !vmax ? rc : reserve_eval(ws, n, vmax);
+}
+
 // exact gains of cand[0..ncand) into ev (zeroed by the pick) on cooperative grids
 static int eval_coop(const im_graph *g, uint32_t R, uint32_t ncand, uint32_t vmax, im_workspace *ws,
                      hipStream_t s)
@@ -3655,7 +3698,7 @@ static bool reserve_eval_snap(im_workspace *ws, uint32_t n, uint32_t R, uint32_t
     const uint64_t per = (uint64_t)B * R, nq = per * n;
     const uint64_t nb = n > EVS_LDS_NODES ? per * ((n + 31) / 32) : 0;
     if (ws->lazy_engine != 2 || ws->eval_split || per >= (1ull << 31) || (nq + nb) * 4 > LZ_BUDGET) return false;
-    reserve_rev(ws, (uint64_t)n * R, (uint64_t)n * ((R + 63) / 64), (R + 63) / 64);
+    reserve_rev(ws, (uint64_t)n * R, (uint64_t)n * ((R + 63) / 64), (R + 63) / 64, ws->sp_on[0]);
     if (!ws->rv_on) return false;
     if (nq > ws->cap_lz_q || per > ws->cap_lz) {
         const uint64_t cq = std::max(nq, ws->cap_lz_q), cp = std::max(per, ws->cap_lz);
@@ -3694,9 +3737,7 @@ static int select_lazy(const im_graph *g, uint32_t R, uint32_t k, uint32_t B, co
     const uint32_t n = g->n, W = (R + 63) / 64;
     const bool learned = model != nullptr;
     const float invR = 1.0f / (float)R;
-    if ((rc = reserve_celf(ws, n))) return rc;
     const uint32_t vmax = ws->lazy_engine == 1 ? eval_vmax(n, W) : 0u;
-    if (vmax && (rc = reserve_eval(ws, n, vmax))) return rc;
     k_copy_u32<<<grid_for(n, 256), 256, 0, s>>>(ws->gain, ws->c_bound, n);
     fill<uint32_t>(ws->c_fresh, n, 0u, s);
     fill<uint32_t>(ws->c_ctl, CC_COUNT, 0u, s);
@@ -4032,7 +4073,7 @@ extern "C" int im_snapshot_masks(const im_graph *g, uint32_t R, uint64_t seed, u
     if ((rc = check_args(g, R))) return rc;
     if (!ws || (g->m && !mask_out)) return im_fail(IM_EINVAL, "null workspace or output");
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = check_and_reserve(g, R, 0, ws, s))) return rc;
+    if ((rc = check_and_reserve(g, R, 0, ws, s, PREP_MASKS))) return rc;
     if (ws->live_edge == 1) build_reverse(g, ws, s);   // linear threshold draws per in-row
     build_masks(g, R, seed, ws, mask_out, false, s);
     HIPCHK(hipGetLastError());
@@ -4447,7 +4488,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     int rc;
     uint64_t N = 0, M = 0, K = 0, pairs = 0;
     uint32_t Rmax = 0, kmax = 0, nmax = 0;
-    ws->rv_on = ws->lt_on = false;   // (the workspace's last call may have set them)
+    optional_off(ws);   // (the workspace's last call may have set them)
     if (ws->live_edge || ws->pair_coins)
         return im_fail(IM_EINVAL, "batches draw one coin per stored arc (independent cascade)");
     for (uint32_t i = 0; i < count; i++) {
@@ -4468,9 +4509,13 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     const uint32_t W = (Rmax + 63) / 64;
     ws->batch.count = count;  // sizes the per-round key arrays
     rc = ws_reserve(ws, (uint32_t)N, M, W, kmax, nmax);
-    if (!rc) reserve_rev(ws, pairs, N * W, W);
-    ws->batch.count = 1;
     if (!rc) rc = reserve_batch(ws, count, N, M);
+    if (!rc) {
+        for (int d = 0; d < 2; d++) reserve_sparse(ws, d, (uint32_t)N, M, Rmax);
+        reserve_rev(ws, pairs, N * W, W, ws->sp_on[0] && ws->sp_on[1]);
+        reserve_bits(ws, nmax);
+    }
+    ws->batch.count = 1;
     if (rc) return rc;
     // per-instance tables, staged in pinned memory
     uint32_t *hu = (uint32_t *)ws->b_host;              // R, k, kpre, node_off
@@ -4932,7 +4977,7 @@ extern "C" int im_autotune(const im_graph *g, uint32_t R, uint64_t seed, im_work
     if ((rc = check_args(g, R))) return rc;
     if (!ws) return im_fail(IM_EINVAL, "null workspace");
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = check_and_reserve(g, R, 0, ws, s))) return rc;
+    if ((rc = check_and_reserve(g, R, 0, ws, s, PREP_MASKS))) return rc;
     TuneKey key;
     if ((rc = graph_signature(g, R, ws, s, &key))) return rc;
     bool hit;
@@ -5051,7 +5096,7 @@ extern "C" int im_autotune_lazy(const im_graph *g, uint32_t R, uint32_t k, uint6
             ws->lazy_engine = eng;
             float ms_min = -1.0f;
             for (int rep = 0; rep < 2 && !rc; rep++) {
-                if ((rc = check_and_reserve(g, R, kt, ws, s, false))) break;
+                if ((rc = check_and_reserve(g, R, kt, ws, s, model ? PREP_INDEG : PREP_FORWARD))) break;
                 if ((rc = (int)(hipEventRecord(e0, s) != hipSuccess ? IM_EHIP : IM_OK))) break;
                 rc = enqueue_prepare(g, R, seed, kt, ws, s, model ? PREP_INDEG : PREP_FORWARD);
                 if (!rc) rc = select_lazy(g, R, kt, B, model, sd, gd, ws, s);
@@ -5106,7 +5151,7 @@ extern "C" int im_node_features(const im_graph *g, float *feat_out, im_workspace
     if (!g || !ws || (g->n && !feat_out)) return im_fail(IM_EINVAL, "null argument");
     if ((rc = check_args(g, 1))) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = check_and_reserve(g, 1, 0, ws, s))) return rc;
+    if ((rc = check_and_reserve(g, 1, 0, ws, s, PREP_MASKS))) return rc;
     if (g->n == 0) return IM_OK;
     build_reverse(g, ws, s);
     launch_features(ws->row32, g->col, g->prob, ws->in_row, g->n, feat_out, s);

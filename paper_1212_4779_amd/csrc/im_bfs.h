@@ -82,7 +82,7 @@ struct HubLists {
 // their single snapshot bit, so only arcs live in the delta's snapshots are
 // read.
 struct SparseLists {
-    const uint32_t *off;    // [64 W][stride], nullptr: no lists
+    const uint32_t *off;    // [R][stride], nullptr: no lists
     const uint32_t *adj;
     uint64_t stride;        // 257 ceil(n / 256)
 };
