@@ -1532,6 +1532,23 @@ static void dfree(Tv *&p)
     p = nullptr;
 }
 
+// Whether the device has room for `bytes` that a call can do without. What is
+// left has to serve the runtime: kernels with private memory (k_forward_coop,
+// k_lt_round and others: up to 250 bytes a lane, 130 MB on a full device, per
+// hardware queue) get it when they are launched, and a launch that cannot have
+// it ends the process.
+constexpr uint64_t ROOM_LEFT = 1ull << 30;
+
+static bool room_for(uint64_t bytes)
+{
+    size_t left = 0, total = 0;
+    if (hipMemGetInfo(&left, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return left >= bytes + ROOM_LEFT;
+}
+
 struct EvalArgs;
 __global__ __launch_bounds__(FWD_NT) void k_eval_coop(EvalArgs a);
 
@@ -1700,11 +1717,14 @@ static void reserve_bits(im_workspace *ws, uint32_t nmax)
     if (groups == 0) return;
     if (groups * per > ws->cap_cb) {
         ws->cap_cb = 0;
-        if (dalloc(&ws->cb_queue, groups * per)) return;
+        dfree(ws->cb_queue);
+        if (!room_for(groups * per * 4) || dalloc(&ws->cb_queue, groups * per)) return;
         ws->cap_cb = groups * per;
     }
     if (ws->cb_table && groups * marks > ws->cap_cb_any) {
         ws->cap_cb_any = 0;
+        dfree(ws->cb_any);
+        if (!room_for(groups * marks * 4)) return;
         if (dalloc(&ws->cb_any, groups * marks) || ws_memset(ws->cb_any, groups * marks * 4)) return;
         ws->cap_cb_any = groups * marks;
     }
@@ -1823,12 +1843,14 @@ static void reserve_sparse(im_workspace *ws, int d, uint32_t n, uint64_t m, uint
     bool ok = true;
     if (len > ws->sp_len[d] || !ws->sp_off[d]) {
         ws->sp_len[d] = 0;
-        ok = dalloc(&ws->sp_off[d], len) == IM_OK;
+        dfree(ws->sp_off[d]);
+        ok = room_for(len * 4) && dalloc(&ws->sp_off[d], len) == IM_OK;
         if (ok) ws->sp_len[d] = len;
     }
     if (ok && (cap > ws->sp_cap[d] || !ws->sp_adj[d])) {
         ws->sp_cap[d] = 0;
-        ok = dalloc(&ws->sp_adj[d], cap) == IM_OK;
+        dfree(ws->sp_adj[d]);
+        ok = room_for(cap * 4) && dalloc(&ws->sp_adj[d], cap) == IM_OK;
         if (ok) ws->sp_cap[d] = cap;
     }
     if (!ok) {
@@ -1855,6 +1877,8 @@ static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t 
         const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
         const uint64_t ct = cs / 64 + cb, cw = std::max(nW, ws->cap_rv_nW);   // (one partial task per bin)
         ws->cap_rv_src = ws->cap_rv_bins = ws->cap_rv_nW = 0;
+        dfree(ws->rv_src); dfree(ws->rv_tasks); dfree(ws->rv_q); dfree(ws->rv_stamp);
+        if (!room_for(4 * cs + 12 * ct + 4 * cw)) return;
         if (dalloc(&ws->rv_src, cs) || dalloc(&ws->rv_tasks, ct) || dalloc(&ws->rv_q, ct) ||
             dalloc(&ws->rv_stamp, cw)) {
             dfree(ws->rv_src); dfree(ws->rv_tasks); dfree(ws->rv_q); dfree(ws->rv_stamp);
@@ -1879,6 +1903,9 @@ static void reserve_lt(im_workspace *ws, uint32_t n, uint32_t R)
     if (nR > ws->cap_lt_nR || nW > ws->cap_lt_nW) {
         const uint64_t cR = std::max(nR, ws->cap_lt_nR), cW = std::max(nW, ws->cap_lt_nW);
         ws->cap_lt_nR = ws->cap_lt_nW = 0;
+        dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord);
+        dfree(ws->lt_sc); dfree(ws->lt_pos); dfree(ws->lt_stamp); dfree(ws->lt_deg);
+        if (!room_for(28 * cR + 12 * cW)) return;
         if (dalloc(&ws->lt_par, cR) || dalloc(&ws->lt_cur, cR) || dalloc(&ws->lt_ord, cR) ||
             dalloc(&ws->lt_sc, cR) || dalloc(&ws->lt_pos, cR) || dalloc(&ws->lt_stamp, cW) ||
             dalloc(&ws->lt_deg, cW)) {
@@ -3703,12 +3730,16 @@ static bool reserve_eval_snap(im_workspace *ws, uint32_t n, uint32_t R, uint32_t
     if (nq > ws->cap_lz_q || per > ws->cap_lz) {
         const uint64_t cq = std::max(nq, ws->cap_lz_q), cp = std::max(per, ws->cap_lz);
         ws->cap_lz_q = ws->cap_lz = 0;
+        dfree(ws->lz_q);
+        if (!room_for(4 * cq + 4 * cp)) return false;
         if (dalloc(&ws->lz_q, cq) || dalloc(&ws->lz_len, cp) || dalloc(&ws->lz_src, CELF_BMAX)) return false;
         ws->cap_lz_q = cq;
         ws->cap_lz = cp;
     }
     if (nb > ws->cap_lz_b) {
         ws->cap_lz_b = 0;
+        dfree(ws->lz_bits);
+        if (!room_for(nb * 4)) return false;
         if (dalloc(&ws->lz_bits, nb) || ws_memset(ws->lz_bits, nb * 4)) return false;
         ws->cap_lz_b = nb;
     }
