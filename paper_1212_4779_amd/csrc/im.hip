@@ -1593,11 +1593,11 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
 {
     if (!ws) return IM_OK;
     (void)hipDeviceSynchronize();
+    im_ws_give_back(ws);
     dfree(ws->row32); dfree(ws->in_row); dfree(ws->in_col); dfree(ws->in2out);
     dfree(ws->cnt); dfree(ws->scan_sums); dfree(ws->mask_out); dfree(ws->mask_in);
     dfree(ws->gain); dfree(ws->sel); dfree(ws->covered); dfree(ws->newly);
     dfree(ws->fpend); dfree(ws->fqa); dfree(ws->fqb); dfree(ws->fvis); dfree(ws->bqa); dfree(ws->bqb); dfree(ws->fctr);
-    dfree(ws->rv_src); dfree(ws->rv_q); dfree(ws->rv_stamp); dfree(ws->rv_tasks);
     dfree(ws->pk); dfree(ws->boff); dfree(ws->plist); dfree(ws->mlist);
     dfree(ws->tnodes); dfree(ws->tcounts); dfree(ws->keys); dfree(ws->ovf_q); dfree(ws->ovf_q2); dfree(ws->ctrs);
     dfree(ws->b_reach);
@@ -1607,7 +1607,6 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
         dfree(ws->hadj[d]); dfree(ws->hbase[d]);
     }
     dfree(ws->hnum); dfree(ws->halloc);
-    for (int d = 0; d < 2; d++) { dfree(ws->sp_off[d]); dfree(ws->sp_adj[d]); }
     dfree(ws->sp_alloc);
     dfree(ws->b_node_inst); dfree(ws->b_mcol); dfree(ws->b_mprob); dfree(ws->b_u32);
     dfree(ws->b_u64); dfree(ws->b_desc);
@@ -1621,10 +1620,6 @@ extern "C" int im_workspace_destroy(im_workspace *ws)
     ws->und = nullptr;
     dfree(ws->pair);
     dfree(ws->lt_start); dfree(ws->lt_task);
-    dfree(ws->cb_queue); dfree(ws->cb_any);
-    dfree(ws->lz_q); dfree(ws->lz_len); dfree(ws->lz_src); dfree(ws->lz_bits);
-    dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord); dfree(ws->lt_stamp); dfree(ws->lt_sc); dfree(ws->lt_pos);
-    dfree(ws->lt_deg);
     dfree(ws->a_reach); dfree(ws->a_pend); dfree(ws->a_qa); dfree(ws->a_qb); dfree(ws->a_vis);
     dfree(ws->a_mark); dfree(ws->a_list); dfree(ws->a_cnt); dfree(ws->a_ctrs);
     dfree(ws->v_row32); dfree(ws->v_coin); dfree(ws->v_queue); dfree(ws->v_bits);
@@ -2640,13 +2635,56 @@ static void optional_off(im_workspace *ws)
     ws->cb_groups = 0;
 }
 
-// workspace growth and input validation (synchronous); the buffers that a call
-// can do without come last, out of what the others leave
-static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_workspace *ws,
-                             hipStream_t s, int need = PREP_REVERSE)
+// The optional buffers of earlier calls are given back. (hipFree waits for the
+// device, so work in flight keeps them until it is done.)
+void im_ws_give_back(im_workspace *ws)
+{
+    optional_off(ws);
+    dfree(ws->cb_queue); dfree(ws->cb_any);
+    ws->cap_cb = ws->cap_cb_any = 0;
+    dfree(ws->rv_src); dfree(ws->rv_q); dfree(ws->rv_stamp); dfree(ws->rv_tasks);
+    ws->cap_rv_src = ws->cap_rv_bins = ws->cap_rv_nW = 0;
+    dfree(ws->lz_q); dfree(ws->lz_len); dfree(ws->lz_src); dfree(ws->lz_bits);
+    ws->cap_lz_q = ws->cap_lz = ws->cap_lz_b = 0;
+    dfree(ws->lt_par); dfree(ws->lt_cur); dfree(ws->lt_ord); dfree(ws->lt_stamp); dfree(ws->lt_sc);
+    dfree(ws->lt_pos); dfree(ws->lt_deg);
+    ws->cap_lt_nR = ws->cap_lt_nW = 0;
+    for (int d = 0; d < 2; d++) {
+        dfree(ws->sp_off[d]); dfree(ws->sp_adj[d]);
+        ws->sp_len[d] = ws->sp_cap[d] = 0;
+    }
+}
+
+// Run `reserve` (buffers that the call cannot do without); where the device has
+// no room left for them, once more without what earlier calls keep on this
+// workspace but could do without. What is there after a second failure is not
+// used again: the next call reserves everything afresh.
+template <typename F>
+static int with_room(im_workspace *ws, F reserve)
+{
+    int rc = reserve();
+    if (rc != IM_ENOMEM) return rc;
+    im_ws_give_back(ws);
+    rc = reserve();
+    if (rc == IM_ENOMEM) {
+        ws->cap_n = ws->cap_W = ws->cap_k = 0;
+        ws->cap_m = ws->cap_hub = ws->cap_keys = ws->slots_entries = 0;
+        ws->cap_aff_nW = 0;
+        ws->cap_aff_n = ws->cap_aff_k = 0;
+        ws->cap_celf = 0;
+        ws->cap_sort = ws->cap_kept = ws->cap_eval = 0;
+        ws->cap_lt_m = ws->cap_pair = 0;
+        ws->cap_lt_n = ws->cap_count = 0;
+        ws->cap_bn = ws->cap_bm = 0;
+    }
+    return rc;
+}
+
+// the buffers that a call cannot do without (and of linear threshold and pair
+// coins, what their preparation needs)
+static int reserve_needed(const im_graph *g, uint32_t R, uint32_t k, im_workspace *ws, int need)
 {
     int rc;
-    optional_off(ws);
     if ((rc = ws_reserve(ws, g->n, g->m, (R + 63) / 64, k, g->n))) return rc;
     if (ws->aff_gain && ws->batch.count == 1) {
         const uint64_t nW = (uint64_t)g->n * ((R + 63) / 64);
@@ -2677,10 +2715,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
     if (k && g->n && (need == PREP_FORWARD || need == PREP_INDEG) &&
         (rc = reserve_lazy(ws, g->n, (R + 63) / 64)))
         return rc;
-    if ((rc = validate(g, ws, s, ws->row32))) return rc;
     if (ws->live_edge == 1) {
-        if (ws->batch.count > 1) return im_fail(IM_EINVAL, "linear-threshold snapshots apply to single graphs only");
-        if (ws->pair_coins) return im_fail(IM_EINVAL, "pair coins and linear-threshold snapshots exclude each other");
         if (g->m > ws->cap_lt_m || !ws->lt_start) {
             if ((rc = dalloc(&ws->lt_start, g->m))) return rc;
             ws->cap_lt_m = g->m;
@@ -2690,14 +2725,30 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
             ws->cap_lt_n = g->n + 1;
         }
     }
+    if (ws->pair_coins && (g->m > ws->cap_pair || !ws->pair)) {
+        if ((rc = dalloc(&ws->pair, g->m))) return rc;
+        ws->cap_pair = g->m;
+    }
+    return IM_OK;
+}
+
+// workspace growth and input validation (synchronous); the buffers that a call
+// can do without come last, out of what the others leave
+static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_workspace *ws,
+                             hipStream_t s, int need = PREP_REVERSE)
+{
+    int rc;
+    optional_off(ws);
+    if ((rc = with_room(ws, [&] { return reserve_needed(g, R, k, ws, need); }))) return rc;
+    if ((rc = validate(g, ws, s, ws->row32))) return rc;
+    if (ws->live_edge == 1) {
+        if (ws->batch.count > 1) return im_fail(IM_EINVAL, "linear-threshold snapshots apply to single graphs only");
+        if (ws->pair_coins) return im_fail(IM_EINVAL, "pair coins and linear-threshold snapshots exclude each other");
+    }
     if (ws->pair_coins) {
         // the pair of every arc (host-synchronous; before any capture)
         if (ws->batch.count > 1) return im_fail(IM_EINVAL, "pair coins apply to single graphs only");
-        if (g->m > ws->cap_pair || !ws->pair) {
-            if ((rc = dalloc(&ws->pair, g->m))) return rc;
-            ws->cap_pair = g->m;
-        }
-        if ((rc = und_pair_ids(g, ws->row32, ws->pair, ws, s))) return rc;
+        if ((rc = with_room(ws, [&] { return und_pair_ids(g, ws->row32, ws->pair, ws, s); }))) return rc;
     }
     if (need == PREP_MASKS) return IM_OK;
     const bool rounds = need == PREP_REVERSE && k;
@@ -4011,7 +4062,7 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
                             : lanes == 128 ? spread_groups<128>(ws, n, R, lds)
                             : lanes == 256 ? spread_groups<256>(ws, n, R, lds)
                                            : spread_groups<512>(ws, n, R, lds);
-    if ((rc = reserve_spread(ws, n, m, groups))) return rc;
+    if ((rc = with_room(ws, [&] { return reserve_spread(ws, n, m, groups); }))) return rc;
     if ((rc = validate(g, ws, s, ws->v_row32))) return rc;
     if (marg_out && nS) fill<unsigned long long>((unsigned long long *)marg_out, nS, 0ull, s);
     if (per_snapshot_out) fill<uint32_t>(per_snapshot_out, R, 0u, s);
@@ -4120,7 +4171,7 @@ extern "C" int im_transpose(const im_graph *g, uint32_t *in_row_ptr, uint32_t *i
     if (!ws || !in_row_ptr || (g->m && (!in_col || !in2out)))
         return im_fail(IM_EINVAL, "null workspace or output");
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = ws_reserve(ws, g->n, g->m, 1, 0, g->n))) return rc;
+    if ((rc = with_room(ws, [&] { return ws_reserve(ws, g->n, g->m, 1, 0, g->n); }))) return rc;
     if ((rc = validate(g, ws, s, ws->row32))) return rc;
     build_reverse(g, ws, s);
     HIPCHK(hipMemcpyAsync(in_row_ptr, ws->in_row, ((uint64_t)g->n + 1) * sizeof(uint32_t),
@@ -4539,8 +4590,10 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     if (K && !need_out) return im_fail(IM_EINVAL, "null seeds or gains output");
     const uint32_t W = (Rmax + 63) / 64;
     ws->batch.count = count;  // sizes the per-round key arrays
-    rc = ws_reserve(ws, (uint32_t)N, M, W, kmax, nmax);
-    if (!rc) rc = reserve_batch(ws, count, N, M);
+    rc = with_room(ws, [&] {
+        const int r = ws_reserve(ws, (uint32_t)N, M, W, kmax, nmax);
+        return r ? r : reserve_batch(ws, count, N, M);
+    });
     if (!rc) {
         for (int d = 0; d < 2; d++) reserve_sparse(ws, d, (uint32_t)N, M, Rmax);
         reserve_rev(ws, pairs, N * W, W, ws->sp_on[0] && ws->sp_on[1]);

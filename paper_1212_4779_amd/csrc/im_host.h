@@ -26,3 +26,5 @@ int und_pair_ids(const im_graph *g, const uint32_t *row32, uint32_t *pair, im_wo
 UndState **im_ws_und(im_workspace *ws);              // im.hip
 int im_ws_validate(const im_graph *g, im_workspace *ws, hipStream_t s, uint32_t *row32);
 void im_ws_set_last_stream(im_workspace *ws, hipStream_t s);
+// frees what earlier calls keep on the workspace but could do without
+void im_ws_give_back(im_workspace *ws);

@@ -610,18 +610,35 @@ extern "C" int im_select_undirected(const im_graph *g, uint32_t R, uint32_t k, u
     if (k && (!seeds_out || !gains_out)) return im_fail(IM_EINVAL, "null seeds or gains output");
     hipStream_t s = (hipStream_t)stream;
     UndState *st;
-    if ((rc = und_state(ws, &st)) || (rc = reserve_pairs(st, n, g->m))) return rc;
     const uint64_t nR = (uint64_t)n * R;
-    if (nR > st->cap_nR || !st->lab) {
-        if ((rc = ualloc(&st->lab, nR)) || (rc = ualloc(&st->cnt, nR)) || (rc = ualloc(&st->rk, nR)) ||
-            (rc = ualloc(&st->start, nR)) || (rc = ualloc(&st->mem, nR)))
-            return rc;
-        st->cap_nR = nR;
+    auto reserve = [&]() -> int {
+        int r;
+        if ((r = und_state(ws, &st)) || (r = reserve_pairs(st, n, g->m))) return r;
+        if (nR > st->cap_nR || !st->lab) {
+            st->cap_nR = 0;
+            if ((r = ualloc(&st->lab, nR)) || (r = ualloc(&st->cnt, nR)) || (r = ualloc(&st->rk, nR)) ||
+                (r = ualloc(&st->start, nR)) || (r = ualloc(&st->mem, nR)))
+                return r;
+            st->cap_nR = nR;
+        }
+        if (!st->cursor && (r = ualloc(&st->cursor, IM_R_MAX))) return r;
+        if (k + 1 > st->cap_k || !st->ukeys) {
+            if ((r = ualloc(&st->ukeys, (uint64_t)k + 1))) return r;
+            st->cap_k = k + 1;
+        }
+        return IM_OK;
+    };
+    if ((rc = reserve()) == IM_ENOMEM) {
+        im_ws_give_back(ws);
+        rc = reserve();
     }
-    if (!st->cursor && (rc = ualloc(&st->cursor, IM_R_MAX))) return rc;
-    if (k + 1 > st->cap_k || !st->ukeys) {
-        if ((rc = ualloc(&st->ukeys, (uint64_t)k + 1))) return rc;
-        st->cap_k = k + 1;
+    if (rc) {
+        // (nothing of it is used again)
+        if (UndState *u = *im_ws_und(ws)) {
+            u->cap_slots = u->cap_m = u->cap_nR = 0;
+            u->cap_n = u->cap_k = 0;
+        }
+        return rc;
     }
     if ((rc = im_ws_validate(g, ws, s, st->row32))) return rc;
     if ((rc = match_pairs(g, st, nullptr, s))) return rc;
