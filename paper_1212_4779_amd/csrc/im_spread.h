@@ -59,8 +59,7 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
 {
     extern __shared__ uint32_t lds_bits[];   // [ceil(n / 32)] unless a.bits
     __shared__ uint32_t q[SPR_Q], ex[NT], rs[NT], wsum[NT / 64 + 1], cnt;
-    // (64 bits: a workgroup adds up n times its share of R, up to 2^20)
-    __shared__ unsigned long long acc[SPR_ACC];
+    __shared__ uint32_t acc[SPR_ACC];
     const uint32_t tid = threadIdx.x, words = (a.n + 31) / 32;
     uint32_t *bits = a.bits ? a.bits + (uint64_t)blockIdx.x * words : lds_bits;
     uint32_t *queue = a.queue + (uint64_t)blockIdx.x * a.n;
@@ -123,9 +122,15 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
                 }
                 head = end;
             }
-            if (tid == 0 && a.marg && head != before) {
-                if (sum_here) acc[g0] += head - before;   // (marginals: one seed per search)
-                else atomicAdd(&a.marg[g0], (unsigned long long)(head - before));
+            if (tid == 0 && a.marg && head != before) {   // (marginals: one seed per search)
+                unsigned long long sum = head - before;
+                if (sum_here) {
+                    // 32 bits (in 64 the workgroup's LDS is larger and two wavefronts fewer fit a CU
+                    // on small graphs): what does not fit goes out, as a share can be n R
+                    sum += acc[g0];
+                    acc[g0] = sum >> 32 ? 0u : (uint32_t)sum;
+                }
+                if (!sum_here || sum >> 32) atomicAdd(&a.marg[g0], sum);
             }
         }
         if (tid == 0 && a.per_snapshot) a.per_snapshot[r] = head;
@@ -135,5 +140,5 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
     }
     if (sum_here)
         for (uint32_t i = tid; i < a.nS; i += NT)
-            if (acc[i]) atomicAdd(&a.marg[i], acc[i]);
+            if (acc[i]) atomicAdd(&a.marg[i], (unsigned long long)acc[i]);
 }
