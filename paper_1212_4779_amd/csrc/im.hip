@@ -3982,17 +3982,31 @@ static int select_lazy(const im_graph *g, uint32_t R, uint32_t k, uint32_t B, co
 // ---------------------------------------------------------------------------
 constexpr uint64_t SPR_BUDGET = 4ull << 30;      // queues (and visit bits) of the workgroups
 constexpr uint32_t SPR_LDS_NODES = 1u << 18;     // visit bits in LDS up to this many nodes (32 KB)
-// Lanes per snapshot. A snapshot of a small graph fills a wavefront at best
-// (its searches are a chain of levels), and one wavefront needs no workgroup
-// barrier: 15,000 nodes, 50 seeds: 0.53 ms at R = 300 and 2.06 ms at 20,000,
-// against 0.61 / 4.8 with 128 lanes and 0.64 / 19.7 with 512. Larger graphs
-// have hubs whose arcs one wavefront would take long to draw: 60,000 nodes,
-// weighted cascade: R = 500 3.9 / 2.6 / 1.7 / 1.25 ms with 64 / 128 / 256 / 512
-// lanes, R = 2,000 4.2 / 2.8 / 2.9 / 4.1 ms; past the LDS visit bits, 10^6
-// nodes: R = 256 5.9 / 3.5 / 2.1 / 1.4 ms, R = 4,096 23 / 13.7 / 8.5 / 10.1 ms.
-static int spread_lanes(uint32_t n, uint32_t R)
+// Lanes per snapshot. A snapshot of a small sparse graph fills a wavefront at
+// best (its searches are a chain of levels), and one wavefront needs no workgroup
+// barrier: 15,000 nodes, 50 seeds: 0.53 ms at R = 300 and 1.98 at 20,000,
+// against 0.61 / 4.8 with 128 lanes and 0.64 / 19.7 with 512. Graphs of more
+// arcs have levels that one wavefront would take long to draw, and as long as
+// the snapshots leave the device room, wide workgroups share them; with thousands
+// of snapshots the device is full either way. ms with 64 / 128 / 256 / 512 lanes:
+//   16,000 nodes, 1.9*10^5 arcs, p = 0.05: R = 300      0.62  0.60  0.57  0.56
+//                                          R = 2,000    0.67  0.64  0.95  1.77
+//                                          R = 20,000   2.9   4.8   8.2   16.3
+//   16,000 nodes, 6.4*10^5 arcs, p = 0.1:  R = 8        4.6   2.6   1.5   0.9
+//                                          R = 1,000    5.1   3.0   1.8   1.8
+//                                          R = 4,000    6.5   6.3   6.6   7.1
+//   16,000 nodes, 2*10^7 arcs, p = 0.05:   R = 8        135   74    40    22
+//                                          R = 1,000    148   84    50    53
+//   60,000 nodes, weighted cascade:        R = 500      2.8   2.1   1.7   1.5
+//                                          R = 2,000    3.2   2.4   3.0   5.0
+//   10^6 nodes (no LDS visit bits):        R = 256      5.9   3.5   2.1   1.4
+//                                          R = 4,096    23    13.7  8.5   10.1
+// (Masks drawn 64 snapshots at a time, one search per word: 36 to 63 ms on the
+// graph of 2*10^7 arcs. They are ahead on small graphs whose every arc is drawn
+// anyway: 4,000 nodes, 4*10^5 arcs, p = 0.2, R = 20,000: 13.5 against 21.4.)
+static int spread_lanes(uint32_t n, uint64_t m, uint32_t R)
 {
-    if (n <= 16384u) return 64;
+    if (n <= 16384u && (m < (1u << 17) || R >= 8192u)) return 64;
     if (R < 1024u) return 512;
     return n <= SPR_LDS_NODES ? 128 : 256;
 }
@@ -4056,7 +4070,7 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
         for (uint32_t i = 0; i < nS; i++)
             if (hs[i] >= n) return im_fail(IM_EINVAL, "S[%u] = %u is not a node (n = %u)", i, hs[i], n);
     }
-    const int lanes = spread_lanes(n, R);
+    const int lanes = spread_lanes(n, m, R);
     const unsigned lds = n > SPR_LDS_NODES ? 0u : (n + 31) / 32 * 4u;
     const unsigned groups = lanes == 64 ? spread_groups<64>(ws, n, R, lds)
                             : lanes == 128 ? spread_groups<128>(ws, n, R, lds)
