@@ -4011,30 +4011,36 @@ static int spread_lanes(uint32_t n, uint64_t m, uint32_t R)
     return n <= SPR_LDS_NODES ? 128 : 256;
 }
 
-static int reserve_spread(im_workspace *ws, uint32_t n, uint64_t m, uint32_t groups)
+// Buffers of `groups` workgroups, fewer where the device has no room for all,
+// and the arcs' records (16 bytes each), which *records says are there: without
+// room for them a draw makes its own (10^6 nodes, 3*10^7 arcs, R = 256: 2.7
+// against 3.5 ms).
+static int reserve_spread(im_workspace *ws, uint32_t n, uint64_t m, unsigned *groups, bool *records)
 {
     int rc;
-    const uint64_t nq = (uint64_t)n * groups;
-    const uint64_t nb = n > SPR_LDS_NODES ? (uint64_t)((n + 31) / 32) * groups : 0;
+    const uint64_t words = n > SPR_LDS_NODES ? ((uint64_t)n + 31) / 32 : 0;
     if (n > ws->cap_sp_n || !ws->v_row32) {
         if ((rc = dalloc(&ws->v_row32, (uint64_t)n + 1))) return rc;
         ws->cap_sp_n = n;
     }
+    if (n * (uint64_t)*groups > ws->cap_sp_q || words * *groups > ws->cap_sp_b || !ws->v_queue) {
+        ws->cap_sp_q = ws->cap_sp_b = 0;
+        dfree(ws->v_queue); dfree(ws->v_bits);
+        while (*groups > 1 && !room_for((n + words) * 4 * *groups)) *groups = (*groups + 1) / 2;
+        if ((rc = dalloc(&ws->v_queue, n * (uint64_t)*groups))) return rc;
+        if (words) {
+            if ((rc = dalloc(&ws->v_bits, words * *groups))) return rc;
+            HIPCHK(hipMemset(ws->v_bits, 0, words * *groups * sizeof(uint32_t)));
+        }
+        ws->cap_sp_q = n * (uint64_t)*groups;
+        ws->cap_sp_b = words * *groups;
+    }
     if (m > ws->cap_sp_m || !ws->v_coin) {
-        if ((rc = dalloc(&ws->v_coin, m))) return rc;
-        ws->cap_sp_m = m;
+        ws->cap_sp_m = 0;
+        dfree(ws->v_coin);
+        if (room_for(16 * m) && dalloc(&ws->v_coin, m) == IM_OK) ws->cap_sp_m = m;
     }
-    if (nq > ws->cap_sp_q || !ws->v_queue) {
-        ws->cap_sp_q = 0;
-        if ((rc = dalloc(&ws->v_queue, nq))) return rc;
-        ws->cap_sp_q = nq;
-    }
-    if (nb > ws->cap_sp_b) {
-        ws->cap_sp_b = 0;
-        if ((rc = dalloc(&ws->v_bits, nb))) return rc;
-        HIPCHK(hipMemset(ws->v_bits, 0, nb * sizeof(uint32_t)));
-        ws->cap_sp_b = nb;
-    }
+    *records = ws->v_coin != nullptr;
     return IM_OK;
 }
 
@@ -4042,7 +4048,7 @@ template <int NT>
 static unsigned spread_groups(const im_workspace *ws, uint32_t n, uint32_t R, unsigned lds)
 {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_spread<NT>, NT, lds) != hipSuccess || b < 1) b = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_spread<NT, true>, NT, lds) != hipSuccess || b < 1) b = 1;
     const uint64_t fit = SPR_BUDGET / (4ull * n + 4ull * ((n + 31) / 32) + 1);
     return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)b * ws->num_cu, R, fit}));
 }
@@ -4072,28 +4078,30 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
     }
     const int lanes = spread_lanes(n, m, R);
     const unsigned lds = n > SPR_LDS_NODES ? 0u : (n + 31) / 32 * 4u;
-    const unsigned groups = lanes == 64 ? spread_groups<64>(ws, n, R, lds)
+    unsigned groups = lanes == 64 ? spread_groups<64>(ws, n, R, lds)
                             : lanes == 128 ? spread_groups<128>(ws, n, R, lds)
                             : lanes == 256 ? spread_groups<256>(ws, n, R, lds)
                                            : spread_groups<512>(ws, n, R, lds);
-    if ((rc = with_room(ws, [&] { return reserve_spread(ws, n, m, groups); }))) return rc;
+    bool records = false;
+    if ((rc = with_room(ws, [&] { return reserve_spread(ws, n, m, &groups, &records); }))) return rc;
     if ((rc = validate(g, ws, s, ws->v_row32))) return rc;
     if (marg_out && nS) fill<unsigned long long>((unsigned long long *)marg_out, nS, 0ull, s);
     if (per_snapshot_out) fill<uint32_t>(per_snapshot_out, R, 0u, s);
     if (nS && n) {
-        if (m) k_arc_coins<<<grid_for(m, 256), 256, 0, s>>>(g->col, g->prob, m, seed, ws->v_coin);
+        if (m && records) k_arc_coins<<<grid_for(m, 256), 256, 0, s>>>(g->col, g->prob, m, seed, ws->v_coin);
         SpreadArgs a;
-        a.row = ws->v_row32; a.coin = ws->v_coin;
+        a.row = ws->v_row32; a.coin = ws->v_coin; a.col = g->col; a.prob = g->prob; a.seed = seed;
         a.n = n; a.R = R; a.S = S; a.nS = nS;
         a.group = marg_out ? 1u : nS;
         a.queue = ws->v_queue;
         a.bits = n > SPR_LDS_NODES ? ws->v_bits : nullptr;
         a.marg = (unsigned long long *)marg_out;
         a.per_snapshot = per_snapshot_out;
-        if (lanes == 64) k_spread<64><<<groups, 64, lds, s>>>(a);
-        else if (lanes == 128) k_spread<128><<<groups, 128, lds, s>>>(a);
-        else if (lanes == 256) k_spread<256><<<groups, 256, lds, s>>>(a);
-        else k_spread<512><<<groups, 512, lds, s>>>(a);
+        if (!records) k_spread<512, false><<<groups, 512, lds, s>>>(a);
+        else if (lanes == 64) k_spread<64, true><<<groups, 64, lds, s>>>(a);
+        else if (lanes == 128) k_spread<128, true><<<groups, 128, lds, s>>>(a);
+        else if (lanes == 256) k_spread<256, true><<<groups, 256, lds, s>>>(a);
+        else k_spread<512, true><<<groups, 512, lds, s>>>(a);
     }
     HIPCHK(hipGetLastError());
     ws->last_stream = s;

@@ -25,22 +25,29 @@ struct __align__(16) ArcCoin {
     uint32_t last, head;
 };
 
+__device__ __forceinline__ ArcCoin arc_coin(const uint32_t *col, const float *prob, uint64_t seed, uint64_t e)
+{
+    const uint64_t thr = (uint64_t)((double)prob[e] * 4294967296.0);   // 0 .. 2^32
+    ArcCoin c;
+    c.key = sm64_finalise(seed + (e + 1ull) * IM_GOLDEN);
+    c.last = (uint32_t)(thr - 1ull);
+    c.head = thr ? col[e] : IM_EMPTY;
+    return c;
+}
+
 __global__ __launch_bounds__(256) void k_arc_coins(const uint32_t *col, const float *prob, uint64_t m,
                                                    uint64_t seed, ArcCoin *coin)
 {
-    for (uint64_t e = blockIdx.x * 256ull + threadIdx.x; e < m; e += (uint64_t)gridDim.x * 256u) {
-        const uint64_t thr = (uint64_t)((double)prob[e] * 4294967296.0);   // 0 .. 2^32
-        ArcCoin c;
-        c.key = sm64_finalise(seed + (e + 1ull) * IM_GOLDEN);
-        c.last = (uint32_t)(thr - 1ull);
-        c.head = thr ? col[e] : IM_EMPTY;
-        coin[e] = c;
-    }
+    for (uint64_t e = blockIdx.x * 256ull + threadIdx.x; e < m; e += (uint64_t)gridDim.x * 256u)
+        coin[e] = arc_coin(col, prob, seed, e);
 }
 
 struct SpreadArgs {
     const uint32_t *row;
-    const ArcCoin *coin;
+    const ArcCoin *coin;         // a record per arc; without (RECORDS false) it is made for each draw
+    const uint32_t *col;
+    const float *prob;
+    uint64_t seed;
     uint32_t n, R;
     const uint32_t *S;
     uint32_t nS, group;          // seeds per search
@@ -54,7 +61,7 @@ constexpr int SPR_Q = 1024;      // queue entries kept in LDS as well
 constexpr int SPR_ACC = 256;     // marginals added up per workgroup up to this many seeds
 constexpr int SPR_U = 4;         // arcs in flight per lane
 
-template <int NT>
+template <int NT, bool RECORDS>
 __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
 {
     extern __shared__ uint32_t lds_bits[];   // [ceil(n / 32)] unless a.bits
@@ -109,7 +116,8 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
                             c[u].key = 0; c[u].last = 0;
                             if (j < total && j >= j0) {
                                 const int k = upper_index<NT>(ex, j);
-                                c[u] = a.coin[rs[k] + (j - ex[k])];
+                                const uint32_t e = rs[k] + (j - ex[k]);
+                                c[u] = RECORDS ? a.coin[e] : arc_coin(a.col, a.prob, a.seed, e);
                             }
                         }
 #pragma unroll
