@@ -31,6 +31,12 @@ constexpr int CB_WAVES = 16;     // most wavefronts (bits at a time) per workgro
 constexpr int CB_Q = 64;         // queue entries per wavefront kept in LDS as well
 constexpr uint32_t CB_LIST = 4096;   // tables: words of a task's marks that are listed
 constexpr int CB_TASKS = 8;      // most tasks in progress per workgroup
+// Most arcs without live lists that a wavefront reads for one snapshot: a hub whose
+// lists did not fit has its arcs' masks read once per snapshot here and once
+// per word in the dense tier, which takes its task (a star of 200,000 arcs, p =
+// 0.05, R = 256: 46 ms here, 3.2 there; bounds from 1,024 to 65,536 arcs measure
+// the same on weighted-cascade graphs, 1,024 costs supercritical ones 4 %)
+constexpr uint32_t CB_SCAN = 4096;
 constexpr uint32_t CB_PROBE = 8; // searches after which a task's snapshots are compared
 constexpr int CB_CS1 = 512, CB_CS2 = 4096;  // table entries per wavefront: first launch, second
 
@@ -246,6 +252,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                             if (p < CB_LIST) list[p] = i >> 5;
                         }
                     }
+                    if (sp.kind == 2 && sp.len > CB_SCAN) { tk.over = 1; sp.len = 0; }
                     wave_expand(L.B, a.g, w, b, sp, visit, arcs);
                 }
                 head = end;
