@@ -1300,8 +1300,9 @@ constexpr int T1_NT = 256, T1_T = 4, T1_CS = 256, T1_LIM = 192, T1_U = 4;
 constexpr int T2_NT = 256, T2_U = 8;
 constexpr int T2W_NT = 1024;   // the wide variant: more lanes per task
 constexpr int T2S_NT = 64;     // the narrow variant: more tasks at once (long, thin searches)
-// per-phase device counters: grab0, n1, grab1, n2, grab2
-constexpr int PH_CTRS = 9;
+// per-phase device counters: queue lengths and task counters of the launches,
+// and the two of the probes (9, 10: im_bits.h)
+constexpr int PH_CTRS = 11;
 
 // ---------------------------------------------------------------------------
 // workspace
@@ -2173,6 +2174,7 @@ static bool cnt_bits(const BfsArgs &t, im_workspace *ws, uint32_t *ctr, int ph, 
     a.out_q = ws->ovf_q; a.out_n = ctr + 5; a.grab = ctr + 4;   // (ovf_q: tier 1 is done with it)
     a.queue = ws->cb_queue; a.any = ws->cb_any; a.nmax = ws->slots_n; a.tasks = ws->cb_tasks;
     a.list = ws->cb_table ? ws->cb_queue + (uint64_t)ws->cb_groups * CB_TABLE_WAVES * CB_CS2 : nullptr;
+    a.judged = ctr + 9;
     a.stats = t.stats;
     PhaseTimer pt(ws, ph, s);
     const unsigned lds = cb_lds(ws, ws->slots_n);

@@ -21,7 +21,19 @@
 // Where the snapshots do share their nodes (supercritical graphs), one search
 // of the word does less: the task is handed to the dense tier if its first
 // CB_PROBE searches reached more than twice the nodes that the task had marked
-// by then (the sources aside).
+// by then (the sources aside). On a graph whose tasks nearly all share three
+// quarters and more, the probes themselves cost up to one and a half times the
+// dense tier: once CB_JUDGED tasks were judged (every fourth is) and seven eighths
+// of them shared that much, only one in 16 is still probed, as a sample, and the
+// others go on without (ms of this step; probing all -> sampling; the dense tier alone):
+//   20,000 nodes, 2*10^5 arcs, p = 1, R = 64      445 -> 231; 178
+//   8,000 nodes, 3.2*10^5 arcs, p = 0.6, R = 64   227 -> 166; 139
+//   8,000 nodes, 8*10^4 arcs, p = 0.6 / 0.2       118 -> 100; 85 / 72 -> 73; 113
+//   weighted cascade, 60,000 nodes, R = 128       18.7 -> 18.7; 61
+// (Two counter loads before every task instead of the sums of every fourth judged:
+// 210, 156 and 95 ms, but 2 to 3 % on small weighted-cascade graphs.)
+// (Judged at twice instead of six times the marks, p = 0.05 on the denser graph
+// took 144 ms instead of 119.)
 // Measured (tier 2 of the initial counts): see cnt_bits.
 #pragma once
 
@@ -38,6 +50,8 @@ constexpr int CB_TASKS = 8;      // most tasks in progress per workgroup
 // the same on weighted-cascade graphs, 1,024 costs supercritical ones 4 %)
 constexpr uint32_t CB_SCAN = 4096;
 constexpr uint32_t CB_PROBE = 8; // searches after which a task's snapshots are compared
+constexpr uint32_t CB_SHARED = 6;    // ... that reached this many times the marks: shared
+constexpr uint32_t CB_JUDGED = 32;
 constexpr int CB_CS1 = 512, CB_CS2 = 4096;  // table entries per wavefront: first launch, second
 
 struct BitsArgs {
@@ -48,6 +62,7 @@ struct BitsArgs {
     const uint32_t *in_q, *in_n;
     uint32_t *out_q, *out_n;     // tasks for the dense tier
     uint32_t *grab;
+    uint32_t *judged;            // tasks judged by their probe, and those that shared (zero before)
     uint32_t *queue;             // [workgroups][wavefronts][nmax] (bitmaps) or [..][CS] (tables)
     uint32_t *any;               // tables: [workgroups][tasks][words of the largest instance], zero at rest
     uint32_t *list;              // tables: [workgroups][tasks][CB_LIST]
@@ -131,7 +146,7 @@ struct WaveLds {
 // A task in progress. Its number among the workgroup's tasks is `ord`: free is
 // the number that may take the place next, open that of the task in it plus one.
 struct CntTask {
-    uint32_t free, open, task, done, over, sum, reached, words;
+    uint32_t free, open, task, done, over, judge, sum, reached, words;
     unsigned long long relax, trav, arcs;
 };
 
@@ -149,7 +164,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     // bitmaps: [wavefronts + tasks][words of the largest instance]; tables:
     // [wavefronts][CS] nodes; then [wavefronts] of WaveLds
     extern __shared__ uint32_t maps[];
-    __shared__ uint32_t cnt[CB_WAVES], s_item;
+    __shared__ uint32_t cnt[CB_WAVES], s_item, s_skip;
     __shared__ CntTask T[CB_TASKS];
     __shared__ unsigned long long red[CB_WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, nw = blockDim.x >> 6;
@@ -165,10 +180,10 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     WaveLds &L = ((WaveLds *)(maps + nmaps))[wv];
     for (uint32_t i = tid; i < nmaps; i += blockDim.x)
         maps[i] = TABLE ? IM_EMPTY : 0u;
-    if (tid == 0) s_item = 0;
+    if (tid == 0) { s_item = 0; s_skip = 0; }
     if (tid < CB_TASKS) {
         CntTask &t = T[tid];
-        t.free = tid; t.open = 0; t.task = 0; t.done = 0; t.over = 0; t.sum = 0; t.reached = 0; t.words = 0;
+        t.free = tid; t.open = 0; t.task = 0; t.done = 0; t.over = 0; t.judge = 0; t.sum = 0; t.reached = 0; t.words = 0;
         t.relax = 0; t.trav = 0; t.arcs = 0;
     }
     // lane 0: of the tasks that this wavefront finished
@@ -191,6 +206,8 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
             if (lane == 0) {
                 const uint32_t i = ord == 0 ? blockIdx.x : gridDim.x + atomicAdd(a.grab, 1u);
                 tk.task = i < nt ? a.in_q[i] : IM_EMPTY;
+                tk.judge = (i & 3u) == 0;
+                if ((i & 15u) != 0 && peek(&s_skip)) { tk.judge = 0; tk.over = 1; }
                 post(&tk.open, ord + 1);
             }
         }
@@ -279,7 +296,16 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
             done = __hip_atomic_fetch_add(&tk.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) + 1;
         done = __builtin_amdgcn_readfirstlane(done);
         // the first searches: do the snapshots share their nodes?
-        if (done == CB_PROBE && lane == 0 && tk.sum > 2u * tk.reached + 64u) post(&tk.over, 1u);
+        if (done == CB_PROBE && lane == 0) {
+            const uint32_t sum = tk.sum, reached = tk.reached;
+            if (sum > 2u * reached + 64u) post(&tk.over, 1u);
+            if (tk.judge) {
+                const uint32_t judged = atomicAdd(&a.judged[0], 1u) + 1;
+                const uint32_t yes = sum > CB_SHARED * reached ? 1u : 0u;
+                const uint32_t shared = atomicAdd(&a.judged[1], yes) + yes;
+                post(&s_skip, judged >= CB_JUDGED && shared >= judged / 8 * 7 ? 1u : 0u);
+            }
+        }
         if (done < 64) continue;
         // (marks in memory can be far more than the task reached: clearing the
         // words that it touched, not n / 32, took the first launch on 10^6 nodes
