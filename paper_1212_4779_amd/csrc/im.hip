@@ -88,7 +88,26 @@ static void fill(Tv *p, uint64_t cnt, Tv v, hipStream_t s)
 // ---------------------------------------------------------------------------
 // A1: validation and reverse CSR
 // ---------------------------------------------------------------------------
-enum { ERR_ROW0 = 1, ERR_ROWN = 2, ERR_ROWDEC = 4, ERR_ROWBIG = 8, ERR_COL = 16, ERR_PROB = 32 };
+enum { ERR_ROW0 = 1, ERR_ROWN = 2, ERR_ROWDEC = 4, ERR_ROWBIG = 8, ERR_COL = 16, ERR_PROB = 32,
+       SEEN_COIN = 64 };   // (no error: an arc below P_SURE)
+
+// Graphs without an arc below this probability: a word's 64 snapshots are nearly
+// the same, and the searches by word, which take them together, do less than
+// those by snapshot. ms per selection, by snapshot and by word: 8,000 nodes of
+// ten arcs, R = 64: p = 0.8 134 and 119 (the rounds alone 46 and 55), 0.9 117 and
+// 97 (48 and 44), 1 96 and 62; 20,000 nodes of three arcs, R = 256: p = 0.9 1,650
+// and 1,295, p = 1 1,326 and 360.
+constexpr float P_SURE = 0.9f;
+
+// flags of a wavefront's lanes into *err, where they are not there yet: all
+// workgroups of a launch see the same few
+__device__ __forceinline__ void wave_flags(uint32_t *err, uint32_t e)
+{
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) e |= __shfl_xor(e, d, 64);
+    if ((threadIdx.x & 63u) == 0 && (e & ~__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+        atomicOr(err, e);
+}
 
 __global__ void k_validate(const uint64_t *row_ptr, const uint32_t *col, const float *prob,
                            uint32_t n, uint64_t m, uint32_t *err, uint32_t *row32)
@@ -109,9 +128,10 @@ __global__ void k_validate(const uint64_t *row_ptr, const uint32_t *col, const f
             if (col[i] >= n) e |= ERR_COL;
             float p = prob[i];
             if (!(p >= 0.0f && p <= 1.0f)) e |= ERR_PROB;
+            if (p < P_SURE) e |= SEEN_COIN;
         }
     }
-    if (e) atomicOr(err, e);
+    wave_flags(err, e);
 }
 
 // 32-bit copy of the row offsets (a plan's replays re-read row_ptr with this)
@@ -265,10 +285,11 @@ __global__ void k_batch_merge(const InstDesc *desc, uint32_t *err, uint32_t *row
             mcol[d.arc_off + j] = d.node_off + c;
             const float p = d.prob[j];
             if (!(p >= 0.0f && p <= 1.0f)) e |= ERR_PROB;
+            if (p < P_SURE) e |= SEEN_COIN;
             mprob[d.arc_off + j] = p;
         }
     }
-    if (e) atomicOr(err, e);
+    wave_flags(err, e);
 }
 
 constexpr int SCAN_NT = 256, SCAN_IPT = 8, SCAN_TILE = SCAN_NT * SCAN_IPT;
@@ -1334,6 +1355,7 @@ struct im_workspace {
     uint32_t *plist = nullptr, *mlist = nullptr;  // [W][n]
     // rounds by snapshot (im_rev.h); rv_on: this call's buffers are in place
     bool rv_on = false;
+    bool sure = false;   // no arc of this call's graph is below P_SURE
     uint64_t cap_rv_src = 0, cap_rv_bins = 0, cap_rv_nW = 0;
     uint32_t *rv_src = nullptr, *rv_q = nullptr, *rv_stamp = nullptr;
     uint2 *rv_tasks = nullptr;
@@ -1862,12 +1884,14 @@ static void reserve_sparse(im_workspace *ws, int d, uint32_t n, uint64_t m, uint
 // past 2^32 pairs the source positions do not fit 32 bits, a launch takes
 // fewer than 2^32 lanes (the forward step: FWS_NT per instance and snapshot of
 // a batch), and the affected-set recompute takes the newly covered nodes by
-// word: such calls, and those whose buffers do not fit the device, run the
-// rounds by word (k_forward_coop and the three tiers of im_bfs.h).
-static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W, bool lists)
+// word: such calls, those whose buffers do not fit the device, and graphs
+// without an arc below P_SURE run the rounds by word (k_forward_coop and the
+// three tiers of im_bfs.h).
+static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W, bool lists,
+                        uint32_t count = 1)
 {
     ws->rv_on = false;
-    const uint64_t bins = (uint64_t)ws->batch.count * W * 64;
+    const uint64_t bins = (uint64_t)count * W * 64;
     if (!lists || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins * FWS_NT >= (1ull << 32)) return;
     if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins || nW > ws->cap_rv_nW) {
         const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
@@ -1946,6 +1970,7 @@ static int validate(const im_graph *g, im_workspace *ws, hipStream_t s, uint32_t
     if (e & (ERR_ROWDEC | ERR_ROWBIG)) return im_fail(IM_EINVAL, "row_ptr is not non-decreasing within [0, m]");
     if (e & ERR_COL) return im_fail(IM_EINVAL, "col entry >= n");
     if (e & ERR_PROB) return im_fail(IM_EINVAL, "prob outside [0, 1] or NaN");
+    ws->sure = g->m && !(e & SEEN_COIN);
     return IM_OK;
 }
 
@@ -2758,6 +2783,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
     if (ws->lt_on) return IM_OK;
     reserve_sparse(ws, 0, g->n, g->m, R);
     if (need == PREP_REVERSE) reserve_sparse(ws, 1, g->n, g->m, R);
+    if (ws->sure) return IM_OK;
     if (rounds)
         reserve_rev(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64), (R + 63) / 64,
                     ws->sp_on[0] && ws->sp_on[1]);
@@ -4618,11 +4644,6 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
         const int r = ws_reserve(ws, (uint32_t)N, M, W, kmax, nmax);
         return r ? r : reserve_batch(ws, count, N, M);
     });
-    if (!rc) {
-        for (int d = 0; d < 2; d++) reserve_sparse(ws, d, (uint32_t)N, M, Rmax);
-        reserve_rev(ws, pairs, N * W, W, ws->sp_on[0] && ws->sp_on[1]);
-        reserve_bits(ws, nmax);
-    }
     ws->batch.count = 1;
     if (rc) return rc;
     // per-instance tables, staged in pinned memory
@@ -4663,8 +4684,14 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(ws->host_err, ws->err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (*ws->host_err)
+    ws->sure = M && !(*ws->host_err & SEEN_COIN);
+    if (*ws->host_err & ~SEEN_COIN)
         return im_fail(IM_EINVAL, "a batch instance failed validation (flags 0x%x)", *ws->host_err);
+    for (int d = 0; d < 2; d++) reserve_sparse(ws, d, (uint32_t)N, M, Rmax);
+    if (!ws->sure) {
+        reserve_rev(ws, pairs, N * W, W, ws->sp_on[0] && ws->sp_on[1], count);
+        reserve_bits(ws, nmax);
+    }
     Batch b;
     b.count = count;
     b.node_inst = ws->b_node_inst;
