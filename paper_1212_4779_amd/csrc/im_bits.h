@@ -30,8 +30,8 @@
 //   8,000 nodes, 3.2*10^5 arcs, p = 0.6, R = 64   227 -> 166; 139
 //   8,000 nodes, 8*10^4 arcs, p = 0.6 / 0.2       118 -> 100; 85 / 72 -> 73; 113
 //   weighted cascade, 60,000 nodes, R = 128       18.7 -> 18.7; 61
-// (Two counter loads before every task instead of the sums of every fourth judged:
-// 210, 156 and 95 ms, but 2 to 3 % on small weighted-cascade graphs.)
+// (Two counter loads per task, before it or at its probe, instead of the sums of
+// every fourth judged: 210, 156 and 95 ms, but 2 to 3 % on weighted-cascade graphs.)
 // (Judged at twice instead of six times the marks, p = 0.05 on the denser graph
 // took 144 ms instead of 119.)
 // Measured (tier 2 of the initial counts): see cnt_bits.
@@ -299,7 +299,8 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
         if (done == CB_PROBE && lane == 0) {
             const uint32_t sum = tk.sum, reached = tk.reached;
             if (sum > 2u * reached + 64u) post(&tk.over, 1u);
-            if (tk.judge) {
+            // (of words with few snapshots the probe is over before they can share)
+            if (tk.judge && __popcll(valid) >= 32) {
                 const uint32_t judged = atomicAdd(&a.judged[0], 1u) + 1;
                 const uint32_t yes = sum > CB_SHARED * reached ? 1u : 0u;
                 const uint32_t shared = atomicAdd(&a.judged[1], yes) + yes;
