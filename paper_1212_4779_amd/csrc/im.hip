@@ -1880,19 +1880,20 @@ static void reserve_sparse(im_workspace *ws, int d, uint32_t n, uint64_t m, uint
 
 // Buffers of the rounds by snapshot: `pairs` (node, snapshot) pairs (n R,
 // summed over a batch's instances) can be newly covered in one round. Without
-// the sparse lists (`lists`: of the directions searched) the searches would read every arc's masks for a single bit,
+// the sparse lists the searches would read every arc's masks for a single bit,
 // past 2^32 pairs the source positions do not fit 32 bits, a launch takes
 // fewer than 2^32 lanes (the forward step: FWS_NT per instance and snapshot of
-// a batch), and the affected-set recompute takes the newly covered nodes by
-// word: such calls, those whose buffers do not fit the device, and graphs
-// without an arc below P_SURE run the rounds by word (k_forward_coop and the
-// three tiers of im_bfs.h).
+// a batch), and the affected-set recompute of a single graph's rounds takes the
+// newly covered nodes by word: such calls, those whose buffers do not fit the
+// device, and graphs without an arc below P_SURE run the rounds by word
+// (k_forward_coop and the three tiers of im_bfs.h). lists: those of the
+// directions searched are in place and the recompute is off.
 static void reserve_rev(im_workspace *ws, uint64_t pairs, uint64_t nW, uint32_t W, bool lists,
                         uint32_t count = 1)
 {
     ws->rv_on = false;
     const uint64_t bins = (uint64_t)count * W * 64;
-    if (!lists || ws->aff_gain || t_arena || pairs >= 0xFFFFFFFFull || bins * FWS_NT >= (1ull << 32)) return;
+    if (!lists || t_arena || pairs >= 0xFFFFFFFFull || bins * FWS_NT >= (1ull << 32)) return;
     if (pairs > ws->cap_rv_src || bins > ws->cap_rv_bins || nW > ws->cap_rv_nW) {
         const uint64_t cs = std::max(pairs, ws->cap_rv_src), cb = std::max(bins, ws->cap_rv_bins);
         const uint64_t ct = cs / 64 + cb, cw = std::max(nW, ws->cap_rv_nW);   // (one partial task per bin)
@@ -2786,7 +2787,7 @@ static int check_and_reserve(const im_graph *g, uint32_t R, uint32_t k, im_works
     if (ws->sure) return IM_OK;
     if (rounds)
         reserve_rev(ws, (uint64_t)g->n * R, (uint64_t)g->n * ((R + 63) / 64), (R + 63) / 64,
-                    ws->sp_on[0] && ws->sp_on[1]);
+                    ws->sp_on[0] && ws->sp_on[1] && !ws->aff_gain);
     reserve_bits(ws, g->n);
     return IM_OK;
 }
