@@ -329,12 +329,14 @@ int im_select_batch(const im_instance *inst, uint32_t count, uint32_t *seeds_out
  * then the split of last-tier reverse tasks (IM_OPT_REV_SPLIT 1 or 2) and
  * the tier reverse tasks start on (IM_OPT_REV_FIRST_TIER 0 or 1; the batch
  * tuner times these two as well, on its own trial).
- * im_autotune caches its choice per graph signature (n, m, R and a checksum
- * of col and prob) for the life of the process; a cached choice is applied
+ * im_autotune caches its choice per graph signature (n, m, R, the snapshot
+ * model and a checksum of col and prob) for the life of the process; a cached
+ * choice is applied
  * without timing (out->tried = 0). When the environment variable
  * IM_TUNE_CACHE names a file, choices are also appended to it (one text line
  * per signature) and looked up there on a miss, so that they persist across
- * processes; an unreadable or unwritable file only disables that.
+ * processes; an unreadable or unwritable file only disables that, and lines
+ * written for other engines than this library's are passed over.
  * im_autotune_batch tunes the schedule on the instances it is given (a
  * caller may pass a representative subset of a batch). */
 typedef struct im_tuning {

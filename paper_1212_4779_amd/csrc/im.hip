@@ -4844,15 +4844,25 @@ __global__ void k_signature(const uint32_t *col, const float *prob, uint64_t m,
     if ((threadIdx.x & 63) == 0 && h) atomicAdd(out, h);
 }
 
+// model: how snapshots are drawn (linear threshold 1, pair coins 2), as the
+// choice for one says nothing about another
 struct TuneKey {
     uint64_t n, m, R, sum;
-    bool operator==(const TuneKey &o) const { return n == o.n && m == o.m && R == o.R && sum == o.sum; }
+    int model;
+    bool operator==(const TuneKey &o) const
+    {
+        return n == o.n && m == o.m && R == o.R && sum == o.sum && model == o.model;
+    }
 };
+// The engines that a choice was timed on: lines of others are not taken (an
+// update strategy chosen against rounds by word would turn those by snapshot off)
+constexpr int TUNE_ENGINES = 2;
 static std::vector<std::pair<TuneKey, im_tuning>> g_tune_cache;
 static std::mutex g_tune_mu;   // guards g_tune_cache and the cache file
 
 // The cache file named by IM_TUNE_CACHE (if set): one line per graph
-// signature, "im-tune-4 n m R sum hub tier1 lanes slots coop affected fwd split first ms".
+// signature, "im-tune-4 n m R sum hub tier1 lanes slots coop affected fwd split first ms
+// model engines".
 // Lines that do not parse are ignored; the last line for a key wins.
 static const char *tune_file() { return getenv("IM_TUNE_CACHE"); }
 
@@ -4865,12 +4875,13 @@ static void tune_file_lookup(const TuneKey &key)
     char line[512];
     while (fgets(line, sizeof line, f)) {
         unsigned long long n, m, R, sum, aff;
-        int hub, t1, lanes, slots, coop, fwd, split, first;
+        int hub, t1, lanes, slots, coop, fwd, split, first, model, engines;
         float ms;
-        if (sscanf(line, "im-tune-4 %llu %llu %llu %llu %d %d %d %d %d %llu %d %d %d %f", &n, &m, &R,
-                   &sum, &hub, &t1, &lanes, &slots, &coop, &aff, &fwd, &split, &first, &ms) != 14)
+        if (sscanf(line, "im-tune-4 %llu %llu %llu %llu %d %d %d %d %d %llu %d %d %d %f %d %d", &n, &m, &R,
+                   &sum, &hub, &t1, &lanes, &slots, &coop, &aff, &fwd, &split, &first, &ms, &model,
+                   &engines) != 16 || engines != TUNE_ENGINES)
             continue;
-        const TuneKey k{n, m, R, sum};
+        const TuneKey k{n, m, R, sum, model};
         if (!(k == key)) continue;
         im_tuning t;
         memset(&t, 0, sizeof t);
@@ -4891,10 +4902,11 @@ static void tune_file_append(const TuneKey &k, const im_tuning &t)
     if (!path || !*path) return;
     FILE *f = fopen(path, "a");
     if (!f) return;   // the in-process cache still holds the choice
-    fprintf(f, "im-tune-4 %llu %llu %llu %llu %d %d %d %d %d %llu %d %d %d %.4f\n", (unsigned long long)k.n,
+    fprintf(f, "im-tune-4 %llu %llu %llu %llu %d %d %d %d %d %llu %d %d %d %.4f %d %d\n", (unsigned long long)k.n,
             (unsigned long long)k.m, (unsigned long long)k.R, (unsigned long long)k.sum, t.hub_degree,
             t.tier1_shape, t.tier2_lanes, t.max_slots, t.coop_forward,
-            (unsigned long long)t.affected_gain, t.fwd_groups, t.rev_split, t.rev_first_tier, t.ms);
+            (unsigned long long)t.affected_gain, t.fwd_groups, t.rev_split, t.rev_first_tier, t.ms, k.model,
+            TUNE_ENGINES);
     fclose(f);
 }
 
@@ -4907,12 +4919,12 @@ static int graph_signature(const im_graph *g, uint32_t R, im_workspace *ws, hipS
     HIPCHK(hipMemcpyAsync(ws->host_stats, ws->stats, sizeof(unsigned long long),
                           hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    *key = TuneKey{g->n, g->m, R, ws->host_stats[0]};
+    *key = TuneKey{g->n, g->m, R, ws->host_stats[0], ws->live_edge | ws->pair_coins << 1};
     return IM_OK;
 }
 
 // time `prepare` (everything up to and including the initial counts) under
-// each candidate schedule; keep the fastest on the workspace
+// each candidate schedule; keep the fastest on the workspace.
 template <typename Prep>
 static int tune(im_workspace *ws, hipStream_t s, Prep prep, im_tuning *best)
 {
