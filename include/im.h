@@ -323,12 +323,14 @@ int im_select_batch(const im_instance *inst, uint32_t count, uint32_t *seeds_out
  * and the first 16 rounds under four per-round update strategies (the
  * IM_OPT_AFFECTED_GAIN thresholds 0, n R / 4096, n R / 256 and 2^62: reverse
  * decrements in every round, the affected-set recompute in the small, in
- * most or in all rounds) and keeps the fastest; when the schedule uses the
- * cooperative forward search, it last times that search's width
- * (IM_OPT_FWD_GROUPS 16 or 32 workgroups per word) on the same trial, and
- * then the split of last-tier reverse tasks (IM_OPT_REV_SPLIT 1 or 2) and
- * the tier reverse tasks start on (IM_OPT_REV_FIRST_TIER 0 or 1; the batch
- * tuner times these two as well, on its own trial).
+ * most or in all rounds) and keeps the fastest. Where the chosen rounds run by
+ * word, and the schedule uses the cooperative forward search, it last times
+ * that search's width (IM_OPT_FWD_GROUPS 16 or 32 workgroups per word) on the
+ * same trial, and then the split of last-tier reverse tasks (IM_OPT_REV_SPLIT
+ * 1 or 2) and the tier reverse tasks start on (IM_OPT_REV_FIRST_TIER 0 or 1;
+ * the batch tuner times these two as well, on its own trial); rounds by
+ * snapshot read none of these, nor the forward engine, and linear-threshold
+ * forests no schedule at all: what is not read is not timed.
  * im_autotune caches its choice per graph signature (n, m, R, the snapshot
  * model and a checksum of col and prob) for the life of the process; a cached
  * choice is applied

@@ -4924,7 +4924,9 @@ static int graph_signature(const im_graph *g, uint32_t R, im_workspace *ws, hipS
 }
 
 // time `prepare` (everything up to and including the initial counts) under
-// each candidate schedule; keep the fastest on the workspace.
+// each candidate schedule; keep the fastest on the workspace. Schedules whose
+// difference nothing reads are left out: the forward engine where the rounds
+// run by snapshot, all but one on linear-threshold forests.
 template <typename Prep>
 static int tune(im_workspace *ws, hipStream_t s, Prep prep, im_tuning *best)
 {
@@ -4936,7 +4938,10 @@ static int tune(im_workspace *ws, hipStream_t s, Prep prep, im_tuning *best)
     ws->prof_mask = 0;
     float best_ms = -1.0f;
     int best_i = 0;
+    uint32_t tried = 0;
     for (int i = 0; i < N_SCHEDULES; i++) {
+        if (tried && (ws->lt_on || (ws->rv_on && !kSchedules[i].coop_forward))) continue;
+        tried++;
         apply_schedule(ws, kSchedules[i]);
         float ms_min = -1.0f;
         for (int rep = 0; rep < 2; rep++) {
@@ -4964,7 +4969,7 @@ static int tune(im_workspace *ws, hipStream_t s, Prep prep, im_tuning *best)
     best->max_slots = kSchedules[best_i].max_slots;
     best->coop_forward = kSchedules[best_i].coop_forward;
     best->ms = best_ms;
-    best->tried = N_SCHEDULES;
+    best->tried = tried;
     best->affected_gain = 0;
     best->fwd_groups = (int32_t)ws->fwd_per_word;
     best->rev_split = (int32_t)ws->rev_split;
@@ -5152,8 +5157,9 @@ extern "C" int im_autotune(const im_graph *g, uint32_t R, uint64_t seed, im_work
         int r = enqueue_prepare(g, R, seed, ka, ws, s);
         return r ? r : enqueue_rounds(g, R, ka, sd, gd, nullptr, ws, s);
     };
-    if (!rc) rc = tune_affected((uint64_t)g->n * R, ws, s, run, &best);
-    if (!rc) rc = tune_fwd_and_split(ws, s, run, &best, true);
+    if (!rc && !ws->lt_on) rc = tune_affected((uint64_t)g->n * R, ws, s, run, &best);
+    if (!rc) rc = run(true);   // (which rounds the choice leads to)
+    if (!rc && !ws->lt_on && !ws->rv_on) rc = tune_fwd_and_split(ws, s, run, &best, true);
     (void)hipStreamSynchronize(s);
     dfree(sd);
     dfree(gd);
@@ -5192,7 +5198,7 @@ extern "C" int im_autotune_batch(const im_instance *inst, uint32_t count, im_wor
         return r ? r : enqueue_rounds(&mg, Rmax, kt, sd, gd, nullptr, ws, s);
     };
     rc = tune(ws, s, prep, &best);
-    if (!rc) rc = tune_fwd_and_split(ws, s, prep, &best, false);
+    if (!rc && !ws->rv_on) rc = tune_fwd_and_split(ws, s, prep, &best, false);
     (void)hipStreamSynchronize(s);
     dfree(sd);
     dfree(gd);

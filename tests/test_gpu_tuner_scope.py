@@ -34,7 +34,7 @@ def test_choice_per_snapshot_model(im):
     ws = im.Workspace()
     ws.set_live_edge(1)
     t = im.autotune(d, 70, 3, ws=ws)
-    assert t["tried"] >= 1
+    assert t["tried"] == 1 and t["affected_gain"] == 0   # forests read no schedule
     assert im.autotune(d, 70, 3, ws=ws)["tried"] == 0
     s, gn, _ = oracle.select_du_lt(g.row_ptr, g.col, g.prob, 70, 5, 3, trace=True)
     seeds, gains, _ = im.select(d, 70, 5, 3, ws=ws)
@@ -45,6 +45,18 @@ def test_choice_per_snapshot_model(im):
     s, gn, _, _ = oracle.select_du(g.row_ptr, g.col, g.prob, 70, 5, 3)
     seeds, gains, _ = im.select(d, 70, 5, 3, ws=ws)
     assert [seeds.cpu().tolist(), gains.cpu().tolist()] == [s.tolist(), gn.tolist()]
+
+
+def test_knobs_that_nothing_reads_are_not_timed(im):
+    g = gg.chung_lu_graph(1100, 6000, 2.5, 82, True, 0.05)
+    d = _dev(im, g)
+    t = im.autotune(d, 64, 3, ws=im.Workspace())
+    if t["affected_gain"] == 0:   # rounds by snapshot: seven schedules, four update strategies
+        assert t["tried"] == 7 + 4 and t["coop_forward"] == 1
+    ws = im.Workspace()
+    ws.set_sparse_lists(0)
+    h = gg.chung_lu_graph(1000, 6000, 2.5, 83, True, 0.05)
+    assert im.autotune(_dev(im, h), 64, 3, ws=ws)["tried"] >= 10 + 4 + 4   # rounds by word: all
 
 
 def test_lines_of_earlier_engines_are_passed_over(im, tmp_path):
