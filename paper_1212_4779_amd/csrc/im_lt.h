@@ -261,15 +261,18 @@ __global__ __launch_bounds__(256) void k_lt_up(LtForest f)
     for (;;) {
         const uint32_t p = f.par[off + v];
         if (p == LT_NONE) break;
-        const uint32_t d0 = atomicAdd(&f.cur[off + p], degs);
-        // the degree sum is in place before this child counts as arrived
-        __builtin_amdgcn_s_waitcnt(0);
-        asm volatile("" ::: "memory");
+        // The degree sum is in place before this child counts as arrived: what it
+        // is added to comes back first, and the second addition waits for that
+        // value. (Whoever counts the last child reads the sum by an atomic too. A
+        // release and acquire of the whole memory instead writes the L2 back at
+        // every step: 5.6 -> 73 ms, 200,000 nodes, R = 256.)
+        const uint32_t before = atomicAdd(&f.cur[off + p], degs);
+        uint32_t add = size;
+        asm volatile("" : "+v"(add) : "v"(before));
         const unsigned long long old =
-            atomicAdd(&f.sc[off + p], (unsigned long long)size - (1ull << 32));
+            atomicAdd(&f.sc[off + p], (unsigned long long)add - (1ull << 32));
         f.pos[off + v] = (old & 0xFFFFFFFFull) | ((unsigned long long)p << 32);
         if ((old >> 32) != 1ull) break;   // other children are still to come
-        (void)d0;
         size += (uint32_t)old;
         degs = atomicAdd(&f.cur[off + p], 0u);
         v = p;
