@@ -32,31 +32,66 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 METRIC = ("k-seed selection wall time + snapshot-edge traversals/s (% HBM peak), "
           "learned vs plain")
-# algorithmic bytes: per (task, reached node) the two row offsets (8 B); per
-# (arc, word) relaxation the head id (4 B) and the snapshot word (8 B); per
-# reached node of a reverse task the gain read-modify-write (8 B); per node of
-# the forward search the covered word read-modify-write (16 B)
+# algorithmic bytes of the searches by word: per (task, reached node) the two row
+# offsets (8 B); per (arc, word) relaxation the head id (4 B) and the snapshot
+# word (8 B); per reached node of a reverse task the gain read-modify-write (8 B);
+# per node of the forward search the covered word read-modify-write (16 B)
 B_NODE, B_RELAX, B_DEC, B_COVER = 8, 12, 8, 16
+# of the searches by snapshot, which read live heads only: per listed head its id
+# (4 B); per reached node both list offsets (8 B) and the row offsets for the
+# counters (8 B), and in a reverse search the gain (8 B); per newly covered (node,
+# snapshot) pair of the forward step also its place among the sources (4 B) and
+# the stamp (8 B). The last tier of the initial counts counts its reached nodes per
+# word, not per snapshot, so its figure is a lower bound.
+B_HEAD, B_LIST, B_SRC, B_STAMP = 4, 8, 4, 8
+# of the linear-threshold forests, per (node, snapshot): k_lt_up reads parent and
+# degree (8 B) and updates size, sum and offset (28 B); k_lt_gain reads size and
+# sum (12 B); k_lt_order reads parent, size and offset (20 B) and writes node and
+# size by position (8 B); per newly covered pair of a round size by position (8 B),
+# node (4 B), stamp (8 B), degrees (8 B) and gain (8 B)
+B_LT = {"init_t0": 36, "init_t1": 12, "init_t2": 28}
+B_LT_COVER = 36
 PROPAGATION = ("init_t0", "init_t1", "init_t2", "forward", "rev_t0", "rev_t1", "rev_t2")
 
 
-def kernel_bytes(st, n, W):
-    """Algorithmic bytes of each propagation phase over one call."""
+def by_snapshot(prof):
+    """Whether the profiled call's rounds ran by snapshot (those by word pack their reverse tasks)."""
+    return prof["pack"][1] == 0
+
+
+def kernel_bytes(st, n, W, covered=None):
+    """Algorithmic bytes of each propagation phase over one call. covered: (node, snapshot) pairs
+    covered by the selection (the sum of its gains) if its rounds ran by snapshot."""
     out = {}
     for t in range(3):
         out[f"init_t{t}"] = (B_RELAX * st[f"relax_init_t{t}"] + B_NODE * st[f"reached_init_t{t}"]
                              + (4 * n * W if t == 0 else 0))
         out[f"rev_t{t}"] = B_RELAX * st[f"relax_rev_t{t}"] + (B_NODE + B_DEC) * st[f"reached_rev_t{t}"]
     out["forward"] = B_RELAX * st["relax_fwd"] + (B_NODE + B_COVER) * st["tasks_rev"]
+    if covered is not None:
+        out["init_t2"] = B_HEAD * st["arcs_read_init_t2"] + (B_LIST + B_NODE) * st["reached_init_t2"]
+        for t in range(3):
+            out[f"rev_t{t}"] = (B_HEAD * st[f"arcs_read_rev_t{t}"]
+                                + (B_LIST + B_NODE + B_DEC) * st[f"reached_rev_t{t}"])
+        out["forward"] = (B_HEAD + B_LIST + B_NODE + B_SRC + B_STAMP) * covered
     return out
+
+
+def kernel_bytes_lt(n, R, covered):
+    """The same for linear-threshold forests (reverse phases: part of the round's kernel)."""
+    out = {ph: b * n * R for ph, b in B_LT.items()}
+    out["forward"] = B_LT_COVER * covered
+    return dict(out, rev_t0=0, rev_t1=0, rev_t2=0)
 
 
 KERNEL_NAMES = {
     "init_t0": "k_lds_bfs<COUNT,64,...>", "init_t1": "k_lds_bfs<COUNT,256,...>",
-    "init_t2": "k_cnt_bits", "forward": "k_fwd_snap",
-    "rev_t0": "k_lds_bfs<DEC,64,...>", "rev_t1": "k_rev_search<256,...>",
-    "rev_t2": "k_rev_search<512,...>",
+    "init_t2": "k_block_bfs<COUNT,...>", "forward": "k_forward_coop",
+    "rev_t0": "k_lds_bfs<DEC,64,...>", "rev_t1": "k_lds_bfs<DEC,256,...>",
+    "rev_t2": "k_block_bfs<DEC,...>",
 }
+KERNEL_NAMES_SNAPSHOT = dict(KERNEL_NAMES, init_t2="k_cnt_bits", forward="k_fwd_snap",
+                             rev_t1="k_rev_search<256,...>", rev_t2="k_rev_search<512,...>")
 # linear threshold: the same phases on the snapshots' forests
 KERNEL_NAMES_LT = {"init_t0": "k_lt_up", "init_t1": "k_lt_gain", "init_t2": "k_lt_order",
                    "forward": "k_lt_round"}
@@ -95,22 +130,29 @@ WORK_OPTIONS = {"init_t2": (("tier1_shape", 0),),
                 "rev_t2": (("tier1_shape", 0), ("rev_first_tier", 0), ("rev_split", 1))}
 
 
-def load_traffic(phase, workload, schedule):
+SNAPSHOT_PHASES = ("init_t2", "forward", "rev_t1", "rev_t2")
+
+
+def load_traffic(phase, workload, schedule, snapshot=False):
     """HBM bytes per launch of `phase` from the committed rocprofv3 counter
     summary (profiles/traffic.json), if it was taken on this workload, on the
     current source of that kernel, on the kernel this schedule launches and
-    with the same share of the work; else None."""
+    with the same share of the work; else None. snapshot: the rounds ran by
+    snapshot, on kernels that no schedule changes."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
     with open(path) as f:
         t = json.load(f)
     t = t.get("workloads", {}).get(workload, {})
-    k = t.get("kernels", {}).get(phase)
+    own = snapshot and phase in SNAPSHOT_PHASES
+    k = t.get("snapshot_kernels" if own else "kernels", {}).get(phase)
     if not k:
         return None
     if k.get("source_digest") != source_digest(k.get("sources", [])):
         return None
+    if own:
+        return k.get("hbm_bytes_per_launch")
     if kernel_signature(phase, schedule) not in k.get("kernel", ""):
         return None
     for key, default in WORK_OPTIONS.get(phase, ()):
@@ -254,7 +296,9 @@ def run_batch(args, log):
     st = ws.stats()
     W = 4
     n_tot = sum(g.n for g in graphs)
-    kb = kernel_bytes(st, n_tot, W)
+    snapshot = by_snapshot(prof)
+    kb = kernel_bytes(st, n_tot, W, sum(int(gn.sum()) for _, gn in res) if snapshot else None)
+    names = KERNEL_NAMES_SNAPSHOT if snapshot else KERNEL_NAMES
     dom = max(PROPAGATION, key=lambda p: prof[p][0])
     log("phases (ms, launches): " + ", ".join(f"{p}={prof[p][0]:.3f}/{prof[p][1]}" for p in prof))
     ws.profile_enable([dom])
@@ -332,8 +376,8 @@ def run_batch(args, log):
         "selection_ms": ms, "traversals_per_step": trav,
         "phase_ms": {p: round(prof[p][0], 4) for p in prof},
         "roofline": {"bound": "hbm", "achieved": round(ach, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": load_traffic(dom, "batch512", tuning),
-                     "kernel": KERNEL_NAMES[dom], "phase": dom,
+                     "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": load_traffic(dom, "batch512", tuning, snapshot),
+                     "kernel": names[dom], "phase": dom,
                      "algorithmic_bytes_per_launch": int(bpl), "avg_launch_ms": round(avg_ms, 4)},
         "schedule": tuning,
         "cpu_baseline": cpu, "cpu_baseline_all_cores": cpu_all, "parity_vs_oracle_golden": parity,
@@ -379,7 +423,7 @@ def run_lt(args, log):
     seeds, gains, _ = im.select(dg, R, k, seed, ws=ws)
     prof = ws.profile()
     st = ws.stats()
-    kb = kernel_bytes(st, g.n, W)
+    kb = kernel_bytes_lt(g.n, R, int(gains.sum()))
     dom = max(PROPAGATION, key=lambda p: prof[p][0])
     ws.profile_enable([dom])
     stream = torch.cuda.current_stream(dev)
@@ -596,7 +640,9 @@ def main():
     seeds, gains, _ = im.select(dg, R, k, seed, ws=ws)
     prof = ws.profile()
     st = ws.stats()
-    kb = kernel_bytes(st, g.n, W)
+    snapshot = by_snapshot(prof)
+    kb = kernel_bytes(st, g.n, W, int(gains.sum()) if snapshot else None)
+    names = KERNEL_NAMES_SNAPSHOT if snapshot else KERNEL_NAMES
     dom = max(PROPAGATION, key=lambda p: prof[p][0])
     log("phases (ms, launches): " + ", ".join(f"{p}={prof[p][0]:.3f}/{prof[p][1]}" for p in prof))
 
@@ -628,14 +674,14 @@ def main():
         if nl == 0 or tms <= 0:
             continue
         a_gbs = kb[ph] / (tms / 1e3) / 1e9
-        per_kernel[ph] = {"kernel": KERNEL_NAMES[ph], "launches": nl, "ms": round(tms, 4),
+        per_kernel[ph] = {"kernel": names[ph], "launches": nl, "ms": round(tms, 4),
                           "algorithmic_bytes_per_launch": int(kb[ph] / nl),
                           "achieved": round(a_gbs, 2), "frac": round(a_gbs / HBM_PEAK_GBS, 5),
-                          "traffic": load_traffic(ph, args.workload, tuning)}
-    traffic = load_traffic(dom, args.workload, tuning)
+                          "traffic": load_traffic(ph, args.workload, tuning, snapshot)}
+    traffic = load_traffic(dom, args.workload, tuning, snapshot)
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": KERNEL_NAMES[dom], "phase": dom,
+                "kernel": names[dom], "phase": dom,
                 "algorithmic_bytes_per_launch": int(bytes_per_launch),
                 "avg_launch_ms": round(avg_launch_ms, 4)}
 

@@ -189,19 +189,26 @@ typedef struct im_stats {
     uint64_t celf_evals;       /* exact gain evaluations (lazy path)              */
     /* Per pass p (0: initial counts, 1: reverse decrements, 2: exact
      * evaluations) and engine tier t (0: per-wavefront LDS tables, 1:
-     * per-workgroup LDS tables, 2: per-workgroup dense global arrays):    */
+     * per-workgroup LDS tables, 2: per-workgroup dense global arrays). What
+     * runs by snapshot counts as tier 2 in passes 0 and 2, by (task, reached
+     * node) of the words as the tiers do in pass 0, by snapshot in pass 2, and
+     * in pass 1 as tiers 1 and 2 (the two launches), a task being up to 64
+     * sources of one snapshot and an arc a listed live one:               */
     uint64_t relax[3][3];      /* sum over (node, word) tasks of the degree of    */
                                /* every node reached in that word                 */
     uint64_t reached[3][3];    /* (task, reached node) pairs                      */
     uint64_t arcs_read[3][3];  /* (arc, word) reads issued, re-expansions included*/
     uint64_t handed_over[3][3];/* tasks passed on to the next tier                */
-    uint64_t fwd_levels;       /* levels of the forward searches (sum over words) */
+    uint64_t fwd_levels;       /* levels of the forward searches that run one     */
+                               /* workgroup per word (sum over words); the        */
+                               /* cooperative ones and those by snapshot count none*/
     uint64_t fwd_entries;      /* frontier entries expanded by them               */
     uint64_t celf_batches;     /* evaluation batches of the lazy path             */
     uint64_t celf_fallbacks;   /* learned picks that fell back to bound order     */
     uint64_t max_levels[3][3]; /* per pass and tier: the most search levels one   */
                                /* workgroup ran in any launch of the call (the    */
-                               /* launch's critical path in levels)               */
+                               /* launch's critical path in levels); searches by  */
+                               /* snapshot count none                             */
     uint64_t barrier_failures; /* grid barriers of the cooperative kernels whose */
                                /* wait timed out (always 0 on a working device;   */
                                /* the launch was then abandoned, results invalid) */
