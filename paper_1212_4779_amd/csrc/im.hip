@@ -88,32 +88,35 @@ static void fill(Tv *p, uint64_t cnt, Tv v, hipStream_t s)
 // ---------------------------------------------------------------------------
 // A1: validation and reverse CSR
 // ---------------------------------------------------------------------------
-enum { ERR_ROW0 = 1, ERR_ROWN = 2, ERR_ROWDEC = 4, ERR_ROWBIG = 8, ERR_COL = 16, ERR_PROB = 32,
-       SEEN_COIN = 64 };   // (no error: an arc below P_SURE)
+enum { ERR_ROW0 = 1, ERR_ROWN = 2, ERR_ROWDEC = 4, ERR_ROWBIG = 8, ERR_COL = 16, ERR_PROB = 32 };
 
 // Graphs without an arc below this probability: a word's 64 snapshots are nearly
 // the same, and the searches by word, which take them together, do less than
-// those by snapshot. ms per selection, by snapshot and by word: 8,000 nodes of
-// ten arcs, R = 64: p = 0.8 134 and 119 (the rounds alone 46 and 55), 0.9 117 and
-// 97 (48 and 44), 1 96 and 62; 20,000 nodes of three arcs, R = 256: p = 0.9 1,650
-// and 1,295, p = 1 1,326 and 360.
+// those by snapshot. ms of ten rounds, by snapshot and by word: 8,000 nodes of ten
+// arcs, R = 64: p = 0.8 46 and 55, 0.9 49 and 44, 1 51 and 27; 20,000 nodes of
+// three arcs, R = 256: p = 0.8 577 and 946, 0.9 695 and 644, 1 797 and 186.
 constexpr float P_SURE = 0.9f;
 
-// flags of a wavefront's lanes into *err, where they are not there yet: all
-// workgroups of a launch see the same few
-__device__ __forceinline__ void wave_flags(uint32_t *err, uint32_t e)
+// A lane's error flags into err[0], and the arcs of a wavefront none of which is
+// below P_SURE into err[1], which has all arcs at the end if none is: graphs of
+// coins have hardly such a wavefront, and add nothing (a flag for an arc below
+// met at one address from thousands of wavefronts: 192 -> 238 us for scoring
+// seven seeds on 4*10^5 arcs).
+__device__ __forceinline__ void report_arcs(uint32_t *err, uint32_t e, uint32_t arcs, bool sure)
 {
+    if (e) atomicOr(err, e);
+    if (!__all(sure)) return;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) e |= __shfl_xor(e, d, 64);
-    if ((threadIdx.x & 63u) == 0 && (e & ~__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-        atomicOr(err, e);
+    for (int d = 32; d >= 1; d >>= 1) arcs += __shfl_xor(arcs, d, 64);
+    if ((threadIdx.x & 63u) == 0 && arcs) atomicAdd(err + 1, arcs);
 }
 
 __global__ void k_validate(const uint64_t *row_ptr, const uint32_t *col, const float *prob,
                            uint32_t n, uint64_t m, uint32_t *err, uint32_t *row32)
 {
     uint64_t lim = (uint64_t)n + 1 > m ? (uint64_t)n + 1 : m;
-    uint32_t e = 0;
+    uint32_t e = 0, arcs = 0;
+    bool sure = true;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < lim;
          i += (uint64_t)gridDim.x * blockDim.x) {
         if (i <= n) {
@@ -128,10 +131,11 @@ __global__ void k_validate(const uint64_t *row_ptr, const uint32_t *col, const f
             if (col[i] >= n) e |= ERR_COL;
             float p = prob[i];
             if (!(p >= 0.0f && p <= 1.0f)) e |= ERR_PROB;
-            if (p < P_SURE) e |= SEEN_COIN;
+            sure = sure && p >= P_SURE;
+            arcs++;
         }
     }
-    wave_flags(err, e);
+    report_arcs(err, e, arcs, sure);
 }
 
 // 32-bit copy of the row offsets (a plan's replays re-read row_ptr with this)
@@ -267,7 +271,8 @@ __global__ void k_batch_merge(const InstDesc *desc, uint32_t *err, uint32_t *row
     const uint32_t i = blockIdx.y;
     const InstDesc d = desc[i];
     const uint64_t lim = (uint64_t)d.n + 1 > d.m ? (uint64_t)d.n + 1 : d.m;
-    uint32_t e = 0;
+    uint32_t e = 0, arcs = 0;
+    bool sure = true;
     for (uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; j < lim;
          j += (uint64_t)gridDim.x * blockDim.x) {
         if (j <= d.n) {
@@ -285,11 +290,12 @@ __global__ void k_batch_merge(const InstDesc *desc, uint32_t *err, uint32_t *row
             mcol[d.arc_off + j] = d.node_off + c;
             const float p = d.prob[j];
             if (!(p >= 0.0f && p <= 1.0f)) e |= ERR_PROB;
-            if (p < P_SURE) e |= SEEN_COIN;
+            sure = sure && p >= P_SURE;
+            arcs++;
             mprob[d.arc_off + j] = p;
         }
     }
-    wave_flags(err, e);
+    report_arcs(err, e, arcs, sure);
 }
 
 constexpr int SCAN_NT = 256, SCAN_IPT = 8, SCAN_TILE = SCAN_NT * SCAN_IPT;
@@ -1559,11 +1565,13 @@ static void dfree(Tv *&p)
 // left has to serve the runtime: kernels with private memory (k_forward_coop,
 // k_lt_round and others: up to 250 bytes a lane, 130 MB on a full device, per
 // hardware queue) get it when they are launched, and a launch that cannot have
-// it ends the process.
-constexpr uint64_t ROOM_LEFT = 1ull << 30;
+// it ends the process. (Small buffers are not worth the question: a workspace has
+// a dozen at most.)
+constexpr uint64_t ROOM_LEFT = 1ull << 30, ROOM_SMALL = 16ull << 20;
 
 static bool room_for(uint64_t bytes)
 {
+    if (bytes <= ROOM_SMALL) return true;
     size_t left = 0, total = 0;
     if (hipMemGetInfo(&left, &total) != hipSuccess) {
         (void)hipGetLastError();
@@ -1603,8 +1611,8 @@ extern "C" int im_workspace_create(im_workspace **out)
     int rc;
     if ((rc = ws_init_device(ws))) { delete ws; return rc; }
     if ((rc = dalloc(&ws->stats, ST_COUNT * ST_STRIPES))) { delete ws; return rc; }
-    if ((rc = dalloc(&ws->err, 1))) { delete ws; return rc; }
-    HIPCHK(hipHostMalloc((void **)&ws->host_err, sizeof(uint32_t), hipHostMallocDefault));
+    if ((rc = dalloc(&ws->err, 2))) { delete ws; return rc; }
+    HIPCHK(hipHostMalloc((void **)&ws->host_err, 2 * sizeof(uint32_t), hipHostMallocDefault));
     HIPCHK(hipHostMalloc((void **)&ws->host_stats, ST_COUNT * ST_STRIPES * sizeof(unsigned long long),
                          hipHostMallocDefault));
     HIPCHK(hipMemset(ws->stats, 0, ST_COUNT * ST_STRIPES * sizeof(unsigned long long)));
@@ -1958,12 +1966,12 @@ static int check_args(const im_graph *g, uint32_t R)
 static int validate(const im_graph *g, im_workspace *ws, hipStream_t s, uint32_t *row32)
 {
     PhaseTimer pt(ws, IM_PH_VALIDATE, s);
-    HIPCHK(hipMemsetAsync(ws->err, 0, sizeof(uint32_t), s));
+    HIPCHK(hipMemsetAsync(ws->err, 0, 2 * sizeof(uint32_t), s));
     uint64_t lim = std::max<uint64_t>((uint64_t)g->n + 1, g->m);
     k_validate<<<grid_for(lim, 256), 256, 0, s>>>(g->row_ptr, g->col, g->prob, g->n, g->m,
                                                   ws->err, row32);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(ws->host_err, ws->err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(ws->host_err, ws->err, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     uint32_t e = *ws->host_err;
     if (e & ERR_ROW0) return im_fail(IM_EINVAL, "row_ptr[0] != 0");
@@ -1971,7 +1979,7 @@ static int validate(const im_graph *g, im_workspace *ws, hipStream_t s, uint32_t
     if (e & (ERR_ROWDEC | ERR_ROWBIG)) return im_fail(IM_EINVAL, "row_ptr is not non-decreasing within [0, m]");
     if (e & ERR_COL) return im_fail(IM_EINVAL, "col entry >= n");
     if (e & ERR_PROB) return im_fail(IM_EINVAL, "prob outside [0, 1] or NaN");
-    ws->sure = g->m && !(e & SEEN_COIN);
+    ws->sure = g->m && ws->host_err[1] == g->m;
     return IM_OK;
 }
 
@@ -4280,7 +4288,7 @@ struct NoAllocDev {
     int num_cu = 0;
     unsigned fwd_grid = 0, eval_grid = 0;
     im_workspace ws;       // host view of the carved buffers, rebuilt by every call
-    uint32_t host_err = 0;
+    uint32_t host_err[2] = {};
     unsigned long long host_stats[ST_COUNT * ST_STRIPES];
 };
 static NoAllocDev g_noalloc[NA_MAX_DEV];
@@ -4296,7 +4304,7 @@ static void noalloc_options(im_workspace *ws)
 static int noalloc_reserve(im_workspace *ws, const im_graph *g, uint32_t R, uint32_t k)
 {
     int rc;
-    if ((rc = dalloc(&ws->stats, ST_COUNT * ST_STRIPES)) || (rc = dalloc(&ws->err, 1))) return rc;
+    if ((rc = dalloc(&ws->stats, ST_COUNT * ST_STRIPES)) || (rc = dalloc(&ws->err, 2))) return rc;
     return ws_reserve(ws, g->n, g->m, (R + 63) / 64, k, g->n);
 }
 
@@ -4352,7 +4360,7 @@ extern "C" int im_select_noalloc(const im_graph *g, uint32_t R, uint32_t k, uint
     ws->fwd_grid = d.fwd_grid;
     ws->eval_grid = d.eval_grid;
     noalloc_options(ws);
-    ws->host_err = &d.host_err;
+    ws->host_err = d.host_err;
     ws->host_stats = d.host_stats;
     Arena a = {d.ptr, IM_NOALLOC_SCRATCH_BYTES, 0, s};
     t_arena = &a;
@@ -4680,13 +4688,13 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     HIPCHK(hipMemcpyAsync(ws->b_u32, hu, (4ull * (count + 1)) * 4, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(ws->b_u64, h64, (3ull * (count + 1)) * 8, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(ws->b_desc, hd, (uint64_t)count * sizeof(InstDesc), hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemsetAsync(ws->err, 0, sizeof(uint32_t), s));
+    HIPCHK(hipMemsetAsync(ws->err, 0, 2 * sizeof(uint32_t), s));
     launch_merge(inst, count, ws, s);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(ws->host_err, ws->err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(ws->host_err, ws->err, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    ws->sure = M && !(*ws->host_err & SEEN_COIN);
-    if (*ws->host_err & ~SEEN_COIN)
+    ws->sure = M && ws->host_err[1] == M;
+    if (*ws->host_err)
         return im_fail(IM_EINVAL, "a batch instance failed validation (flags 0x%x)", *ws->host_err);
     for (int d = 0; d < 2; d++) reserve_sparse(ws, d, (uint32_t)N, M, Rmax);
     if (!ws->sure) {
