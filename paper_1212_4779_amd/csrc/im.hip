@@ -4133,6 +4133,7 @@ extern "C" int im_spread(const im_graph *g, uint32_t R, uint64_t seed, const uin
         a.queue = ws->v_queue;
         a.bits = n > SPR_LDS_NODES ? ws->v_bits : nullptr;
         a.marg = (unsigned long long *)marg_out;
+        a.sum_here = nS <= (uint32_t)SPR_ACC && (uint64_t)n * ((R + groups - 1) / groups) < (1ull << 32);
         a.per_snapshot = per_snapshot_out;
         if (!records) k_spread<512, false><<<groups, 512, lds, s>>>(a);
         else if (lanes == 64) k_spread<64, true><<<groups, 64, lds, s>>>(a);

@@ -54,6 +54,8 @@ struct SpreadArgs {
     uint32_t *queue;             // [workgroups][n]
     uint32_t *bits;              // [workgroups][ceil(n / 32)], zero at rest; LDS is used if null
     unsigned long long *marg;    // [ceil(nS / group)] (accumulated over snapshots) or nullptr
+    bool sum_here;               // ... per workgroup first, in 32 bits: at most SPR_ACC seeds,
+                                 // and its snapshots' nodes below 2^32 in all
     uint32_t *per_snapshot;      // [R] or nullptr
 };
 
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
     uint32_t *queue = a.queue + (uint64_t)blockIdx.x * a.n;
     if (!a.bits)
         for (uint32_t i = tid; i < words; i += NT) bits[i] = 0;
-    const bool sum_here = a.marg && a.nS <= (uint32_t)SPR_ACC;
+    const bool sum_here = a.marg && a.sum_here;
     for (uint32_t i = tid; i < (uint32_t)SPR_ACC; i += NT) acc[i] = 0;
     auto visit = [&](uint32_t v) {
         const uint32_t bit = 1u << (v & 31u);
@@ -131,14 +133,8 @@ __global__ __launch_bounds__(NT) void k_spread(SpreadArgs a)
                 head = end;
             }
             if (tid == 0 && a.marg && head != before) {   // (marginals: one seed per search)
-                unsigned long long sum = head - before;
-                if (sum_here) {
-                    // 32 bits (in 64 the workgroup's LDS is larger and two wavefronts fewer fit a CU
-                    // on small graphs): what does not fit goes out, as a share can be n R
-                    sum += acc[g0];
-                    acc[g0] = sum >> 32 ? 0u : (uint32_t)sum;
-                }
-                if (!sum_here || sum >> 32) atomicAdd(&a.marg[g0], sum);
+                if (sum_here) acc[g0] += head - before;
+                else atomicAdd(&a.marg[g0], (unsigned long long)(head - before));
             }
         }
         if (tid == 0 && a.per_snapshot) a.per_snapshot[r] = head;
