@@ -210,6 +210,30 @@ __device__ __forceinline__ bool lt_place(uint32_t nb, uint32_t rows, uint32_t &b
     return row < rows;
 }
 
+// The lanes of a wavefront with this lane's parent p (LT_NONE: none): all of them
+// as a mask, itself among them; group(mask) is called by the whole wavefront for
+// each of several lanes. A hub that keeps thousands of children in a snapshot has
+// their additions queue at its words otherwise (R = 256, k_lt_up: a star of
+// 200,000 arcs kept half the time 42.7 -> 1.4 ms, ten hubs with their leaves dealt
+// in turn 11.9 -> 2.6). Parents are looked for as long as lanes share them:
+// LT_SINGLE lanes that are alone end it.
+constexpr int LT_SINGLE = 2;
+
+template <typename Group>
+__device__ __forceinline__ uint64_t lt_same_parent(uint32_t p, Group group)
+{
+    uint64_t left = __ballot(p != LT_NONE), mine = 1ull << (threadIdx.x & 63u);
+    for (int single = 0; left && single < LT_SINGLE;) {
+        const int lead = __ffsll((unsigned long long)left) - 1;
+        const uint64_t same = __ballot(p == (uint32_t)__builtin_amdgcn_readlane((int)p, lead));
+        left &= ~same;
+        if (same & (same - 1)) group(same);
+        else single++;
+        if (same & mine) mine = same;
+    }
+    return mine;
+}
+
 // Each thread draws its node's kept in-arc in LTP_R snapshots: the largest j
 // with start[j] <= draw (an arc of length zero shares its start with the next
 // one, which comes later), if the draw lies in that arc's interval.
@@ -223,8 +247,9 @@ __global__ __launch_bounds__(256) void k_lt_parent(const uint32_t *row, const ui
     uint32_t block, rows;
     if (!lt_place((f.n + 255) / 256, (f.R + LTP_R - 1) / LTP_R, block, rows)) return;
     const uint32_t v = block * 256u + threadIdx.x, r0 = rows * LTP_R;
-    if (v >= f.n) return;
-    const uint32_t a = in_row[v], b = in_row[v + 1], dg = row[v + 1] - row[v];
+    const bool in = v < f.n;
+    const uint32_t a = in ? in_row[v] : 0u, b = in ? in_row[v + 1] : 0u;
+    const uint32_t dg = in ? row[v + 1] - row[v] : 0u;
     const uint64_t key = sm64_finalise(seed + ((uint64_t)v + 1ull) * IM_GOLDEN);
     for (uint32_t r = r0; r < min(r0 + (uint32_t)LTP_R, f.R); r++) {
         uint32_t p = LT_NONE;
@@ -238,9 +263,15 @@ __global__ __launch_bounds__(256) void k_lt_parent(const uint32_t *row, const ui
             if (d - start[lo] < lt_len(prob, in2out[lo])) p = in_col[lo];
         }
         const uint64_t at = (uint64_t)r * f.n + v;
-        f.par[at] = p;
-        f.cur[at] = dg;
-        if (p != LT_NONE) atomicAdd(&f.sc[(uint64_t)r * f.n + p], 1ull << 32);
+        if (in) {
+            f.par[at] = p;
+            f.cur[at] = dg;
+        }
+        unsigned long long *sc = f.sc + (uint64_t)r * f.n;
+        const uint32_t lane = threadIdx.x & 63u;
+        const uint64_t same = lt_same_parent(p, [](uint64_t) {});
+        if (p != LT_NONE && (uint32_t)__ffsll((unsigned long long)same) == lane + 1)
+            atomicAdd(&sc[p], (unsigned long long)__popcll(same) << 32);
     }
 }
 
@@ -253,29 +284,55 @@ __global__ __launch_bounds__(256) void k_lt_up(LtForest f)
 {
     uint32_t block, r;
     if (!lt_place((f.n + 255) / 256, f.R, block, r)) return;
-    const uint32_t u = block * 256u + threadIdx.x;
-    if (u >= f.n) return;
+    const uint32_t u = block * 256u + threadIdx.x, lane = threadIdx.x & 63u;
     const uint64_t off = (uint64_t)r * f.n;
-    if (f.sc[off + u] != 1ull) return;
-    uint32_t v = u, size = 1, degs = f.cur[off + v];
-    for (;;) {
-        const uint32_t p = f.par[off + v];
-        if (p == LT_NONE) break;
-        // The degree sum is in place before this child counts as arrived: what it
-        // is added to comes back first, and the second addition waits for that
-        // value. (Whoever counts the last child reads the sum by an atomic too. A
-        // release and acquire of the whole memory instead writes the L2 back at
-        // every step: 5.6 -> 73 ms, 200,000 nodes, R = 256.)
-        const uint32_t before = atomicAdd(&f.cur[off + p], degs);
-        uint32_t add = size;
-        asm volatile("" : "+v"(add) : "v"(before));
-        const unsigned long long old =
-            atomicAdd(&f.sc[off + p], (unsigned long long)add - (1ull << 32));
+    const bool leaf = u < f.n && f.sc[off + u] == 1ull;
+    uint32_t v = u, size = 1, degs = leaf ? f.cur[off + u] : 0u;
+    uint32_t p = leaf ? f.par[off + u] : LT_NONE;   // (LT_NONE: the walk has ended)
+    // `kids` subtrees of `nodes` nodes and degree sum `sum` in all arrive at p:
+    // what was there before. The degree sum is in place before they count as
+    // arrived: what it is added to comes back first, and the second addition
+    // waits for that value. (Whoever counts the last child reads the sum by an
+    // atomic too. A release and acquire of the whole memory instead writes the L2
+    // back at every step: 5.6 -> 73 ms, 200,000 nodes, R = 256.)
+    auto arrive = [&](uint32_t kids, uint32_t nodes, uint32_t sum) -> unsigned long long {
+        const uint32_t before = atomicAdd(&f.cur[off + p], sum);
+        asm volatile("" : "+v"(nodes) : "v"(before));
+        return atomicAdd(&f.sc[off + p], (unsigned long long)nodes - ((unsigned long long)kids << 32));
+    };
+    // on from p if all its children have arrived with these
+    auto climb = [&](unsigned long long old, uint32_t kids, uint32_t nodes) {
+        if ((old >> 32) == kids) {
+            size = (uint32_t)old + nodes;
+            degs = atomicAdd(&f.cur[off + p], 0u);
+            v = p;
+            p = f.par[off + v];
+        } else {
+            p = LT_NONE;   // other children are still to come
+        }
+    };
+    // leaves of one parent arrive together, the first of them for all
+    uint32_t sum = degs;
+    const uint64_t same = lt_same_parent(p, [&](uint64_t g) {
+        const bool in = (g >> lane) & 1ull;
+        const uint32_t all = (uint32_t)wave_sum_u64(in ? degs : 0u);
+        if (in) sum = all;
+    });
+    const uint32_t kids = (uint32_t)__popcll(same), lead = (uint32_t)__ffsll((unsigned long long)same) - 1;
+    const bool first = lane == lead;
+    unsigned long long old = 0;
+    if (p != LT_NONE && first) old = arrive(kids, kids, sum);
+    old = __shfl(old, (int)lead, 64);
+    if (p != LT_NONE) {
+        f.pos[off + v] = ((old & 0xFFFFFFFFull) + (uint32_t)__popcll(same & ((1ull << lane) - 1ull))) |
+                         ((unsigned long long)p << 32);
+        if (first) climb(old, kids, kids);
+        else p = LT_NONE;
+    }
+    while (p != LT_NONE) {
+        old = arrive(1, size, degs);
         f.pos[off + v] = (old & 0xFFFFFFFFull) | ((unsigned long long)p << 32);
-        if ((old >> 32) != 1ull) break;   // other children are still to come
-        size += (uint32_t)old;
-        degs = atomicAdd(&f.cur[off + p], 0u);
-        v = p;
+        climb(old, 1, size);
     }
 }
 
