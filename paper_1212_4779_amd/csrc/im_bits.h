@@ -43,12 +43,14 @@ constexpr int CB_WAVES = 16;     // most wavefronts (bits at a time) per workgro
 constexpr int CB_Q = 64;         // queue entries per wavefront kept in LDS as well
 constexpr uint32_t CB_LIST = 4096;   // tables: words of a task's marks that are listed
 constexpr int CB_TASKS = 8;      // most tasks in progress per workgroup
-// Most arcs without live lists that a wavefront reads for one snapshot: a hub whose
-// lists did not fit has its arcs' masks read once per snapshot here and once
-// per word in the dense tier, which takes its task (a star of 200,000 arcs, p =
-// 0.05, R = 256: 46 ms here, 3.2 there; bounds from 1,024 to 65,536 arcs measure
-// the same on weighted-cascade graphs, 1,024 costs supercritical ones 4 %)
-constexpr uint32_t CB_SCAN = 4096;
+// Nodes whose live lists did not fit have their arcs' masks read once per snapshot
+// here and once per word in the dense tier. With fewer tasks than workgroups a
+// wavefront that reads a hub's arcs is what the launch waits for, and a span past
+// CB_SCAN hands its task over at once (a star of 200,000 arcs, p = 0.05, R = 256:
+// 46 ms here, 3.2 there; a hub of 60,000 among many tasks, 120,000 nodes, p = 0.15:
+// 90 ms here, 133 there). With more, the probe decides: CB_SCANNED times as many
+// arcs read by mask as nodes reached.
+constexpr uint32_t CB_LONG = 1024, CB_SCAN = 16384, CB_SCANNED = 8;
 constexpr uint32_t CB_PROBE = 8; // searches after which a task's snapshots are compared
 constexpr uint32_t CB_SHARED = 6;    // ... that reached this many times the marks: shared
 constexpr uint32_t CB_JUDGED = 32;
@@ -147,7 +149,7 @@ struct WaveLds {
 // the number that may take the place next, open that of the task in it plus one.
 struct CntTask {
     uint32_t free, open, task, done, over, judge, sum, reached, words;
-    unsigned long long relax, trav, arcs;
+    unsigned long long relax, trav, arcs, scanned;
 };
 
 // The wavefronts take (task, bit) pairs in order, without a barrier: the sizes
@@ -176,6 +178,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     uint32_t *queue = a.queue + ((uint64_t)blockIdx.x * nw + wv) * (TABLE ? (uint32_t)CS : a.nmax);
     const uint32_t nt = *a.in_n;
     if (blockIdx.x >= nt) return;
+    const bool few = nt <= gridDim.x;
     const uint32_t nmaps = TABLE ? nw * per : (nw + a.tasks) * words;
     WaveLds &L = ((WaveLds *)(maps + nmaps))[wv];
     for (uint32_t i = tid; i < nmaps; i += blockDim.x)
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
     if (tid < CB_TASKS) {
         CntTask &t = T[tid];
         t.free = tid; t.open = 0; t.task = 0; t.done = 0; t.over = 0; t.judge = 0; t.sum = 0; t.reached = 0; t.words = 0;
-        t.relax = 0; t.trav = 0; t.arcs = 0;
+        t.relax = 0; t.trav = 0; t.arcs = 0; t.scanned = 0;
     }
     // lane 0: of the tasks that this wavefront finished
     unsigned long long t_relax = 0, t_reached = 0, t_trav = 0, t_arcs = 0;
@@ -221,6 +224,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
         if (((valid >> b) & 1ull) && !peek(&tk.over)) {
             // (of one search, each below 2^32: nodes, arcs, degrees of distinct nodes)
             uint32_t relax = 0, trav = 0, arcs = 0, reached = 0;
+            unsigned long long scanned = 0;   // (the same in every lane)
             // queue entries are nodes (bitmaps) or table positions
             auto entry = [&](uint32_t i) { return i < (uint32_t)CB_Q ? L.q[i] : queue[i]; };
             auto push = [&](uint32_t x) {
@@ -269,7 +273,10 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                             if (p < CB_LIST) list[p] = i >> 5;
                         }
                     }
-                    if (sp.kind == 2 && sp.len > CB_SCAN) { tk.over = 1; sp.len = 0; }
+                    if (__any(sp.len >= CB_LONG)) {   // (hubs alone are that long)
+                        if (sp.kind == 2 && sp.len > CB_SCAN && few) { tk.over = 1; sp.len = 0; }
+                        scanned += wave_sum_dpp(sp.kind == 2 ? sp.len : 0u);
+                    }
                     wave_expand(L.B, a.g, w, b, sp, visit, arcs);
                 }
                 head = end;
@@ -288,6 +295,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                 atomicAdd(&tk.relax, (unsigned long long)relax);
                 atomicAdd(&tk.trav, (unsigned long long)trav);
                 atomicAdd(&tk.arcs, (unsigned long long)arcs);
+                if (scanned) atomicAdd(&tk.scanned, scanned);
             }
         }
         uint32_t done = 0;
@@ -298,7 +306,8 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
         // the first searches: do the snapshots share their nodes?
         if (done == CB_PROBE && lane == 0) {
             const uint32_t sum = tk.sum, reached = tk.reached;
-            if (sum > 2u * reached + 64u) post(&tk.over, 1u);
+            if (sum > 2u * reached + 64u || tk.scanned > (unsigned long long)CB_SCANNED * (sum + CB_PROBE))
+                post(&tk.over, 1u);
             // (of words with few snapshots the probe is over before they can share)
             if (tk.judge && __popcll(valid) >= 32) {
                 const uint32_t judged = atomicAdd(&a.judged[0], 1u) + 1;
@@ -324,7 +333,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cnt_bits(BitsArgs a)
                 t_relax += tk.relax; t_reached += tk.reached; t_trav += tk.trav; t_arcs += tk.arcs;
             }
             tk.done = 0; tk.over = 0; tk.sum = 0; tk.reached = 0; tk.words = 0;
-            tk.relax = 0; tk.trav = 0; tk.arcs = 0;
+            tk.relax = 0; tk.trav = 0; tk.arcs = 0; tk.scanned = 0;
         }
         wave_order();
         if (TABLE) __builtin_amdgcn_s_waitcnt(0);   // the marks are gone before the place is open

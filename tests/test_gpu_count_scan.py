@@ -1,6 +1,6 @@
 """Initial counts of a hub whose live lists do not fit (most of its arcs live in many snapshots): around
-the arcs that one wavefront still reads by mask, on bitmaps and on tables, alone and behind a node that
-has lists; gains and the traversal counter against the oracle."""
+the arcs that one wavefront still reads by mask, on bitmaps and on tables, alone, behind a few nodes and
+behind thousands; gains and the traversal counter against the oracle."""
 import numpy as np
 import pytest
 
@@ -30,8 +30,8 @@ def _graph(n, arcs, p, back):
 
 
 @pytest.mark.parametrize("n,arcs,p,back,R", [
-    (6000, 4095, 0.5, 0, 65), (6000, 4096, 0.5, 3, 65), (6000, 4097, 0.5, 3, 65), (9000, 8000, 0.3, 40, 130),
-    (260000, 4096, 0.05, 5, 70), (260000, 4097, 0.05, 5, 70), (260000, 100000, 0.5, 4, 64)])
+    (18000, 16383, 0.5, 0, 65), (18000, 16384, 0.5, 3, 65), (18000, 16385, 0.5, 3, 65), (40000, 30000, 0.3, 40, 130),
+    (60000, 30000, 0.2, 3000, 20), (260000, 16384, 0.05, 5, 70), (260000, 16385, 0.05, 5, 70), (260000, 100000, 0.5, 4, 64)])
 def test_hub_without_lists(im, n, arcs, p, back, R):
     g = _graph(n, arcs, p, back)
     ref, st = oracle.initial_gains(g.row_ptr, g.col, g.prob, R, 5)
