@@ -75,7 +75,8 @@ int im_workspace_destroy(im_workspace *ws);
  *   Rounds of the dynamic update run by snapshot -- a forward search per
  *   snapshot, reverse searches from up to 64 sources of one snapshot --
  *   wherever the sparse lists are on, a single graph's IM_OPT_AFFECTED_GAIN is 0, some arc's
- *   probability is below 0.9 (else a word's snapshots are nearly the same) and
+ *   probability is below 0.9 (else, from two arcs a node on, a word's snapshots
+ *   are nearly the same) and
  *   the call's (node, snapshot) pairs fit 32-bit positions and the device; otherwise
  *   (im_select_noalloc among them) by word, on the engines that
  *   IM_OPT_COOP_GAIN, IM_OPT_FWD_GROUPS, IM_OPT_REV_SPLIT and

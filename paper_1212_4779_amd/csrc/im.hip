@@ -94,8 +94,11 @@ enum { ERR_ROW0 = 1, ERR_ROWN = 2, ERR_ROWDEC = 4, ERR_ROWBIG = 8, ERR_COL = 16,
 // the same, and the searches by word, which take them together, do less than
 // those by snapshot. ms of ten rounds, by snapshot and by word: 8,000 nodes of ten
 // arcs, R = 64: p = 0.8 46 and 55, 0.9 49 and 44, 1 51 and 27; 20,000 nodes of
-// three arcs, R = 256: p = 0.8 577 and 946, 0.9 695 and 644, 1 797 and 186.
+// three arcs, R = 256: p = 0.8 577 and 946, 0.9 695 and 644, 1 797 and 186. (Thin
+// graphs break up all the same: a path of 20,000 nodes at p = 0.99, R = 64, takes
+// 117 ms by snapshot and 156 by word.)
 constexpr float P_SURE = 0.9f;
+constexpr uint64_t SURE_ARCS = 2;   // per node
 
 // A lane's error flags into err[0], and the arcs of a wavefront none of which is
 // below P_SURE into err[1], which has all arcs at the end if none is: graphs of
@@ -1979,7 +1982,7 @@ static int validate(const im_graph *g, im_workspace *ws, hipStream_t s, uint32_t
     if (e & (ERR_ROWDEC | ERR_ROWBIG)) return im_fail(IM_EINVAL, "row_ptr is not non-decreasing within [0, m]");
     if (e & ERR_COL) return im_fail(IM_EINVAL, "col entry >= n");
     if (e & ERR_PROB) return im_fail(IM_EINVAL, "prob outside [0, 1] or NaN");
-    ws->sure = g->m && ws->host_err[1] == g->m;
+    ws->sure = ws->host_err[1] == g->m && g->m >= SURE_ARCS * (uint64_t)g->n && g->m;
     return IM_OK;
 }
 
@@ -4694,7 +4697,7 @@ static int batch_setup(const im_instance *inst, uint32_t count, bool need_out, i
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(ws->host_err, ws->err, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    ws->sure = M && ws->host_err[1] == M;
+    ws->sure = ws->host_err[1] == M && M >= SURE_ARCS * N && M;
     if (*ws->host_err)
         return im_fail(IM_EINVAL, "a batch instance failed validation (flags 0x%x)", *ws->host_err);
     for (int d = 0; d < 2; d++) reserve_sparse(ws, d, (uint32_t)N, M, Rmax);

@@ -60,3 +60,13 @@ def test_rounds_of_sure_arcs(im, low, by_word):
         assert _lists((plan.seeds, plan.gains)) == ref
         im.select(dh, 130, 3, 5, ws=ws)   # eager work between the replays
     plan.close()
+
+
+@pytest.mark.parametrize("m,by_word", [(2399, False), (2400, True)])
+def test_thin_graphs_stay_by_snapshot(im, m, by_word):
+    g = _graph(1200, m, 73, None)
+    s_ref, g_ref, _, _ = oracle.select_du(g.row_ptr, g.col, g.prob, 65, 5, 4)
+    ws = im.Workspace()
+    seeds, gains, _ = im.select(im.Graph.from_numpy(g.row_ptr, g.col, g.prob, device="cuda:0"), 65, 5, 4, ws=ws)
+    assert _lists((seeds, gains)) == [s_ref.tolist(), g_ref.tolist()]
+    assert (ws.stats()["reached_rev_t0"] > 0) == by_word
