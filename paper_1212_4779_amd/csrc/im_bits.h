@@ -14,8 +14,8 @@
 // memory), which gives its (node, word) counts.
 // Bound: the two dependent loads of a level (list offsets, listed heads), times
 // the levels, over the searches that the bitmaps leave room for (13 per CU at
-// 60,000 nodes): the wavefronts wait nine tenths of their time, and taking the
-// L2 misses out (lists of eight snapshots per XCD) did not change it while a
+// 60,000 nodes): the wavefronts wait three quarters of their time, and taking
+// the L2 misses out (lists of eight snapshots per XCD) did not change it while a
 // workgroup still ended its tasks one by one. All 64 frontiers of a task in one
 // LDS table, level by level, were slower too (27 -> 28 to 46 ms).
 // Where the snapshots do share their nodes (supercritical graphs), one search
